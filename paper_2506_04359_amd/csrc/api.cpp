@@ -89,6 +89,8 @@ struct DeviceTables {
   int32_t* tile_rec = nullptr;
   uint32_t* lists = nullptr;
   int32_t* win_order = nullptr;
+  ChunkRec* chunk_rec = nullptr;
+  WinDev* win_rec = nullptr;
   int cls_begin[kClasses + 1] = {0, 0, 0, 0, 0};
   int cls_win_begin[kClasses + 1] = {0, 0, 0, 0, 0};
   int cls_win_nf[kClasses] = {0, 0, 0, 0};
@@ -178,6 +180,8 @@ ba_status upload_tables(ba_batch_s* b, int which, int tp, int chunk_obs) {
     d.chunk_end = t.win_chunk_begin[i + 1];
     d.sum_off = so;
     d.sum_groups = sum_groups(d.chunk_end - d.chunk_begin);
+    d.self = (int32_t)i;
+    d.part_off = d.chunk_end > d.chunk_begin ? t.chunk_part_off[d.chunk_begin] : 0;
     so += (int32_t)partial_elems(w.n_free);
     po += w.n_poses;
     lo += w.n_points;
@@ -185,7 +189,38 @@ ba_status upload_tables(ba_batch_s* b, int which, int tp, int chunk_obs) {
     oo += (int32_t)w.n_obs;
     pa += (int32_t)w.n_pairs();
   }
+  std::vector<WinDev> wrec;
+  for (int32_t i : t.win_order) wrec.push_back(wd[i]);
+  std::vector<ChunkRec> crec;
+  for (int32_t c : t.chunk_order) {
+    const WinDev& w = wd[t.chunk_window[c]];
+    ChunkRec r{};
+    r.chunk = c;
+    r.wi = w.self;
+    r.t0 = t.chunk_tile_begin[c];
+    r.t1 = t.chunk_tile_begin[c + 1];
+    r.n_poses = w.n_poses;
+    r.n_cams = w.n_cams;
+    r.n_free = w.n_free;
+    r.pose_off = w.pose_off;
+    r.point_off = w.point_off;
+    r.cam_off = w.cam_off;
+    r.obs_off = w.obs_off;
+    r.part_off = t.chunk_part_off[c];
+    r.chunk_begin = w.chunk_begin;
+    r.chunk_end = w.chunk_end;
+    auto tile = [&](int32_t k, int4& a, int4& bb) {
+      if (k >= r.t1) return;
+      std::memcpy(&a, &t.tile_rec[8 * (size_t)k], sizeof(int4));
+      std::memcpy(&bb, &t.tile_rec[8 * (size_t)k + 4], sizeof(int4));
+    };
+    tile(r.t0, r.ta0, r.tb0);
+    tile(r.t0 + 1, r.ta1, r.tb1);
+    crec.push_back(r);
+  }
   Blob blob;
+  const size_t o_cr = blob.add(crec);
+  const size_t o_wr = blob.add(wrec);
   const size_t o_win = blob.add(wd);
   const size_t o_tile = blob.add(t.tile_lm_begin);
   const size_t o_cw = blob.add(t.chunk_window);
@@ -219,6 +254,8 @@ ba_status upload_tables(ba_batch_s* b, int which, int tp, int chunk_obs) {
   D.chunk_obs = chunk_obs;
   D.n_chunks = t.n_chunks();
   D.part_elems = t.part_elems;
+  D.chunk_rec = (ChunkRec*)((char*)mem + o_cr);
+  D.win_rec = (WinDev*)((char*)mem + o_wr);
   D.win = (WinDev*)((char*)mem + o_win);
   D.tile_lm_begin = (int32_t*)((char*)mem + o_tile);
   D.chunk_window = (int32_t*)((char*)mem + o_cw);
@@ -476,6 +513,8 @@ DevSettings dev_settings(const ba_settings* s) {
 
 DevTiles dev_tiles(const DeviceTables& t) {
   DevTiles d;
+  d.chunk_rec = t.chunk_rec;
+  d.win_rec = t.win_rec;
   d.tile_lm_begin = t.tile_lm_begin;
   d.chunk_window = t.chunk_window;
   d.chunk_tile_begin = t.chunk_tile_begin;

@@ -32,7 +32,23 @@ struct WinDev {
   int32_t pose_off, point_off, cam_off, obs_off;   // first pose / landmark / camera / observation
   int32_t pair_off, chunk_begin, chunk_end, sum_off;   // sum_off: summed system in the workspace
   int32_t sum_groups;   // chunk groups of k_sum (see sum_groups())
+  int32_t self;         // the window's index
+  int64_t part_off;     // first chunk's partial
 };
+
+// Everything a workgroup of the chunk kernels needs to know about its chunk and
+// its window, in one 128-byte read: with the fields looked up in their own
+// tables (order -> window -> its record -> tile record) a workgroup's first
+// pair records were five dependent reads away, about 0.7 us each.
+struct ChunkRec {
+  int32_t chunk, wi, t0, t1;                       // chunk, window, tiles
+  int32_t n_poses, n_cams, n_free, pose_off;       // of the window
+  int32_t point_off, cam_off, obs_off, pad;
+  int64_t part_off;                                // the chunk's partial
+  int32_t chunk_begin, chunk_end;                  // the window's chunks
+  int4 ta0, tb0, ta1, tb1;                         // tile records of t0 and t0 + 1 (zeros when past the end)
+};
+static_assert(sizeof(ChunkRec) == 128, "chunk record is two cache lines of 64 bytes");
 
 // Per-window LM state, in the workspace.
 struct WinState {
@@ -62,6 +78,8 @@ struct DevPlan {
 };
 
 struct DevTiles {
+  const ChunkRec* chunk_rec;      // per chunk, grouped by size class (as chunk_order)
+  const WinDev* win_rec;          // per window, grouped by size class (as win_order)
   const int32_t* chunk_order;     // chunks grouped by size class
   const int32_t* win_order;       // windows grouped by size class
   const int32_t* pair_rec;        // 4 per pair position (thread order of its tile)

@@ -431,15 +431,11 @@ struct ChunkLds {
   static constexpr int kCam = 32 * 16;    // doubles
 };
 
-// Window caches: poses (current state), camera table, free slots.
-__device__ __forceinline__ void load_window(const DevPlan& P, const WinDev& W,
-                                            const double* __restrict__ poses, double* sPose,
-                                            double* sCam, int* sFree) {
+// Window caches of pass B: poses (current state) and camera table.
+__device__ __forceinline__ void load_window(const DevPlan& P, const ChunkRec& W, const double* __restrict__ poses,
+                                            double* sPose, double* sCam) {
   for (int k = threadIdx.x; k < W.n_poses * 12; k += blockDim.x) sPose[k] = poses[k];
-  for (int k = threadIdx.x; k < W.n_cams * 16; k += blockDim.x)
-    sCam[k] = P.cam[16 * W.cam_off + k];
-  for (int k = threadIdx.x; k < W.n_poses; k += blockDim.x)
-    sFree[k] = P.free_slot[W.pose_off + k];
+  for (int k = threadIdx.x; k < W.n_cams * 16; k += blockDim.x) sCam[k] = P.cam[16 * W.cam_off + k];
 }
 
 // ---------------------------------------------------------------------------
@@ -514,15 +510,6 @@ __device__ __forceinline__ void run_sums(Real* v, int key) {
   run_step<Real, N, 0x143, 0xc>(v, key);   // row_bcast:31 into rows 2 and 3
 }
 
-// Rows of one target block per Schur work unit in pass A (1, 2, 3 or 6): two
-// rows read 8 Z rows per product for 36 FMAs and keep enough units per tile to
-// balance the threads (measured faster than three or six rows per unit).
-#ifndef BA_ROWS_PER_UNIT
-#define BA_ROWS_PER_UNIT 2
-#endif
-constexpr int kRowsPerUnit = BA_ROWS_PER_UNIT;
-static_assert(6 % kRowsPerUnit == 0, "rows per unit must divide 6");
-
 // Per-pose sums of pass A: U - Z sigma Z^T (21, upper), reduced rhs (6), diag(U) (6).
 constexpr int kPoseSums = 33;
 
@@ -592,12 +579,66 @@ struct PassALds {
   static constexpr int NW = TP / 64;
   static size_t bytes(int np, int nc, int nf, int list_bytes, bool adj) {
     const size_t nblk = (size_t)nf * (nf + 1) / 2;
-    return (size_t)(nc * 16 + np * 12 + 16) * sizeof(double) + (64 + (adj ? TP : 0) + 4 + 8) * sizeof(int) +
+    return (size_t)(nc * 16 + np * 12 + 16) * sizeof(double) + ((adj ? TP : 0) + 4 + 8) * sizeof(int) +
            (nblk * kBS + 12 * (size_t)nf + (size_t)2 * NW * kPoseSums) * sizeof(Real) + 16 +
            ((size_t)TP * ZRow<Real>::S + (size_t)(TP / 2) * 12) * sizeof(Real) + 16 +
            ((size_t)list_bytes + 15) / 16 * 16;
   }
 };
+
+// Phase 4 of pass A for a tile of few target blocks: a unit owns CG entries of one
+// row of a block and sums -Z_a[r] sigma Z_c^T over the block's products in list
+// order (the same chain of FMAs per entry as the 2 x 6 units).  Two register sets
+// in turn, so that a unit waits for LDS once per product; at its end the reads are
+// clamped to the last product (read, not used).  LM only (sigma = 1).
+template <typename Real, int TP, int CG>
+__device__ __forceinline__ void schur_fine(const uint32_t* sLst, int nseg, const Real* sPZ, Real* sS) {
+  constexpr int kZS = ZRow<Real>::S, ZR = ZRow<Real>::R;
+  constexpr int NC = 6 / CG, UPS = 6 * NC;
+  const uint16_t* sProd = reinterpret_cast<const uint16_t*>(sLst + nseg);
+  const int u = threadIdx.x;   // one round: the caller checked nseg UPS <= TP
+  if (u >= nseg * UPS) return;
+  const uint32_t wd = sLst[u / UPS];
+  const int row = (u % UPS) / NC, col = (u % NC) * CG;
+  const int blk = wd & 1023, start = (wd >> 10) & 8191, len = wd >> 23;
+  if (len == 0) return;
+  Real acc[CG], a0[3], z0[CG][3], a1[3], z1[CG][3];
+#pragma unroll
+  for (int c = 0; c < CG; ++c) acc[c] = (Real)0;
+  auto load = [&](uint32_t pp, Real (&a)[3], Real (&z)[CG][3]) {
+    const Real* Za = sPZ + kZS * (pp & 255) + ZR * row;
+    const Real* Zc = sPZ + kZS * (pp >> 8) + ZR * col;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) a[m] = Za[m];
+#pragma unroll
+    for (int c = 0; c < CG; ++c)
+#pragma unroll
+      for (int m = 0; m < 3; ++m) z[c][m] = Zc[ZR * c + m];
+  };
+  auto madd = [&](const Real (&a)[3], const Real (&z)[CG][3]) {
+#pragma unroll
+    for (int c = 0; c < CG; ++c)
+#pragma unroll
+      for (int m = 0; m < 3; ++m) acc[c] = fma(a[m], z[c][m], acc[c]);
+  };
+  const int end = start + len, last = end - 1;
+  uint32_t i1 = sProd[min(start + 1, last)];
+  load(sProd[start], a0, z0);
+  for (int k = start;; k += 2) {
+    const uint32_t i2 = sProd[min(k + 2, last)];
+    load(i1, a1, z1);
+    madd(a0, z0);
+    if (k + 1 >= end) break;
+    const uint32_t i3 = sProd[min(k + 3, last)];
+    load(i2, a0, z0);
+    madd(a1, z1);
+    if (k + 2 >= end) break;
+    i1 = i3;
+  }
+  Real* B = sS + kBS * blk + 6 * row + col;
+#pragma unroll
+  for (int c = 0; c < CG; ++c) B[c] -= acc[c];
+}
 
 // FP32: at least two waves per SIMD (the register budget that LDS allows);
 // FP64 runs one workgroup per CU anyway.
@@ -609,12 +650,23 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
   constexpr int NW = TP / 64;
   constexpr int LR = ListRegs<TP>::N;
   constexpr int kZS = ZRow<Real>::S, ZR = ZRow<Real>::R;
-  const int chunk = T.chunk_order[cls_begin + xcd_chunk(blockIdx.x, gridDim.x)];
-  const int wi = T.chunk_window[chunk];
-  const WinDev W = P.win[wi];
-  const WinState& st = K.state[wi];
-  if (!ADJ && st.frozen) return;   // the whole work item (every thread of it) returns
+  const ChunkRec W = T.chunk_rec[cls_begin + xcd_chunk(blockIdx.x, gridDim.x)];
+  const int chunk = W.chunk;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int4* trec = reinterpret_cast<const int4*>(T.tile_rec);
+  const int4* prec = reinterpret_cast<const int4*>(T.pair_rec);
+  // The global data of a tile is fetched one tile ahead, in three steps: tile
+  // records two tiles ahead, pair records one tile ahead (both issued during
+  // tile t - 1), and the pairs' points and first observations at the start of
+  // tile t - 1 (their pair records are there by then).  The first tiles' records
+  // come with the chunk's.
+  const int t0 = W.t0, t1 = W.t1;
+  int4 ta = W.ta0, tb = W.tb0, nta = W.ta1, ntb = W.tb1;
+  int4 rec = make_int4(0, 0, 0, -1), nrec = rec;
+  if (tid < ta.y) rec = prec[ta.x + tid];
+  if (tid < nta.y) nrec = prec[nta.x + tid];
+  const WinState& st = K.state[W.wi];
+  if (!ADJ && st.frozen) return;   // the whole work item (every thread of it) returns
   const int cur = ADJ ? 0 : st.cur;
   const double lam = ADJ ? 0.0 : st.lambda;
   const double* poses = (cur ? K.poses_b : U.poses) + 12 * W.pose_off;
@@ -624,8 +676,7 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
   double* sCam = reinterpret_cast<double*>(smem);             // nc * 16
   double* sPose = sCam + D.nc * 16;                           // np * 12
   double* sRed = sPose + D.np * 12;                           // 16
-  int* sFree = reinterpret_cast<int*>(sRed + 16);             // 64
-  int* sPL = sFree + 64;                                      // TP (adjoint): pair -> tile-local landmark
+  int* sPL = reinterpret_cast<int*>(sRed + 16);               // TP (adjoint): pair -> tile-local landmark
   int* sFlag = sPL + (ADJ ? TP : 0);                          // 4
   int* sBndSlot = sFlag + 4;                                  // 8: slot of each edge run (or -1)
   Real* sS = reinterpret_cast<Real*>(sBndSlot + 8);           // nblk * kBS
@@ -641,33 +692,6 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
   Real* sLF = sPZ + TP * kZS;                                 // TP / 2 * 12: landmark factors
   const int oLst = ((int)(reinterpret_cast<unsigned char*>(sLF + (TP / 2) * 12) - smem) + 15) & ~15;
   uint32_t* sLst = reinterpret_cast<uint32_t*>(smem + oLst);  // product lists (stored in phase 1)
-
-  const int4* trec = reinterpret_cast<const int4*>(T.tile_rec);
-  const int4* prec = reinterpret_cast<const int4*>(T.pair_rec);
-  const int t0 = T.chunk_tile_begin[chunk], t1 = T.chunk_tile_begin[chunk + 1];
-  // The global data of a tile is fetched one tile ahead, in three steps:
-  // tile records two tiles ahead, pair records one tile ahead (both issued
-  // during tile t - 1), and the pairs' points and first observations at the
-  // start of tile t - 1 (their pair records are there by then).
-  int4 ta = make_int4(0, 0, 0, 0), tb = make_int4(0, 0, 0, 0), nta = ta, ntb = tb;
-  int4 rec = make_int4(0, 0, 0, -1), nrec = rec;
-  if (t0 < t1) {
-    ta = trec[2 * t0];
-    tb = trec[2 * t0 + 1];
-    if (tid < ta.y) rec = prec[ta.x + tid];
-  }
-  if (t0 + 1 < t1) {
-    nta = trec[2 * (t0 + 1)];
-    ntb = trec[2 * (t0 + 1) + 1];
-    if (tid < nta.y) nrec = prec[nta.x + tid];
-  }
-
-  for (int k = tid; k < W.n_cams * 16; k += TP) sCam[k] = P.cam[16 * W.cam_off + k];
-  for (int k = tid; k < W.n_poses * 12; k += TP) sPose[k] = poses[k];
-  for (int k = tid; k < W.n_poses; k += TP) sFree[k] = P.free_slot[W.pose_off + k];
-  for (int k = tid; k < nblk * kBS + 2 * nS; k += TP) sS[k] = (Real)0;
-  if (tid == 0) sFlag[0] = 0;
-  __syncthreads();
 
   // a pair's point and first observation
   double px = 0, py = 0, pz = 0;
@@ -689,6 +713,17 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
     wo = K.w ? wv : (Real)1;
   };
   if (t0 < t1) fetch_pair(rec, tid < ta.y, px, py, pz, du0, dv0, wo0, cam0);
+
+  for (int k = tid; k < W.n_cams * 16; k += TP) sCam[k] = P.cam[16 * W.cam_off + k];
+  for (int k = tid; k < W.n_poses * 12; k += TP) sPose[k] = poses[k];
+  {
+    // the partial starts 16 bytes aligned; the last store may run into sBnd,
+    // which is written before it is read
+    const int nz = (int)(((nblk * kBS + 2 * nS) * sizeof(Real) + 15) / 16);
+    for (int k = tid; k < nz; k += TP) reinterpret_cast<float4*>(sS)[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  if (tid == 0) sFlag[0] = 0;
+  __syncthreads();
 
   double cost = 0.0, gmax = 0.0;
   for (int t = t0; t < t1; ++t) {
@@ -935,13 +970,26 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
       if (cur >= 0) pose_sum_add1<Real, ADJ>(sS, sB, sD, nf, cur, k, acc);
     }
 
-    // ---- phase 4: Schur blocks.  Unit (segment, rows r0..r0+kRowsPerUnit-1)
-    // owns those rows of one off-diagonal target block for this tile: it sums
-    // -Z_a[r] sigma Z_c^T over the segment's products in registers and
-    // updates its rows of the partial once.
+    // ---- phase 4: Schur blocks.  Unit (segment, rows r0, r0 + 1) owns those rows
+    // of one off-diagonal target block for this tile: it sums -Z_a[r] sigma Z_c^T
+    // over the segment's products in registers and updates its rows of the partial
+    // once.  A tile of few target blocks has long lists of products in each, which
+    // one unit sums in series: as long as one round holds them, finer units shorten
+    // that chain (a product of a one-entry unit is 6 LDS reads and 3 FMAs, of a
+    // 2 x 6 unit 24 and 36; more LDS traffic in all, which bounds the phase once
+    // the threads are busy: at 36 blocks 1 x 6 and 2 x 6 units measure alike).
+    // FP64, 10 attempts, 2 x 6 units against these: 3 free poses 446 -> 409 us a
+    // solve, 6 to 8 free poses 122 -> 117 us an attempt.  The adjoint has one
+    // pass and keeps the coarse units.
+    if (!ADJ && nseg * 36 <= TP) {
+      schur_fine<Real, TP, 1>(sLst, nseg, sPZ, sS);
+    } else if (!ADJ && nseg * 12 <= TP) {
+      schur_fine<Real, TP, 3>(sLst, nseg, sPZ, sS);
+    } else if (!ADJ && nseg * 6 <= TP) {
+      schur_fine<Real, TP, 6>(sLst, nseg, sPZ, sS);
+    } else {
     const uint16_t* sProd = reinterpret_cast<const uint16_t*>(sLst + nseg);
-    {
-      constexpr int RG = kRowsPerUnit, UPS = 6 / RG;
+      constexpr int RG = 2, UPS = 6 / RG;
       const int nun = nseg * UPS;
       for (int u = tid; u < nun; u += TP) {
         const uint32_t wd = sLst[u / UPS];
@@ -1028,7 +1076,8 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
   }
 
   // ---- chunk partial out (the last tile's phase 4 ended with a barrier)
-  Real* part = K.part + T.chunk_part_off[chunk];
+  Real* part = K.part + W.part_off;
+#pragma unroll 4
   for (int k = tid; k < nblk * kBS + 2 * nS; k += TP) part[k] = sS[k];
   // the cost sum and the landmark-gradient maximum in one reduction
   double gm = gmax;
@@ -1213,9 +1262,8 @@ __device__ __forceinline__ void trail_item(double* sS, double* sB, int k, int nf
 template <typename Real>
 __global__ __launch_bounds__(256) void k_sum(DevPlan P, DevTiles T, DevWork<Real> K, int wbase) {
   __shared__ double sG[kSumE][256];
-  const int wi = T.win_order[wbase + blockIdx.x];
-  if (K.state[wi].frozen) return;
-  const WinDev W = P.win[wi];
+  const WinDev W = T.win_rec[wbase + blockIdx.x];
+  if (K.state[W.self].frozen) return;
   const int nf = W.n_free, nblk = nf * (nf + 1) / 2;
   const int ne = nblk * kBS + 12 * nf;
   const int G = W.sum_groups, L = 256 / G;
@@ -1223,7 +1271,7 @@ __global__ __launch_bounds__(256) void k_sum(DevPlan P, DevTiles T, DevWork<Real
   const int e0 = blockIdx.y * (L * kSumE);
   if (e0 >= ne) return;
   const int nch = W.chunk_end - W.chunk_begin;
-  const Real* base = K.part + (nch > 0 ? T.chunk_part_off[W.chunk_begin] : 0);
+  const Real* base = K.part + W.part_off;
   // loads are unconditional (entries past the end read the last entry and
   // are dropped), so a step's 16 loads are all in flight before the first
   // is waited for
@@ -1280,8 +1328,8 @@ template <typename Real, int NT, bool ADJ>
 __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Real> K, DevUser U,
                                                DevSettings S, int it, int wbase) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int wi = T.win_order[wbase + blockIdx.x];
-  const WinDev W = P.win[wi];
+  const WinDev W = T.win_rec[wbase + blockIdx.x];
+  const int wi = W.self;
   WinState& st = K.state[wi];
   const int tid = threadIdx.x;
   const int nf = W.n_free, nblk = nf * (nf + 1) / 2, nS = 6 * nf;
@@ -1572,11 +1620,16 @@ template <typename Real, int TP, bool ADJ>
 __global__ __launch_bounds__(TP) void k_pass_b(DevPlan P, DevTiles T, DevWork<Real> K, DevUser U,
                                                DevSettings S, int it, int cbase) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int chunk = T.chunk_order[cbase + xcd_chunk(blockIdx.x, gridDim.x)];
-  const int wi = T.chunk_window[chunk];
-  const WinDev W = P.win[wi];
-  const WinState& st = K.state[wi];
+  const ChunkRec W = T.chunk_rec[cbase + xcd_chunk(blockIdx.x, gridDim.x)];
+  const int chunk = W.chunk, wi = W.wi;
   const int tid = threadIdx.x;
+  const int4* trec = reinterpret_cast<const int4*>(T.tile_rec);
+  const int4* prec = reinterpret_cast<const int4*>(T.pair_rec);
+  const int t0 = W.t0, t1 = W.t1;
+  int4 ta = W.ta0;
+  int4 rec = make_int4(0, 0, 0, -1);
+  if (tid < ta.y) rec = prec[ta.x + tid];
+  const WinState& st = K.state[wi];
   if (!ADJ && (st.fail || st.frozen)) {
     if (tid == 0) {
       K.part_cost_b[chunk] = 0.0;
@@ -1599,27 +1652,9 @@ __global__ __launch_bounds__(TP) void k_pass_b(DevPlan P, DevTiles T, DevWork<Re
   double* sDp = sPoseC + ChunkLds::kPose;          // kDpStride
   double* sLP = sDp + kDpStride;                   // TP * 3 (candidate point / a_l)
   double* sRed = sLP + 3 * TP;                     // 16
-  int* sFree = reinterpret_cast<int*>(sRed + 16);  // 64
-  int* sFlag = sFree + 64;                         // 4
+  int* sFlag = reinterpret_cast<int*>(sRed + 16);  // 4
   Real* sPV = reinterpret_cast<Real*>(sFlag + 4);  // TP * 12: V, g, W^T dp per pair
 
-  load_window(P, W, poses, sPose, sCam, sFree);
-  if (!ADJ)
-    for (int k = tid; k < W.n_poses * 12; k += TP) sPoseC[k] = cposes[k];
-  for (int k = tid; k < nS; k += TP) sDp[k] = K.dp[kDpStride * wi + k];
-  if (tid == 0) sFlag[0] = 0;
-  __syncthreads();
-
-  double cost = 0.0, smax = 0.0;
-  const int t0 = T.chunk_tile_begin[chunk], t1 = T.chunk_tile_begin[chunk + 1];
-  const int4* trec = reinterpret_cast<const int4*>(T.tile_rec);
-  const int4* prec = reinterpret_cast<const int4*>(T.pair_rec);
-  int4 ta = make_int4(0, 0, 0, 0);
-  int4 rec = make_int4(0, 0, 0, -1);
-  if (t0 < t1) {
-    ta = trec[2 * t0];
-    if (tid < ta.y) rec = prec[ta.x + tid];
-  }
   // A tile's global data is fetched during the tile before it: each pair's
   // point and first observation (after the pair records arrive, behind phase
   // 3), each landmark's pair range and point (behind the whole tile).
@@ -1651,6 +1686,14 @@ __global__ __launch_bounds__(TP) void k_pass_b(DevPlan P, DevTiles T, DevWork<Re
     if (tid < ta.y) fetch_pair(rec, px, py, pz, du0, dv0, wo0, cam0);
     if (tid < ta.w) fetch_lm(ta.z + tid, lb0, lb1, lx, ly, lz);
   }
+  load_window(P, W, poses, sPose, sCam);
+  if (!ADJ)
+    for (int k = tid; k < W.n_poses * 12; k += TP) sPoseC[k] = cposes[k];
+  for (int k = tid; k < nS; k += TP) sDp[k] = K.dp[kDpStride * wi + k];
+  if (tid == 0) sFlag[0] = 0;
+  __syncthreads();
+
+  double cost = 0.0, smax = 0.0;
   for (int t = t0; t < t1; ++t) {
     // the tile's pairs in the plan's thread order; q is the pair's index in
     // landmark order (the layout of the per-pair LDS rows)
@@ -1848,8 +1891,8 @@ __global__ void k_accept(DevPlan P, DevTiles T, DevWork<Real> K, DevUser U, DevS
   const int i = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (i >= nwin) return;
-  const int wi = T.win_order[wbase + i];
-  const WinDev W = P.win[wi];
+  const WinDev W = T.win_rec[wbase + i];
+  const int wi = W.self;
   int depth = 0;
   double F = 0.0;
   wave_chunk_sums(K.part_flag_b, K.part_cost_b, W.chunk_begin, W.chunk_end, true, lane, depth, F);
@@ -1957,7 +2000,7 @@ size_t pass_a_lds(int np, int nc, int nf, int list_bytes, bool adj) {
 template <typename Real, int TP>
 size_t pass_b_lds() {
   return (2 * ChunkLds::kPose + ChunkLds::kCam + kDpStride + 3 * TP + 16) * sizeof(double) +
-         (64 + 4) * sizeof(int) + (size_t)TP * 12 * sizeof(Real);
+         4 * sizeof(int) + (size_t)TP * 12 * sizeof(Real);
 }
 
 // The reduce kernel's LDS: the reduced system of the largest window.
