@@ -1343,25 +1343,9 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
   const int ne = nblk * kBS + 2 * nS;
   if (!ADJ && st.frozen) return;
   {
-    // chunk flags and costs (wave 0)
-    const bool need_cost = !ADJ && it == 0;
-    int f = 0;
-    double F = 0.0;
-    if (tid < 64) wave_chunk_sums(K.part_flag_a, K.part_cost_a, c0, c1, need_cost, tid, f, F);
-    if (tid == 0) {
-      sFail[0] = f;
-      if (need_cost) {
-        F *= 0.5;
-        if (K.vi_cost_a) F += K.vi_cost_a[wi];
-        st.cost = F;
-        st.init_cost = F;
-        if (!isfinite(F)) st.status = 1;
-      }
-    }
-  }
-  {
-    // eight loads in flight per thread (the system is up to 160 KB); the
-    // blocks move from the summed partials' stride kBS to the dense kRS
+    // the summed system, eight loads in flight per thread (up to 160 KB); the
+    // blocks move from the summed partials' stride kBS to the dense kRS.  The
+    // first round's loads go out before the chunk flags' chain of loads (wave 0).
     const double* src = K.ssum + W.sum_off;
     const int nb = nblk * kBS;
     constexpr int B = 8;
@@ -1370,7 +1354,23 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
 #pragma unroll
       for (int b = 0; b < B; ++b) {
         const int e = base + tid + b * NT;
-        v[b] = e < ne ? src[e] : 0.0;
+        v[b] = src[e < ne ? e : ne - 1];
+      }
+      if (base == 0 && tid < 64) {
+        const bool need_cost = !ADJ && it == 0;
+        int f = 0;
+        double F = 0.0;
+        wave_chunk_sums(K.part_flag_a, K.part_cost_a, c0, c1, need_cost, tid, f, F);
+        if (tid == 0) {
+          sFail[0] = f;
+          if (need_cost) {
+            F *= 0.5;
+            if (K.vi_cost_a) F += K.vi_cost_a[wi];
+            st.cost = F;
+            st.init_cost = F;
+            if (!isfinite(F)) st.status = 1;
+          }
+        }
       }
 #pragma unroll
       for (int b = 0; b < B; ++b) {
@@ -1429,8 +1429,8 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
       sS[kRS * blk_index(f, f, nf) + 7 * r] += lam * (d > 1e-9 ? d : 1e-9);
     }
   }
-  __syncthreads();
-  // mirror the diagonal blocks (only their upper triangles were accumulated)
+  // mirror the diagonal blocks (only their upper triangles were accumulated;
+  // their diagonals, damped above, are not touched here)
   for (int e = tid; e < nf * 36; e += NT) {
     const int f = e / 36, r = (e % 36) / 6, c = e % 6;
     if (c < r) {
@@ -1527,42 +1527,47 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
     __syncthreads();
     failed = sFail[0] != 0;
   }
+  // The candidate poses are wave 1's (a window has at most 64 poses): its reads
+  // go out while wave 0 substitutes.
+  int cslot = -1;
+  double Tp[12];
+  const bool cpose = !ADJ && wave == 1 && lane < W.n_poses;
+  if (cpose) {
+    cslot = P.free_slot[W.pose_off + lane];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) Tp[k] = poses[12 * lane + k];
+  }
   if (!failed && wave == 0 && nf > 0) {
     // back substitution R x = y in one wave.  Lane l keeps rows 3 l .. 3 l + 2
     // (all three in block row l / 2), so the rows of block k sit in lanes
-    // 2 k and 2 k + 1 at register positions known at compile time, and x
-    // replaces y there.  A block issues its reads and broadcasts together and
-    // waits for them once; the column reads are waited for only after the
-    // block's serial chain.
+    // 2 k and 2 k + 1 at register positions known at compile time; a lane's y is
+    // not used any more once its block's x is known, so the lanes past it update
+    // theirs with whatever they read.  Two register sets in turn: the next block's
+    // reads are in flight while a block's chain runs.
     double y[3];
 #pragma unroll
     for (int t = 0; t < 3; ++t) y[t] = 3 * lane + t < nS ? sB[3 * lane + t] : 0.0;
-    for (int k = nf - 1; k >= 0; --k) {
+    auto fetch = [&](int k, double (&dku)[15], double (&iv)[6], double (&bv)[18]) {
       const double* Dk = sS + kRS * blk_index(k, k, nf);
-      double dku[15], iv[6], yv[6], bv[18];
 #pragma unroll
       for (int i = 0, q = 0; i < 6; ++i)
 #pragma unroll
         for (int m = i + 1; m < 6; ++m, ++q) dku[q] = Dk[6 * i + m];
 #pragma unroll
       for (int i = 0; i < 6; ++i) iv[i] = sInv[6 * k + i];
-      {
-        // lanes at or past block row k are not updated; they read block row 0
-        const int l = lane < 2 * k ? lane : 0;
-        const double* B = sS + kRS * blk_index(l >> 1, k, nf) + 18 * (l & 1);
+      const int l = lane < 2 * k ? lane : 0;   // lanes at or past block row k read block row 0
+      const double* B = sS + kRS * blk_index(l >> 1, k, nf) + 18 * (l & 1);
 #pragma unroll
-        for (int m = 0; m < 18; m += 2) {
-          const double2 b2 = *reinterpret_cast<const double2*>(B + m);
-          bv[m] = b2.x;
-          bv[m + 1] = b2.y;
-        }
+      for (int m = 0; m < 18; m += 2) {
+        const double2 b2 = *reinterpret_cast<const double2*>(B + m);
+        bv[m] = b2.x;
+        bv[m + 1] = b2.y;
       }
+    };
+    auto solve = [&](int k, const double (&dku)[15], const double (&iv)[6], const double (&bv)[18]) {
+      double yv[6], x[6];
 #pragma unroll
       for (int i = 0; i < 6; ++i) yv[i] = wave_bcast(y[i % 3], 2 * k + i / 3);
-      lds_fence(dku);
-      lds_fence(iv);
-      lds_fence(yv);
-      double x[6];
 #pragma unroll
       for (int i = 5; i >= 0; --i) {
         double v = yv[i];
@@ -1572,16 +1577,28 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
         for (int m = i + 1; m < 6; ++m) v -= dku[q0 + m - i - 1] * x[m];
         x[i] = v * iv[i];
       }
+      if (lane == 0) {
+#pragma unroll
+        for (int i = 0; i < 6; i += 2) *reinterpret_cast<double2*>(sB + 6 * k + i) = make_double2(x[i], x[i + 1]);
+      }
 #pragma unroll
       for (int t = 0; t < 3; ++t) {
-        const double d = bv[6 * t] * x[0] + bv[6 * t + 1] * x[1] + bv[6 * t + 2] * x[2] +
-                         bv[6 * t + 3] * x[3] + bv[6 * t + 4] * x[4] + bv[6 * t + 5] * x[5];
-        y[t] = lane < 2 * k ? y[t] - d : (lane == 2 * k ? x[t] : (lane == 2 * k + 1 ? x[3 + t] : y[t]));
-      }
-    }
+        double d = fma(bv[6 * t], x[0], bv[6 * t + 1] * x[1]);
 #pragma unroll
-    for (int t = 0; t < 3; ++t)
-      if (3 * lane + t < nS) sB[3 * lane + t] = y[t];
+        for (int i = 2; i < 6; ++i) d = fma(bv[6 * t + i], x[i], d);
+        y[t] -= d;
+      }
+    };
+    double d0[15], i0[6], b0[18], d1[15], i1[6], b1[18];
+    fetch(nf - 1, d0, i0, b0);
+    for (int k = nf - 1;; k -= 2) {
+      fetch(k > 0 ? k - 1 : 0, d1, i1, b1);
+      solve(k, d0, i0, b0);
+      if (k == 0) break;
+      fetch(k > 1 ? k - 2 : 0, d0, i0, b0);
+      solve(k - 1, d1, i1, b1);
+      if (k == 1) break;
+    }
   }
   __syncthreads();
   double* dp = K.dp + kDpStride * wi;
@@ -1593,21 +1610,21 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
   if (tid == 0) st.fail = failed ? 1 : 0;
   if (failed) return;
   // candidate poses into the other buffer
-  double* cand = (st.cur == 0 ? K.poses_b : U.poses) + 12 * W.pose_off;
-  for (int i = tid; i < W.n_poses; i += NT) {
-    const int f = P.free_slot[W.pose_off + i];
-    const double* Tp = poses + 12 * i;
-    double* Tc = cand + 12 * i;
-    if (f < 0) {
-      for (int k = 0; k < 12; ++k) Tc[k] = Tp[k];
-      continue;
-    }
-    double D[12];
-    exp_se3(sB + 6 * f, D);
-    for (int a = 0; a < 3; ++a) {
-      for (int b = 0; b < 3; ++b)
-        Tc[4 * a + b] = D[4 * a] * Tp[b] + D[4 * a + 1] * Tp[4 + b] + D[4 * a + 2] * Tp[8 + b];
-      Tc[4 * a + 3] = D[4 * a] * Tp[3] + D[4 * a + 1] * Tp[7] + D[4 * a + 2] * Tp[11] + D[4 * a + 3];
+  if (!cpose) return;
+  double* Tc = (st.cur == 0 ? K.poses_b : U.poses) + 12 * (W.pose_off + lane);
+  if (cslot < 0) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) Tc[k] = Tp[k];
+    return;
+  }
+  double D[12];
+  exp_se3(sB + 6 * cslot, D);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const double v = fma(D[4 * a + 2], Tp[8 + b], fma(D[4 * a], Tp[b], D[4 * a + 1] * Tp[4 + b]));
+      Tc[4 * a + b] = b < 3 ? v : v + D[4 * a + 3];
     }
   }
 }
