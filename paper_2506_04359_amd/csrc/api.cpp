@@ -435,7 +435,7 @@ Layout layout(const ba_batch_s* b, const DeviceTables& t, size_t real) {
   L.w = take(real * b->n_obs);
   L.poses_b = take(sizeof(double) * 12 * b->n_poses);
   L.points_b = take(sizeof(double) * 3 * b->n_points);
-  L.state = take(sizeof(WinState) * b->wins.size());
+  L.state = take(2 * sizeof(WinState) * b->wins.size());
   L.dp = take(sizeof(double) * kDpStride * b->wins.size());
   int64_t sum_elems = 0;
   for (auto& w : b->wins) sum_elems += partial_elems(w.n_free);
@@ -604,7 +604,11 @@ ba_status launch(ba_batch_s* b, const ba_settings* s, Op op, DevUser U, void* ws
   A.dims.np = b->max_np;
   A.dims.nc = b->max_nc;
   A.list_bytes = t.list_bytes;
-  A.max_cpw = t.max_cpw;
+  // Every workgroup of pass A then reads all of its window's candidate costs: one
+  // round of loads up to 256 chunks, against a launch of its own (stereo window,
+  // 234 chunks, 10 attempts: 777 -> 747 us; mono window, 8 chunks: 361 -> 344).
+  // The timed solve keeps the launch.
+  A.fused = op != Op::Timed && t.max_cpw <= kFusedChunks;
   for (int c = 0; c < kClasses; ++c) A.cls_sum_slices[c] = t.cls_sum_slices[c];
   A.sum_slices = t.sum_slices;
   A.stream = stream;

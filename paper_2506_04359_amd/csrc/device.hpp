@@ -99,7 +99,7 @@ struct DevWork {
   Real* w;                  // weight, NULL when every weight is 1
   double* poses_b;          // second state buffer (candidate / current)
   double* points_b;
-  WinState* state;
+  WinState* state;          // per window, twice (parity of the attempt)
   double* dp;               // per window, kDpStride doubles: the reduced-system solution
   double* ssum;             // per window: the chunk partials summed in FP64
   Real* part;               // chunk partials of S, the reduced rhs and diag(U)
@@ -155,6 +155,7 @@ inline int sum_groups(int n_chunks) {
 }
 inline int sum_slice_entries(int groups) { return 256 / groups * kSumE; }
 
+constexpr int kFusedChunks = 256;   // most chunks of a window whose acceptance is decided in pass A
 constexpr int kSideStreams = 2;   // side streams of the size classes
 
 // Dimensions of the window caches in LDS (largest in the launch).
@@ -175,7 +176,9 @@ struct LaunchArgs {
   int cls_nf[kClasses];          // largest free-pose count of each class
   LdsDims dims;                  // largest pose / camera count of the batch
   int list_bytes;                // largest per-tile product list (segments + products)
-  int max_cpw;                   // largest number of chunks of one window
+  // 1: no launch of its own for the acceptance; pass A of the next attempt (and
+  // the final copy) decide from the chunks' candidate costs
+  int fused;
   int cls_sum_slices[kClasses];  // k_sum workgroups per window of each class
   int sum_slices;                // the same over all windows
   void* stream;                  // hipStream_t

@@ -123,6 +123,54 @@ __device__ __forceinline__ double wave_bcast(double x, int src) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// Exchange of 64-bit values between lane groups: rows 2-3 of a with rows 0-1
+// of b (permlane32), odd rows of a with even rows of b (permlane16).
+__device__ __forceinline__ void swap_rows32(double& a, double& b) {
+  const long long ia = __double_as_longlong(a), ib = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ia, (unsigned)ib, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ia >> 32), (unsigned)(ib >> 32), false, false);
+  a = __longlong_as_double(((long long)hi[0] << 32) | lo[0]);
+  b = __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ void swap_rows16(double& a, double& b) {
+  const long long ia = __double_as_longlong(a), ib = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ia, (unsigned)ib, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ia >> 32), (unsigned)(ib >> 32), false, false);
+  a = __longlong_as_double(((long long)hi[0] << 32) | lo[0]);
+  b = __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+
+// Sum and maximum over the wave in every lane, as an xor butterfly over lane bits
+// 5, 4, 3, 2, 1, 0 adds them: permlane swaps for the rows, then rotations within a
+// row (after step 8 the lanes l and l ^ 8 agree, so a rotation by 4 reads the value
+// of l ^ 4, and so on).  No LDS, so no bpermute latency per step.
+__device__ __forceinline__ double wave_sum(double v) {
+  double a = v, b = v;
+  swap_rows32(a, b);
+  v = a + b;
+  a = b = v;
+  swap_rows16(a, b);
+  v = a + b;
+  v += dpp_r<0x128, 0xf>(v);   // row_ror:8
+  v += dpp_r<0x124, 0xf>(v);
+  v += dpp_r<0x122, 0xf>(v);
+  v += dpp_r<0x121, 0xf>(v);
+  return v;
+}
+__device__ __forceinline__ double wave_max(double v) {
+  double a = v, b = v;
+  swap_rows32(a, b);
+  v = fmax(a, b);
+  a = b = v;
+  swap_rows16(a, b);
+  v = fmax(a, b);
+  v = fmax(v, dpp_r<0x128, 0xf>(v));
+  v = fmax(v, dpp_r<0x124, 0xf>(v));
+  v = fmax(v, dpp_r<0x122, 0xf>(v));
+  v = fmax(v, dpp_r<0x121, 0xf>(v));
+  return v;
+}
+
 // SE(3) exponential of xi = (rho, phi) as a 3x4 [R | t].  The coefficients
 // A = sin(th)/th, B = (1 - cos th)/th^2, C = (th - sin th)/th^3 come from
 // their power series in th^2 below th = 1 (nine terms: the first omitted one

@@ -312,8 +312,7 @@ __device__ __forceinline__ void damp3(Real* V, double lam) {
 // Block-wide sum of a double, deterministic (fixed shuffle tree + fixed order).
 template <int NT>
 __device__ __forceinline__ double block_sum(double v, double* scratch) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  v = wave_sum(v);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (lane == 0) scratch[wv] = v;
   __syncthreads();
@@ -328,11 +327,8 @@ __device__ __forceinline__ double block_sum(double v, double* scratch) {
 // scratch holds 2 NT / 64 doubles.
 template <int NT>
 __device__ __forceinline__ double block_sum_max(double v, double& m, double* scratch) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    v += __shfl_down(v, off, 64);
-    m = fmax(m, __shfl_down(m, off, 64));
-  }
+  v = wave_sum(v);
+  m = wave_max(m);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (lane == 0) {
     scratch[wv] = v;
@@ -351,8 +347,7 @@ __device__ __forceinline__ double block_sum_max(double v, double& m, double* scr
 
 template <int NT>
 __device__ __forceinline__ double block_max(double v, double* scratch) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_down(v, off, 64));
+  v = wave_max(v);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (lane == 0) scratch[wv] = v;
   __syncthreads();
@@ -363,11 +358,11 @@ __device__ __forceinline__ double block_max(double v, double* scratch) {
   return t;   // valid in thread 0
 }
 
-// Exclusive scan of n (<= NT) ints in LDS, in place, total at a[n].
+
 // Per-chunk flags and costs of a window's chunks [c0, c1), reduced by one
 // wave: lane l takes chunks c0 + l, c0 + l + 64, ... in order (four loads in
-// flight), then an xor butterfly adds the lanes.  The result used is lane 0's,
-// whose order of additions is fixed, so the sum is the same on every run.
+// flight), then a butterfly adds the lanes in a fixed order, so the sum is the
+// same on every run.
 __device__ __forceinline__ void wave_chunk_sums(const int32_t* flag, const double* cost, int c0, int c1,
                                                 bool need_cost, int lane, int& f_out, double& F_out) {
   int f = 0;
@@ -388,37 +383,84 @@ __device__ __forceinline__ void wave_chunk_sums(const int32_t* flag, const doubl
       F += cs[b];
     }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    f |= __shfl_xor(f, o, 64);
-    F += __shfl_xor(F, o, 64);
-  }
-  f_out = __builtin_amdgcn_readfirstlane(f);
-  F_out = wave_bcast(F, 0);
+  f_out = __any(f);
+  F_out = wave_bcast(wave_sum(F), 0);
 }
 
-template <int NT>
-__device__ __forceinline__ void block_scan(int* a, int n, int* scratch) {
-  const int t = threadIdx.x;
-  int v = t < n ? a[t] : 0;
-  // inclusive scan inside the wave
-  const int lane = t & 63, wv = t >> 6;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int u = __shfl_up(v, off, 64);
-    if (lane >= off) v += u;
+// Accept or reject attempt it, by one wave: the chunks' candidate costs and depth
+// flags summed, the costs compared, lambda and the current buffer updated.  `old`
+// is the window's state after the attempt's reduction; every lane returns the
+// state that the next attempt starts from, and the attempt's trace in tr.
+template <typename Real>
+__device__ __forceinline__ WinState decide(const WinState& old, const DevWork<Real>& K, const DevSettings& S, int wi,
+                                           int n_free, int c0, int c1, int lane, ba_iter_trace& tr) {
+  int depth = 0;
+  double F = 0.0;   // (summed before anything of the state is looked at: one latency for both)
+  wave_chunk_sums(K.part_flag_b, K.part_cost_b, c0, c1, true, lane, depth, F);
+  WinState st = old;
+  tr.cost = st.cost;
+  tr.lambda = st.lambda;
+  tr.cand_cost = __builtin_nan("");
+  tr.accepted = 0;
+  tr.status = 0;
+  if (st.frozen) {   // frozen by an earlier attempt or by this one's gradient test
+    tr.status = 3;
+    return st;
   }
-  if (lane == 63) scratch[wv] = v;
-  __syncthreads();
-  int base = 0;
-  for (int k = 0; k < wv; ++k) base += scratch[k];
-  int total = 0;
-  for (int k = 0; k < NT / 64; ++k) total += scratch[k];
-  const int orig = t < n ? a[t] : 0;
-  __syncthreads();
-  if (t < n) a[t] = base + v - orig;
-  if (t == 0) a[n] = total;
-  __syncthreads();
+  // the step's max-norm for the step test: pose tangents and the chunks' point moves
+  double sm = 0.0;
+  if (S.step_tol > 0) {
+    for (int e = lane; e < 6 * n_free; e += 64) sm = fmax(sm, fabs(K.dp[kDpStride * wi + e]));
+    for (int c = c0 + lane; c < c1; c += 64) sm = fmax(sm, K.part_smax[c]);
+    sm = wave_max(sm);
+  }
+  bool accept = false;
+  if (st.fail) {
+    tr.status = 1;
+    st.chol_failures++;
+  } else if (depth) {
+    tr.status = 2;
+    st.depth_rejects++;
+  } else {
+    F *= 0.5;
+    if (K.vi_cost_b) F += K.vi_cost_b[wi];
+    tr.cand_cost = F;
+    st.cand_cost = F;
+    accept = F < st.cost;
+  }
+  if (accept) {
+    st.cost = tr.cand_cost;
+    st.cur ^= 1;
+    st.accepted++;
+    st.lambda = fmax(st.lambda / S.lambda_down, S.lambda_min);
+    if (S.step_tol > 0 && sm <= S.step_tol) st.frozen = 1;
+  } else {
+    st.lambda = fmin(st.lambda * S.lambda_up, S.lambda_max);
+  }
+  tr.accepted = accept ? 1 : 0;
+  st.iters++;
+  st.fail = 0;
+  return st;
+}
+
+// The state that attempt it starts from is kept at parity it: the kernels of
+// attempt it may then read the last one's while one wave writes the new one.
+template <typename Real>
+__device__ __forceinline__ WinState& state_at(const DevPlan& P, const DevWork<Real>& K, int it, int wi) {
+  return K.state[(it & 1) * P.n_windows + wi];
+}
+
+// One wave decides attempt it - 1 and stores the state of attempt it and the trace.
+template <typename Real>
+__device__ __forceinline__ void put_decision(const DevPlan& P, const DevWork<Real>& K, const DevUser& U,
+                                             const DevSettings& S, int it, int wi, int n_free, int c0, int c1,
+                                             int lane) {
+  ba_iter_trace tr;
+  const WinState st = decide(state_at(P, K, it - 1, wi), K, S, wi, n_free, c0, c1, lane, tr);
+  if (lane == 0) {
+    state_at(P, K, it, wi) = st;
+    if (U.traces) U.traces[(size_t)wi * S.max_iters + it - 1] = tr;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -645,7 +687,7 @@ __device__ __forceinline__ void schur_fine(const uint32_t* sLst, int nseg, const
 template <typename Real, int TP, bool ADJ>
 __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevPlan P, DevTiles T, DevWork<Real> K,
                                                DevUser U, DevSettings S, int it, int cls_begin,
-                                               LdsDims D) {
+                                               LdsDims D, int fused) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int NW = TP / 64;
   constexpr int LR = ListRegs<TP>::N;
@@ -665,7 +707,15 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
   int4 rec = make_int4(0, 0, 0, -1), nrec = rec;
   if (tid < ta.y) rec = prec[ta.x + tid];
   if (tid < nta.y) nrec = prec[nta.x + tid];
-  const WinState& st = K.state[W.wi];
+  // With `fused` no launch decided the last attempt: every wave does, from the same
+  // sums in the same order (the loads above are in flight meanwhile).
+  WinState st;
+  if (!ADJ && fused && it > 0) {
+    ba_iter_trace tr;
+    st = decide(state_at(P, K, it - 1, W.wi), K, S, W.wi, W.n_free, W.chunk_begin, W.chunk_end, lane, tr);
+  } else {
+    st = state_at(P, K, it, W.wi);
+  }
   if (!ADJ && st.frozen) return;   // the whole work item (every thread of it) returns
   const int cur = ADJ ? 0 : st.cur;
   const double lam = ADJ ? 0.0 : st.lambda;
@@ -1260,10 +1310,17 @@ __device__ __forceinline__ void trail_item(double* sS, double* sB, int k, int nf
 // group order through LDS.  The partials of a window are contiguous, one
 // per chunk, so the chunk addresses need no table lookup.
 template <typename Real>
-__global__ __launch_bounds__(256) void k_sum(DevPlan P, DevTiles T, DevWork<Real> K, int wbase) {
+__global__ __launch_bounds__(256) void k_sum(DevPlan P, DevTiles T, DevWork<Real> K, DevUser U, DevSettings S, int it,
+                                             int wbase, int fused) {
   __shared__ double sG[kSumE][256];
   const WinDev W = T.win_rec[wbase + blockIdx.x];
-  if (K.state[W.self].frozen) return;
+  // with `fused` the window's first workgroup also stores the decision on the last
+  // attempt, which pass A has taken for itself
+  const bool pending = fused && it > 0;
+  const int frozen = state_at(P, K, pending ? it - 1 : it, W.self).frozen;
+  if (pending && blockIdx.y == 0 && threadIdx.x >= 192)
+    put_decision(P, K, U, S, it, W.self, W.n_free, W.chunk_begin, W.chunk_end, threadIdx.x & 63);
+  if (frozen) return;
   const int nf = W.n_free, nblk = nf * (nf + 1) / 2;
   const int ne = nblk * kBS + 12 * nf;
   const int G = W.sum_groups, L = 256 / G;
@@ -1330,7 +1387,7 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
   extern __shared__ __align__(16) unsigned char smem[];
   const WinDev W = T.win_rec[wbase + blockIdx.x];
   const int wi = W.self;
-  WinState& st = K.state[wi];
+  WinState& st = state_at(P, K, it, wi);
   const int tid = threadIdx.x;
   const int nf = W.n_free, nblk = nf * (nf + 1) / 2, nS = 6 * nf;
   double* sS = reinterpret_cast<double*>(smem);   // nblk * kRS
@@ -1349,13 +1406,11 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
     const double* src = K.ssum + W.sum_off;
     const int nb = nblk * kBS;
     constexpr int B = 8;
-    for (int base = 0; base < ne; base += B * NT) {
+    int base = 0;
+    do {   // once without free poses too (ne = 0): the flags are read in any case
       double v[B];
 #pragma unroll
-      for (int b = 0; b < B; ++b) {
-        const int e = base + tid + b * NT;
-        v[b] = src[e < ne ? e : ne - 1];
-      }
+      for (int b = 0; b < B; ++b) v[b] = src[max(min(base + tid + b * NT, ne - 1), 0)];
       if (base == 0 && tid < 64) {
         const bool need_cost = !ADJ && it == 0;
         int f = 0;
@@ -1383,7 +1438,8 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
           sS[nblk * kRS + (e - nb)] = v[b];
         }
       }
-    }
+      base += B * NT;
+    } while (base < ne);
   }
   __syncthreads();
   if (!ADJ && S.grad_tol > 0) {
@@ -1646,7 +1702,7 @@ __global__ __launch_bounds__(TP) void k_pass_b(DevPlan P, DevTiles T, DevWork<Re
   int4 ta = W.ta0;
   int4 rec = make_int4(0, 0, 0, -1);
   if (tid < ta.y) rec = prec[ta.x + tid];
-  const WinState& st = K.state[wi];
+  const WinState& st = state_at(P, K, it, wi);
   if (!ADJ && (st.fail || st.frozen)) {
     if (tid == 0) {
       K.part_cost_b[chunk] = 0.0;
@@ -1903,76 +1959,29 @@ __global__ __launch_bounds__(TP) void k_pass_b(DevPlan P, DevTiles T, DevWork<Re
 template <typename Real>
 __global__ void k_accept(DevPlan P, DevTiles T, DevWork<Real> K, DevUser U, DevSettings S, int it, int wbase,
                          int nwin) {
-  // one wave per window: the lanes sum the candidate's chunk costs and depth
-  // flags, lane 0 decides
+  // one wave per window
   const int i = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
   if (i >= nwin) return;
   const WinDev W = T.win_rec[wbase + i];
-  const int wi = W.self;
-  int depth = 0;
-  double F = 0.0;
-  wave_chunk_sums(K.part_flag_b, K.part_cost_b, W.chunk_begin, W.chunk_end, true, lane, depth, F);
-  // the step's max-norm for the step test: pose tangents and the chunks' point moves
-  double sm = 0.0;
-  if (S.step_tol > 0) {
-    for (int e = lane; e < 6 * W.n_free; e += 64) sm = fmax(sm, fabs(K.dp[kDpStride * wi + e]));
-    for (int c = W.chunk_begin + lane; c < W.chunk_end; c += 64) sm = fmax(sm, K.part_smax[c]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sm = fmax(sm, __shfl_xor(sm, off, 64));
-  }
-  if (lane != 0) return;
-  WinState st = K.state[wi];
-  ba_iter_trace tr;
-  tr.cost = st.cost;
-  tr.lambda = st.lambda;
-  tr.cand_cost = __builtin_nan("");
-  tr.accepted = 0;
-  tr.status = 0;
-  if (st.frozen) {   // frozen by an earlier attempt or by this one's gradient test
-    tr.status = 3;
-    if (U.traces) U.traces[(size_t)wi * S.max_iters + it] = tr;
-    return;
-  }
-  bool accept = false;
-  if (st.fail) {
-    tr.status = 1;
-    st.chol_failures++;
-  } else {
-    if (depth) {
-      tr.status = 2;
-      st.depth_rejects++;
-    } else {
-      F *= 0.5;
-      if (K.vi_cost_b) F += K.vi_cost_b[wi];
-      tr.cand_cost = F;
-      st.cand_cost = F;
-      accept = F < st.cost;
-    }
-  }
-  if (accept) {
-    st.cost = tr.cand_cost;
-    st.cur ^= 1;
-    st.accepted++;
-    st.lambda = fmax(st.lambda / S.lambda_down, S.lambda_min);
-    if (S.step_tol > 0 && sm <= S.step_tol) st.frozen = 1;
-  } else {
-    st.lambda = fmin(st.lambda * S.lambda_up, S.lambda_max);
-  }
-  tr.accepted = accept ? 1 : 0;
-  st.iters++;
-  st.fail = 0;
-  K.state[wi] = st;
-  if (U.traces) U.traces[(size_t)wi * S.max_iters + it] = tr;
+  put_decision(P, K, U, S, it + 1, W.self, W.n_free, W.chunk_begin, W.chunk_end, threadIdx.x & 63);
 }
 
 // Copy the final state into the user's arrays where it sits in the workspace
 // buffer, and write the report.  One workgroup per window.
 template <typename Real>
-__global__ void k_finalize(DevPlan P, DevWork<Real> K, DevUser U, int need_cost) {
+__global__ void k_finalize(DevPlan P, DevWork<Real> K, DevUser U, DevSettings S, int fused) {
   const int wi = blockIdx.x;
   const WinDev W = P.win[wi];
-  const WinState st = K.state[wi];
+  const int need_cost = S.max_iters == 0;
+  WinState st;
+  if (fused && !need_cost) {   // the last attempt's decision, by every wave
+    ba_iter_trace tr;
+    st = decide(state_at(P, K, S.max_iters - 1, wi), K, S, wi, W.n_free, W.chunk_begin, W.chunk_end,
+                threadIdx.x & 63, tr);
+    if (threadIdx.x == 0 && U.traces) U.traces[(size_t)wi * S.max_iters + S.max_iters - 1] = tr;
+  } else {
+    st = state_at(P, K, S.max_iters, wi);
+  }
   if (st.cur == 1) {
     for (int k = threadIdx.x; k < 12 * W.n_poses; k += blockDim.x)
       U.poses[12 * W.pose_off + k] = K.poses_b[12 * W.pose_off + k];
@@ -2089,11 +2098,11 @@ hipError_t launch_pass_a(const LaunchArgs& A, const DevWork<Real>& K, int it) {
   for (int k = ng - 1; k >= 0; --k)   // side launches first
     if (g[k].stream)
       hipLaunchKernelGGL((k_pass_a<Real, TP, ADJ>), dim3(g[k].n), dim3(TP), g[k].lds, side[g[k].stream - 1], A.plan,
-                         A.tiles, K, A.user, A.settings, it, g[k].begin, A.dims);
+                         A.tiles, K, A.user, A.settings, it, g[k].begin, A.dims, A.fused);
   for (int k = 0; k < ng; ++k)
     if (!g[k].stream)
       hipLaunchKernelGGL((k_pass_a<Real, TP, ADJ>), dim3(g[k].n), dim3(TP), g[k].lds, main, A.plan, A.tiles, K,
-                         A.user, A.settings, it, g[k].begin, A.dims);
+                         A.user, A.settings, it, g[k].begin, A.dims, A.fused);
   for (int s = 1; s <= kSideStreams; ++s)
     if (used[s]) {
       if ((e = hipEventRecord(join[s - 1], side[s - 1])) != hipSuccess) return e;
@@ -2111,15 +2120,21 @@ void launch_stages(const LaunchArgs& A, const DevWork<Real>& K, int it, int wb, 
                    int slices, hipStream_t st) {
   if (nwin <= 0) return;
   const size_t lb = pass_b_lds<Real, TP>(), lr = reduce_lds(nf);
-  hipLaunchKernelGGL(k_sum<Real>, dim3(nwin, slices), dim3(256), 0, st, A.plan, A.tiles, K, wb);
-  if (!ADJ && A.vi) launch_vi_lin(*static_cast<const ViArgs*>(A.vi), wb, nwin, st);
+  hipLaunchKernelGGL(k_sum<Real>, dim3(nwin, slices), dim3(256), 0, st, A.plan, A.tiles, K, A.user,
+                     A.settings, it, wb, A.fused);
+  ViArgs V;
+  if (!ADJ && A.vi) {
+    V = *static_cast<const ViArgs*>(A.vi);
+    V.state += (it & 1) * A.plan.n_windows;
+    launch_vi_lin(V, wb, nwin, st);
+  }
   hipLaunchKernelGGL((k_reduce<Real, kReduceThreads, ADJ>), dim3(nwin), dim3(kReduceThreads), lr, st, A.plan, A.tiles,
                      K, A.user, A.settings, it, wb);
-  if (!ADJ && A.vi) launch_vi_cand(*static_cast<const ViArgs*>(A.vi), wb, nwin, st);
+  if (!ADJ && A.vi) launch_vi_cand(V, wb, nwin, st);
   if (nch > 0)
     hipLaunchKernelGGL((k_pass_b<Real, TP, ADJ>), dim3(nch), dim3(TP), lb, st, A.plan, A.tiles, K, A.user, A.settings,
                        it, cb);
-  if (!ADJ)
+  if (!ADJ && !A.fused)
     hipLaunchKernelGGL(k_accept<Real>, dim3((nwin + 3) / 4), dim3(256), 0, st, A.plan, A.tiles, K, A.user,
                        A.settings, it, wb, nwin);
 }
@@ -2131,7 +2146,7 @@ void launch_pass_a_class(const LaunchArgs& A, const DevWork<Real>& K, int it, in
   if (n <= 0) return;
   const size_t lds = pass_a_lds<Real, TP>(A.dims.np, A.dims.nc, A.cls_nf[c], A.list_bytes, ADJ);
   hipLaunchKernelGGL((k_pass_a<Real, TP, ADJ>), dim3(n), dim3(TP), lds, st, A.plan, A.tiles, K, A.user, A.settings, it,
-                     A.cls_begin[c], A.dims);
+                     A.cls_begin[c], A.dims, A.fused);
 }
 
 // The windows of one size class never meet those of another, so with side
@@ -2218,7 +2233,7 @@ hipError_t run_solve(const LaunchArgs& A, const DevWork<Real>& K) {
   }
   if (iters == 0 && (e = launch_pass_a<Real, TP, false>(A, K, 0)) != hipSuccess)   // the report still needs the input cost
     return e;
-  hipLaunchKernelGGL(k_finalize<Real>, dim3(nw), dim3(256), 0, main, A.plan, K, A.user, iters == 0 ? 1 : 0);
+  hipLaunchKernelGGL(k_finalize<Real>, dim3(nw), dim3(256), 0, main, A.plan, K, A.user, A.settings, A.fused);
   return hipGetLastError();
 }
 
@@ -2263,7 +2278,8 @@ hipError_t run_solve_timed(const LaunchArgs& A, const DevWork<Real>& K, double* 
   for (int it = 0; it < iters && e == hipSuccess; ++it) {
     e = launch_pass_a<Real, TP, false>(A, K, it);
     (void)hipEventRecord(ev[4 * it + 1], main);
-    hipLaunchKernelGGL(k_sum<Real>, dim3(nw, A.sum_slices), dim3(256), 0, main, A.plan, A.tiles, K, 0);
+    hipLaunchKernelGGL(k_sum<Real>, dim3(nw, A.sum_slices), dim3(256), 0, main, A.plan, A.tiles, K, A.user,
+                       A.settings, it, 0, 0);
     hipLaunchKernelGGL((k_reduce<Real, kReduceThreads, false>), dim3(nw), dim3(kReduceThreads), lr, main, A.plan,
                        A.tiles, K, A.user, A.settings, it, 0);
     (void)hipEventRecord(ev[4 * it + 2], main);
@@ -2274,7 +2290,7 @@ hipError_t run_solve_timed(const LaunchArgs& A, const DevWork<Real>& K, double* 
                        A.settings, it, 0, nw);
     (void)hipEventRecord(ev[4 * it + 4], main);
   }
-  hipLaunchKernelGGL(k_finalize<Real>, dim3(nw), dim3(256), 0, main, A.plan, K, A.user, 0);
+  hipLaunchKernelGGL(k_finalize<Real>, dim3(nw), dim3(256), 0, main, A.plan, K, A.user, A.settings, 0);
   if (e == hipSuccess) e = hipGetLastError();
   if (e == hipSuccess) e = hipEventSynchronize(ev[nev - 1]);
   for (int k = 0; k < 4; ++k) stage_ms[k] = 0.0;

@@ -42,23 +42,6 @@ constexpr int kPnpSums = 32;
 __device__ int kCamZero = 0;          // global memory (not constant) keeps the loads
 __device__ double kWeightOne = 1.0;   // below global loads rather than flat ones
 
-// Exchange of 64-bit values between lane groups: rows 2-3 of a with rows 0-1
-// of b (permlane32), odd rows of a with even rows of b (permlane16).
-__device__ __forceinline__ void swap_rows32(double& a, double& b) {
-  const long long ia = __double_as_longlong(a), ib = __double_as_longlong(b);
-  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ia, (unsigned)ib, false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ia >> 32), (unsigned)(ib >> 32), false, false);
-  a = __longlong_as_double(((long long)hi[0] << 32) | lo[0]);
-  b = __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
-}
-__device__ __forceinline__ void swap_rows16(double& a, double& b) {
-  const long long ia = __double_as_longlong(a), ib = __double_as_longlong(b);
-  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ia, (unsigned)ib, false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ia >> 32), (unsigned)(ib >> 32), false, false);
-  a = __longlong_as_double(((long long)hi[0] << 32) | lo[0]);
-  b = __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
-}
-
 // Reduce-scatter of 32 per-lane values over the wave: lanes 2k and 2k+1 end
 // with the wave total of v[k].  Each step halves the list: the lanes on one
 // side of a lane bit keep the first half, the others the second, and each
