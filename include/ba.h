@@ -259,11 +259,13 @@ ba_status ba_adjoint(ba_window w, ba_batch b, const ba_settings* s, const double
                      void* stream);
 
 /* Launch shape of a plan's batched solve (one launch per
- * stage and size class).  Defaults: chunk_obs from the plan's size,
- * tile_pairs 0, every class_chunk_mult 1, class_streams 1. */
+ * stage and size class).  Defaults: chunk_obs from the plan's size (FP64 solves
+ * of small batches use smaller work items than the value reported here, until one is
+ * set), tile_pairs 0, every class_chunk_mult 1, class_streams 1. */
 typedef struct {
   int32_t chunk_obs;            /* target observations per work item, 128..65536 */
-  int32_t tile_pairs;           /* pairs per tile: 0 = 256 when its LDS fits, else 64; or 64 / 256 */
+  int32_t tile_pairs;           /* pairs per tile: 0 = 256 when its LDS fits, else 64 (in BA_FP64 by
+                                   size class); or 64 / 256 */
   int32_t class_chunk_mult[4];  /* per size class (up to 8, 16, 23, 32 free poses): work items of
                                    about class_chunk_mult x chunk_obs observations, 1..4 */
   int32_t class_streams;        /* 1: the size classes run as concurrent chains on two side
@@ -273,7 +275,7 @@ typedef struct {
 /* Launch-shape tuning.  ba_autotune times candidate shapes of the batched
  * solve on this plan (3-attempt solves, best of two after a warm-up;
  * synchronises the stream; not capturable) by coordinate descent: chunk_obs
- * over 1024..16384, then 64-pair tiles, then four per-class multiplier sets,
+ * over 1024..16384 (256..16384 in BA_FP64), then 64-pair tiles, then four per-class multiplier sets,
  * then all classes on one stream; it keeps the fastest in the plan and
  * returns its chunk_obs (ba_get_launch gives the whole shape).  The state
  * arrays are modified: pass scratch copies.  Shapes whose workspace exceeds

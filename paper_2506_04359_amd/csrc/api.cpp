@@ -13,6 +13,7 @@
 #include <mutex>
 #include <sstream>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/ba.h"
@@ -39,11 +40,11 @@ size_t pass_b_lds();
 size_t reduce_lds(int max_nf);
 template <typename Real, int TP, bool ADJ>
 hipError_t set_attrs();
-template <typename Real, int TP>
+template <typename Real>
 hipError_t run_solve(const LaunchArgs& A, const DevWork<Real>& K);
-template <typename Real, int TP>
+template <typename Real>
 hipError_t run_adjoint(const LaunchArgs& A, const DevWork<Real>& K);
-template <typename Real, int TP>
+template <typename Real>
 hipError_t run_solve_timed(const LaunchArgs& A, const DevWork<Real>& K, double* stage_ms);
 
 constexpr size_t kLdsLimit = 160 * 1024;
@@ -72,10 +73,18 @@ struct Blob {
     size = off + std::max<size_t>(parts.back().second.size(), 1);
     return off;
   }
+  // The parts in one host buffer, so that a plan uploads with one copy.
+  hipError_t upload(void* mem) const {
+    std::vector<uint8_t> all(size);
+    for (auto& p : parts)
+      if (!p.second.empty()) std::memcpy(all.data() + p.first, p.second.data(), p.second.size());
+    return hipMemcpy(mem, all.data(), size, hipMemcpyHostToDevice);
+  }
 };
 
 struct DeviceTables {
-  int tp = 0, chunk_obs = 0;
+  int chunk_obs = 0;
+  int cls_tp[kClasses] = {0, 0, 0, 0};           // pairs per tile of each class
   int n_chunks = 0;
   int64_t part_elems = 0;
   void* mem = nullptr;
@@ -95,7 +104,7 @@ struct DeviceTables {
   int cls_win_begin[kClasses + 1] = {0, 0, 0, 0, 0};
   int cls_win_nf[kClasses] = {0, 0, 0, 0};
   int cls_nf[kClasses] = {0, 0, 0, 0};
-  int list_bytes = 0;   // largest per-tile segment + product list
+  int cls_list_bytes[kClasses] = {0, 0, 0, 0};   // largest per-tile segment + product list of each class
   int max_cpw = 0;      // largest chunk count of one window
   int cls_sum_slices[kClasses] = {0, 0, 0, 0};   // k_sum workgroups per window, per class
   int sum_slices = 0;
@@ -112,7 +121,11 @@ struct ba_batch_s {
   int device = 0;
   void* mem = nullptr;   // plan arrays
   DevPlan plan{};
-  DeviceTables tables[2];   // [0]: small tiles, [1]: large tiles
+  // [0]: 64-pair tiles (made when ba_set_launch_config asks for them), [1]:
+  // 256-pair tiles, [2]: FP64 solves by default, when their tiles or work items
+  // differ from [1]
+  DeviceTables tables[3];
+  int fp64_tables = 1;
   // launch shape (ba_launch_config)
   int chunk_obs = 4096;
   int tile_pairs = 0;                      // 0: the largest tiles whose LDS fits
@@ -156,11 +169,11 @@ ba_status hip_fail(hipError_t e, const char* what) {
   return set_error(BA_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-ba_status upload_tables(ba_batch_s* b, int which, int tp, int chunk_obs) {
+ba_status upload_tables(ba_batch_s* b, int which, int tp, int chunk_obs, const int* class_tp = nullptr) {
   std::vector<const HostWindow*> ws;
   for (auto& w : b->wins) ws.push_back(&w);
   LaunchTables t;
-  build_tiles(ws, tp, chunk_obs, t, b->class_mult);
+  build_tiles(ws, tp, chunk_obs, t, b->class_mult, class_tp);
   // per-window records with this table's chunk ranges
   std::vector<WinDev> wd(b->wins.size());
   int32_t po = 0, lo = 0, co = 0, oo = 0, pa = 0, so = 0;
@@ -234,14 +247,10 @@ ba_status upload_tables(ba_batch_s* b, int which, int tp, int chunk_obs) {
   void* mem = nullptr;
   hipError_t e = hipMalloc(&mem, blob.size);
   if (e != hipSuccess) return set_error(BA_ERR_OOM, "plan tables: hipMalloc failed");
-  for (auto& p : blob.parts)
-    if (!p.second.empty()) {
-      e = hipMemcpy((char*)mem + p.first, p.second.data(), p.second.size(), hipMemcpyHostToDevice);
-      if (e != hipSuccess) {
-        (void)hipFree(mem);
-        return hip_fail(e, "plan tables upload");
-      }
-    }
+  if ((e = blob.upload(mem)) != hipSuccess) {
+    (void)hipFree(mem);
+    return hip_fail(e, "plan tables upload");
+  }
   DeviceTables& D = b->tables[which];
   if (D.mem) {
     // hipFree waits for the device, so eager launches are done with the old
@@ -250,8 +259,11 @@ ba_status upload_tables(ba_batch_s* b, int which, int tp, int chunk_obs) {
     else (void)hipFree(D.mem);
   }
   D.mem = mem;
-  D.tp = tp;
   D.chunk_obs = chunk_obs;
+  for (int c = 0; c < kClasses; ++c) {
+    D.cls_tp[c] = class_tp ? class_tp[c] : tp;
+    D.cls_list_bytes[c] = t.class_tile_words[c] * 4 + 16;
+  }
   D.n_chunks = t.n_chunks();
   D.part_elems = t.part_elems;
   D.chunk_rec = (ChunkRec*)((char*)mem + o_cr);
@@ -266,7 +278,6 @@ ba_status upload_tables(ba_batch_s* b, int which, int tp, int chunk_obs) {
   D.pair_rec = (int32_t*)((char*)mem + o_pr);
   D.tile_rec = (int32_t*)((char*)mem + o_tr);
   D.lists = (uint32_t*)((char*)mem + o_ls);
-  D.list_bytes = t.max_tile_words * 4 + 16;
   D.max_cpw = 0;
   for (size_t i = 0; i + 1 < t.win_chunk_begin.size(); ++i)
     D.max_cpw = std::max(D.max_cpw, t.win_chunk_begin[i + 1] - t.win_chunk_begin[i]);
@@ -296,6 +307,59 @@ int default_chunk_obs(int64_t n_obs, size_t n_windows) {
   if (n_windows == 1) return (int)std::min<int64_t>(8192, std::max<int64_t>(128, n_obs / 256));
   const int64_t c = n_obs / 1024;
   return (int)std::min<int64_t>(8192, std::max<int64_t>(1024, c));
+}
+
+// Work-item size of FP64 solves.  A batch's aim at n_obs / 1024 observations too,
+// but may be as small as one tile: an FP64 tile takes about twice an FP32 one's
+// time, a workgroup's partial takes most of a CU's LDS, and a small batch in items of
+// 1024 observations leaves CUs idle while few run several tiles in series (with the
+// tiles below: 16 windows, 154 k observations, 10 attempts 6.4 -> 2.0 ms; a training
+// step of 4 windows, 11 k observations, 1.66 -> 1.00 ms).
+int default_chunk_obs_fp64(int64_t n_obs, size_t n_windows) {
+  if (n_windows == 1) return default_chunk_obs(n_obs, 1);
+  return (int)std::min<int64_t>(8192, std::max<int64_t>(256, n_obs / 1024));
+}
+
+// Pass A's and pass B's LDS of a class in a set of tables.
+size_t chunk_lds(const ba_batch_s* b, const DeviceTables& t, int c, bool fp64) {
+  auto both = [&](auto real, auto tp) {
+    using Real = decltype(real);
+    constexpr int TP = decltype(tp)::value;
+    return std::max(pass_a_lds<Real, TP>(b->max_np, b->max_nc, t.cls_nf[c], t.cls_list_bytes[c], true),
+                    pass_b_lds<Real, TP>());
+  };
+  using Large = std::integral_constant<int, kTileLarge>;
+  using Small = std::integral_constant<int, kTileSmall>;
+  if (fp64) return t.cls_tp[c] == kTileLarge ? both(double(), Large()) : both(double(), Small());
+  return t.cls_tp[c] == kTileLarge ? both(float(), Large()) : both(float(), Small());
+}
+
+bool tables_fit(const ba_batch_s* b, const DeviceTables& t, bool fp64) {
+  if (!t.mem) return false;
+  for (int c = 0; c < kClasses; ++c)
+    if (t.cls_win_begin[c + 1] > t.cls_win_begin[c] && chunk_lds(b, t, c, fp64) > kLdsLimit) return false;
+  return true;
+}
+
+// The tables of a plan for work items of chunk_obs (mixed) and chunk_obs_fp64
+// observations.  FP64 solves use 256-pair tiles for the size classes whose
+// partial leaves room for them (up to 23 free poses) and 64-pair tiles for the
+// others.
+ba_status upload_all(ba_batch_s* b, int chunk_obs, int chunk_obs_fp64) {
+  ba_status s = upload_tables(b, 1, kTileLarge, chunk_obs);
+  if (s != BA_OK) return s;
+  int tp[kClasses];
+  bool same = chunk_obs == chunk_obs_fp64;
+  for (int c = 0; c < kClasses; ++c) {
+    const bool used = b->tables[1].cls_win_begin[c + 1] > b->tables[1].cls_win_begin[c];
+    tp[c] = used && chunk_lds(b, b->tables[1], c, true) > kLdsLimit ? kTileSmall : kTileLarge;
+    same = same && tp[c] == kTileLarge;
+  }
+  b->fp64_tables = same ? 1 : 2;
+  if (!same && (s = upload_tables(b, 2, 0, chunk_obs_fp64, tp)) != BA_OK) return s;
+  if (b->tile_pairs == kTileSmall || !tables_fit(b, b->tables[1], false))
+    s = upload_tables(b, 0, kTileSmall, chunk_obs);
+  return s;
 }
 
 ba_status batch_build(std::vector<HostWindow>&& wins, ba_batch_s** out) {
@@ -344,11 +408,7 @@ ba_status batch_build(std::vector<HostWindow>&& wins, ba_batch_s** out) {
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
   e = hipMalloc(&b->mem, blob.size);
   if (e != hipSuccess) return set_error(BA_ERR_OOM, "plan arrays: hipMalloc failed");
-  for (auto& p : blob.parts)
-    if (!p.second.empty()) {
-      e = hipMemcpy((char*)b->mem + p.first, p.second.data(), p.second.size(), hipMemcpyHostToDevice);
-      if (e != hipSuccess) return hip_fail(e, "plan upload");
-    }
+  if ((e = blob.upload(b->mem)) != hipSuccess) return hip_fail(e, "plan upload");
   char* m = (char*)b->mem;
   b->plan.free_slot = (const int32_t*)(m + o_fs);
   b->plan.cam = (const double*)(m + o_cam);
@@ -361,9 +421,7 @@ ba_status batch_build(std::vector<HostWindow>&& wins, ba_batch_s** out) {
   b->plan.obs_perm = (const int32_t*)(m + o_op);
   b->plan.n_windows = (int32_t)b->wins.size();
   b->chunk_obs = default_chunk_obs(b->n_obs, b->wins.size());
-  ba_status s = upload_tables(b.get(), 0, kTileSmall, b->chunk_obs);
-  if (s != BA_OK) return s;
-  s = upload_tables(b.get(), 1, kTileLarge, b->chunk_obs);
+  const ba_status s = upload_all(b.get(), b->chunk_obs, default_chunk_obs_fp64(b->n_obs, b->wins.size()));
   if (s != BA_OK) return s;
   *out = b.release();
   return BA_OK;
@@ -384,31 +442,22 @@ ba_status check_settings(const ba_settings* s) {
   return BA_OK;
 }
 
-// Tile configuration for a precision: the large tiles when their LDS fits.
+// The tables of a precision: the tile size that was asked for, else the largest
+// tiles whose LDS fits.
 ba_status pick_config(const ba_batch_s* b, int precision, int* which) {
   const int nf = b->max_nf;
-  if (precision == BA_FP64 && nf > kMaxFreeFp64)
+  const bool fp64 = precision == BA_FP64;
+  if (fp64 && nf > kMaxFreeFp64)
     return set_error(BA_ERR_UNSUPPORTED, "BA_FP64 supports at most 29 free poses per window");
-  auto fits = [&](int w) {
-    const DeviceTables& t = b->tables[w];
-    const size_t la = precision == BA_FP64
-                          ? (t.tp == kTileLarge ? pass_a_lds<double, kTileLarge>(b->max_np, b->max_nc, nf, t.list_bytes, true)
-                                                : pass_a_lds<double, kTileSmall>(b->max_np, b->max_nc, nf, t.list_bytes, true))
-                          : (t.tp == kTileLarge ? pass_a_lds<float, kTileLarge>(b->max_np, b->max_nc, nf, t.list_bytes, true)
-                                                : pass_a_lds<float, kTileSmall>(b->max_np, b->max_nc, nf, t.list_bytes, true));
-    const size_t lb = precision == BA_FP64
-                          ? (t.tp == kTileLarge ? pass_b_lds<double, kTileLarge>() : pass_b_lds<double, kTileSmall>())
-                          : (t.tp == kTileLarge ? pass_b_lds<float, kTileLarge>() : pass_b_lds<float, kTileSmall>());
-    return la <= kLdsLimit && lb <= kLdsLimit;
-  };
+  auto fits = [&](int w) { return tables_fit(b, b->tables[w], fp64); };
   if (b->tile_pairs == kTileSmall) {
     if (!fits(0)) return set_error(BA_ERR_UNSUPPORTED, "window too large for LDS");
     *which = 0;
   } else if (b->tile_pairs == kTileLarge) {
     if (!fits(1)) return set_error(BA_ERR_UNSUPPORTED, "window too large for LDS with 256-pair tiles");
     *which = 1;
-  } else if (fits(1)) {
-    *which = 1;
+  } else if (fits(fp64 ? b->fp64_tables : 1)) {
+    *which = fp64 ? b->fp64_tables : 1;
   } else if (fits(0)) {
     *which = 0;
   } else {
@@ -603,7 +652,8 @@ ba_status launch(ba_batch_s* b, const ba_settings* s, Op op, DevUser U, void* ws
   for (int c = 0; c < kClasses; ++c) A.cls_nf[c] = t.cls_nf[c];
   A.dims.np = b->max_np;
   A.dims.nc = b->max_nc;
-  A.list_bytes = t.list_bytes;
+  for (int c = 0; c < kClasses; ++c) A.cls_tp[c] = t.cls_tp[c];
+  for (int c = 0; c < kClasses; ++c) A.cls_list_bytes[c] = t.cls_list_bytes[c];
   // Every workgroup of pass A then reads all of its window's candidate costs: one
   // round of loads up to 256 chunks, against a launch of its own (stereo window,
   // 234 chunks, 10 attempts: 777 -> 747 us; mono window, 8 chunks: 361 -> 344).
@@ -668,27 +718,14 @@ ba_status launch(ba_batch_s* b, const ba_settings* s, Op op, DevUser U, void* ws
     K.vi_states = V.states;
     K.vi_states_b = V.states_b;
   };
-  if (s->precision == BA_FP64) {
-    DevWork<double> K = make_work<double>(L, ws, has_w);
+  auto run = [&](auto real) {
+    using Real = decltype(real);
+    DevWork<Real> K = make_work<Real>(L, ws, has_w);
     vi_work(K);
-    if (op == Op::Solve)
-      e = t.tp == kTileLarge ? run_solve<double, kTileLarge>(A, K) : run_solve<double, kTileSmall>(A, K);
-    else if (op == Op::Timed)
-      e = t.tp == kTileLarge ? run_solve_timed<double, kTileLarge>(A, K, stage_ms)
-                             : run_solve_timed<double, kTileSmall>(A, K, stage_ms);
-    else
-      e = t.tp == kTileLarge ? run_adjoint<double, kTileLarge>(A, K) : run_adjoint<double, kTileSmall>(A, K);
-  } else {
-    DevWork<float> K = make_work<float>(L, ws, has_w);
-    vi_work(K);
-    if (op == Op::Solve)
-      e = t.tp == kTileLarge ? run_solve<float, kTileLarge>(A, K) : run_solve<float, kTileSmall>(A, K);
-    else if (op == Op::Timed)
-      e = t.tp == kTileLarge ? run_solve_timed<float, kTileLarge>(A, K, stage_ms)
-                             : run_solve_timed<float, kTileSmall>(A, K, stage_ms);
-    else
-      e = t.tp == kTileLarge ? run_adjoint<float, kTileLarge>(A, K) : run_adjoint<float, kTileSmall>(A, K);
-  }
+    return op == Op::Solve ? run_solve<Real>(A, K)
+                           : op == Op::Timed ? run_solve_timed<Real>(A, K, stage_ms) : run_adjoint<Real>(A, K);
+  };
+  e = s->precision == BA_FP64 ? run(double()) : run(float());
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   return BA_OK;
 }
@@ -1302,13 +1339,12 @@ ba_status ba_set_launch_config(ba_batch b, const ba_launch_config* cfg) {
   const int old_tp = b->tile_pairs;
   for (int c = 0; c < kClasses; ++c) b->class_mult[c] = cfg->class_chunk_mult[c];
   b->tile_pairs = cfg->tile_pairs;
-  ba_status s = upload_tables(b, 0, kTileSmall, cfg->chunk_obs);
-  if (s == BA_OK) s = upload_tables(b, 1, kTileLarge, cfg->chunk_obs);
+  const int old_chunk64 = b->tables[b->fp64_tables].chunk_obs;
+  ba_status s = upload_all(b, cfg->chunk_obs, cfg->chunk_obs);
   if (s != BA_OK) {   // put the previous shape back (best effort: this only fails on OOM)
     for (int c = 0; c < kClasses; ++c) b->class_mult[c] = old_mult[c];
     b->tile_pairs = old_tp;
-    (void)upload_tables(b, 0, kTileSmall, b->chunk_obs);
-    (void)upload_tables(b, 1, kTileLarge, b->chunk_obs);
+    (void)upload_all(b, b->chunk_obs, old_chunk64);
     return s;
   }
   b->chunk_obs = cfg->chunk_obs;
@@ -1414,7 +1450,8 @@ ba_status ba_autotune(ba_batch b, const ba_settings* s, double* poses, double* p
     }
     return r;
   };
-  for (int chunk : {1024, 2048, 4096, 8192, 16384}) {
+  for (int chunk : {256, 512, 1024, 2048, 4096, 8192, 16384}) {
+    if (chunk < 1024 && s->precision != BA_FP64) continue;
     ba_launch_config c = best;
     c.chunk_obs = chunk;
     if ((st = consider(c)) != BA_OK) break;

@@ -175,7 +175,8 @@ struct LaunchArgs {
   int cls_win_nf[kClasses];      // largest free-pose count of each class's windows
   int cls_nf[kClasses];          // largest free-pose count of each class
   LdsDims dims;                  // largest pose / camera count of the batch
-  int list_bytes;                // largest per-tile product list (segments + products)
+  int cls_tp[kClasses];          // pairs per tile of each class
+  int cls_list_bytes[kClasses];  // largest per-tile product list (segments + products) of each class
   // 1: no launch of its own for the acceptance; pass A of the next attempt (and
   // the final copy) decide from the chunks' candidate costs
   int fused;

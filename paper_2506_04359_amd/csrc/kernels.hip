@@ -32,6 +32,7 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "device.hpp"
 #include "vi.hpp"
@@ -608,7 +609,7 @@ struct ZRow {
 // start) and its store to LDS (after phase 2).
 template <int TP>
 struct ListRegs {
-  static constexpr int N = TP >= 256 ? 12 : 16;
+  static constexpr int N = TP >= 256 ? 12 : 4;
 };
 
 // LDS carve of pass A.  The camera table, the window's poses (FP64, staged
@@ -633,12 +634,12 @@ struct PassALds {
 // order (the same chain of FMAs per entry as the 2 x 6 units).  Two register sets
 // in turn, so that a unit waits for LDS once per product; at its end the reads are
 // clamped to the last product (read, not used).  LM only (sigma = 1).
-template <typename Real, int TP, int CG>
+template <typename Real, int CG>
 __device__ __forceinline__ void schur_fine(const uint32_t* sLst, int nseg, const Real* sPZ, Real* sS) {
   constexpr int kZS = ZRow<Real>::S, ZR = ZRow<Real>::R;
   constexpr int NC = 6 / CG, UPS = 6 * NC;
   const uint16_t* sProd = reinterpret_cast<const uint16_t*>(sLst + nseg);
-  const int u = threadIdx.x;   // one round: the caller checked nseg UPS <= TP
+  const int u = threadIdx.x;   // one round: the caller checked nseg UPS <= threads
   if (u >= nseg * UPS) return;
   const uint32_t wd = sLst[u / UPS];
   const int row = (u % UPS) / NC, col = (u % NC) * CG;
@@ -682,14 +683,19 @@ __device__ __forceinline__ void schur_fine(const uint32_t* sLst, int nseg, const
   for (int c = 0; c < CG; ++c) B[c] -= acc[c];
 }
 
+// Threads of pass A, whatever the tile size: with 64-pair tiles (FP64 partials of
+// more than 23 free poses take most of the LDS) one wave holds the pairs, and all
+// four share the Schur units, which are most of such a tile's time.
+constexpr int kPassAThreads = 256;
+
 // FP32: at least two waves per SIMD (the register budget that LDS allows);
 // FP64 runs one workgroup per CU anyway.
 template <typename Real, int TP, bool ADJ>
-__global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevPlan P, DevTiles T, DevWork<Real> K,
+__global__ __launch_bounds__(kPassAThreads, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevPlan P, DevTiles T, DevWork<Real> K,
                                                DevUser U, DevSettings S, int it, int cls_begin,
                                                LdsDims D, int fused) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int NW = TP / 64;
+  constexpr int NT = kPassAThreads, NW = TP / 64;   // NW: waves that hold pairs
   constexpr int LR = ListRegs<TP>::N;
   constexpr int kZS = ZRow<Real>::S, ZR = ZRow<Real>::R;
   const ChunkRec W = T.chunk_rec[cls_begin + xcd_chunk(blockIdx.x, gridDim.x)];
@@ -764,13 +770,13 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
   };
   if (t0 < t1) fetch_pair(rec, tid < ta.y, px, py, pz, du0, dv0, wo0, cam0);
 
-  for (int k = tid; k < W.n_cams * 16; k += TP) sCam[k] = P.cam[16 * W.cam_off + k];
-  for (int k = tid; k < W.n_poses * 12; k += TP) sPose[k] = poses[k];
+  for (int k = tid; k < W.n_cams * 16; k += NT) sCam[k] = P.cam[16 * W.cam_off + k];
+  for (int k = tid; k < W.n_poses * 12; k += NT) sPose[k] = poses[k];
   {
     // the partial starts 16 bytes aligned; the last store may run into sBnd,
     // which is written before it is read
     const int nz = (int)(((nblk * kBS + 2 * nS) * sizeof(Real) + 15) / 16);
-    for (int k = tid; k < nz; k += TP) reinterpret_cast<float4*>(sS)[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k = tid; k < nz; k += NT) reinterpret_cast<float4*>(sS)[k] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   if (tid == 0) sFlag[0] = 0;
   __syncthreads();
@@ -795,7 +801,7 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
     // every path keep the counter waits exact)
     const int lt = l0 + min(tid, nL > 0 ? nL - 1 : 0);
     const int lq0 = P.lm_pair_begin[lt] - p0, lq1 = P.lm_pair_begin[lt + 1] - p0;
-    const bool lregs = nwords <= LR * TP;
+    const bool lregs = nwords <= LR * NT;
     uint32_t lwv[LR];
     if (lregs) {
       // unconditional loads (clamped to the tile's last word; the table ends
@@ -803,7 +809,7 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
       // prefetches issued after them
       const int last = nwords > 0 ? nwords - 1 : 0;
 #pragma unroll
-      for (int k = 0; k < LR; ++k) lwv[k] = T.lists[lw0 + min(tid + k * TP, last)];
+      for (int k = 0; k < LR; ++k) lwv[k] = T.lists[lw0 + min(tid + k * NT, last)];
     }
     // In flight during this tile (issued after this tile's own loads: the
     // load counter retires in order, so waiting for the list words does not
@@ -856,11 +862,11 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
     if (lregs) {
 #pragma unroll
       for (int k = 0; k < LR; ++k) {
-        const int i = tid + k * TP;
+        const int i = tid + k * NT;
         if (i < nwords) sLst[i] = lwv[k];
       }
     } else {
-      for (int i = tid; i < nwords; i += TP) sLst[i] = T.lists[lw0 + i];
+      for (int i = tid; i < nwords; i += NT) sLst[i] = T.lists[lw0 + i];
     }
     __syncthreads();
 
@@ -963,8 +969,8 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
 #pragma unroll
       for (int k = 0; k < kPoseSums; ++k) v[k] = (Real)0;
     }
-    run_sums<Real, kPoseSums>(v, slot);
-    {
+    if (NW == NT / 64 || wave < NW) {
+      run_sums<Real, kPoseSums>(v, slot);
       // The last lane of each run holds the run's sum.  A run inside the wave
       // is the only one of its pose in the tile (pairs are ordered by pose):
       // it adds into the partial directly.  The runs holding lane 0 or lane 63
@@ -995,8 +1001,8 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
     // units of every round.  A run spanning waves leaves its pieces in
     // consecutive edge slots: they are summed in wave order in registers and
     // added to the partial once.
-    if (tid >= TP - kPoseSums) {
-      const int k = tid - (TP - kPoseSums);
+    if (tid >= NT - kPoseSums) {
+      const int k = tid - (NT - kPoseSums);
       int sl[2 * NW];
       Real x[2 * NW];
 #pragma unroll
@@ -1031,17 +1037,17 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
     // FP64, 10 attempts, 2 x 6 units against these: 3 free poses 446 -> 409 us a
     // solve, 6 to 8 free poses 122 -> 117 us an attempt.  The adjoint has one
     // pass and keeps the coarse units.
-    if (!ADJ && nseg * 36 <= TP) {
-      schur_fine<Real, TP, 1>(sLst, nseg, sPZ, sS);
-    } else if (!ADJ && nseg * 12 <= TP) {
-      schur_fine<Real, TP, 3>(sLst, nseg, sPZ, sS);
-    } else if (!ADJ && nseg * 6 <= TP) {
-      schur_fine<Real, TP, 6>(sLst, nseg, sPZ, sS);
+    if (!ADJ && nseg * 36 <= NT) {
+      schur_fine<Real, 1>(sLst, nseg, sPZ, sS);
+    } else if (!ADJ && nseg * 12 <= NT) {
+      schur_fine<Real, 3>(sLst, nseg, sPZ, sS);
+    } else if (!ADJ && nseg * 6 <= NT) {
+      schur_fine<Real, 6>(sLst, nseg, sPZ, sS);
     } else {
     const uint16_t* sProd = reinterpret_cast<const uint16_t*>(sLst + nseg);
       constexpr int RG = 2, UPS = 6 / RG;
       const int nun = nseg * UPS;
-      for (int u = tid; u < nun; u += TP) {
+      for (int u = tid; u < nun; u += NT) {
         const uint32_t wd = sLst[u / UPS];
         const int r0 = (u % UPS) * RG;
         const int blk = wd & 1023, start = (wd >> 10) & 8191, len = wd >> 23;
@@ -1128,10 +1134,10 @@ __global__ __launch_bounds__(TP, (sizeof(Real) == 4 ? 2 : 1)) void k_pass_a(DevP
   // ---- chunk partial out (the last tile's phase 4 ended with a barrier)
   Real* part = K.part + W.part_off;
 #pragma unroll 4
-  for (int k = tid; k < nblk * kBS + 2 * nS; k += TP) part[k] = sS[k];
+  for (int k = tid; k < nblk * kBS + 2 * nS; k += NT) part[k] = sS[k];
   // the cost sum and the landmark-gradient maximum in one reduction
   double gm = gmax;
-  const double tot = block_sum_max<TP>(cost, gm, sRed);
+  const double tot = block_sum_max<NT>(cost, gm, sRed);
   if (tid == 0) {
     K.part_cost_a[chunk] = tot;
     K.part_flag_a[chunk] = sFlag[0];
@@ -2049,79 +2055,85 @@ hipError_t set_attrs() {
                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
 }
 
-// Pass A over the size classes, each launch with the LDS its largest window
-// needs.  With side streams, the largest class and the next one each run on a
-// side stream, concurrently with the rest on the launch stream: the classes
-// share the CUs, so one class's long workgroups fill the others' launch tails,
-// and workgroups of a small class fit beside one of the largest class in the
+// One pass-A launch of size class c on stream st, with the LDS its largest window
+// needs.
+template <typename Real, bool ADJ>
+void launch_pass_a_class(const LaunchArgs& A, const DevWork<Real>& K, int it, int c, hipStream_t st) {
+  const int n = A.cls_begin[c + 1] - A.cls_begin[c];
+  if (n <= 0) return;
+  auto go = [&](auto tp) {
+    constexpr int TP = decltype(tp)::value;
+    const size_t lds = pass_a_lds<Real, TP>(A.dims.np, A.dims.nc, A.cls_nf[c], A.cls_list_bytes[c], ADJ);
+    hipLaunchKernelGGL((k_pass_a<Real, TP, ADJ>), dim3(n), dim3(kPassAThreads), lds, st, A.plan, A.tiles, K, A.user,
+                       A.settings, it, A.cls_begin[c], A.dims, A.fused);
+  };
+  if (A.cls_tp[c] == kTileLarge) go(std::integral_constant<int, kTileLarge>());
+  else go(std::integral_constant<int, kTileSmall>());
+}
+
+// Pass A over the size classes.  With side streams, the largest class and the next
+// one each run on a side stream, concurrently with the rest on the launch stream: the
+// classes share the CUs, so one class's long workgroups fill the others' launch
+// tails, and workgroups of a small class fit beside one of the largest class in the
 // LDS of a CU (measured on the 256-window batch: +21 % LM attempts per second
 // over the four launches in sequence; merging classes of equal occupancy into
 // one launch gained 6 %).
-struct PassAGroup {
-  int begin, n;
-  size_t lds;
-  int stream;   // 0: the launch stream, k > 0: side stream k - 1
-};
-
-template <typename Real, int TP, bool ADJ>
-int pass_a_groups(const LaunchArgs& A, PassAGroup* g) {
-  int ng = 0;
-  for (int c = 0; c < kClasses; ++c) {
-    const int n = A.cls_begin[c + 1] - A.cls_begin[c];
-    if (n <= 0) continue;
-    const size_t lds = pass_a_lds<Real, TP>(A.dims.np, A.dims.nc, A.cls_nf[c], A.list_bytes, ADJ);
-    g[ng++] = PassAGroup{A.cls_begin[c], n, lds, 0};
-  }
-  if (A.side_stream && ng >= 2) {
-    g[ng - 1].stream = 1;
-    if (ng >= 3) g[ng - 2].stream = 2;
-  }
-  return ng;
-}
-
-template <typename Real, int TP, bool ADJ>
+template <typename Real, bool ADJ>
 hipError_t launch_pass_a(const LaunchArgs& A, const DevWork<Real>& K, int it) {
   static_assert(kSideStreams >= 2, "pass A uses two side streams");
-  PassAGroup g[kClasses];
-  const int ng = pass_a_groups<Real, TP, ADJ>(A, g);
   const hipStream_t main = (hipStream_t)A.stream;
   const hipStream_t* side = (const hipStream_t*)A.side_stream;
   const hipEvent_t* join = (const hipEvent_t*)A.ev_join;
-  bool used[kSideStreams + 1] = {};
-  for (int k = 0; k < ng; ++k) used[g[k].stream] = true;
-  bool fork = false;
-  for (int s = 1; s <= kSideStreams; ++s) fork = fork || used[s];
+  int cls[kClasses], ng = 0;
+  for (int c = 0; c < kClasses; ++c)
+    if (A.cls_begin[c + 1] > A.cls_begin[c]) cls[ng++] = c;
+  const int nside = A.side_stream && ng >= 2 ? (ng >= 3 ? 2 : 1) : 0;   // the largest nside classes
   hipError_t e = hipSuccess;
-  if (fork && (e = hipEventRecord((hipEvent_t)A.ev_fork, main)) != hipSuccess) return e;
-  for (int s = 1; s <= kSideStreams; ++s)
-    if (used[s] && (e = hipStreamWaitEvent(side[s - 1], (hipEvent_t)A.ev_fork, 0)) != hipSuccess) return e;
-  for (int k = ng - 1; k >= 0; --k)   // side launches first
-    if (g[k].stream)
-      hipLaunchKernelGGL((k_pass_a<Real, TP, ADJ>), dim3(g[k].n), dim3(TP), g[k].lds, side[g[k].stream - 1], A.plan,
-                         A.tiles, K, A.user, A.settings, it, g[k].begin, A.dims, A.fused);
-  for (int k = 0; k < ng; ++k)
-    if (!g[k].stream)
-      hipLaunchKernelGGL((k_pass_a<Real, TP, ADJ>), dim3(g[k].n), dim3(TP), g[k].lds, main, A.plan, A.tiles, K,
-                         A.user, A.settings, it, g[k].begin, A.dims, A.fused);
-  for (int s = 1; s <= kSideStreams; ++s)
-    if (used[s]) {
-      if ((e = hipEventRecord(join[s - 1], side[s - 1])) != hipSuccess) return e;
-      if ((e = hipStreamWaitEvent(main, join[s - 1], 0)) != hipSuccess) return e;
-    }
+  if (nside && (e = hipEventRecord((hipEvent_t)A.ev_fork, main)) != hipSuccess) return e;
+  for (int s = 0; s < nside; ++s) {   // side launches first
+    if ((e = hipStreamWaitEvent(side[s], (hipEvent_t)A.ev_fork, 0)) != hipSuccess) return e;
+    launch_pass_a_class<Real, ADJ>(A, K, it, cls[ng - 1 - s], side[s]);
+  }
+  for (int k = 0; k < ng - nside; ++k) launch_pass_a_class<Real, ADJ>(A, K, it, cls[k], main);
+  for (int s = 0; s < nside; ++s) {
+    if ((e = hipEventRecord(join[s], side[s])) != hipSuccess) return e;
+    if ((e = hipStreamWaitEvent(main, join[s], 0)) != hipSuccess) return e;
+  }
   return hipGetLastError();
 }
 
+// Pass B over the chunks of the size classes [ca, cb): neighbouring classes of one
+// tile size share a launch.
+template <typename Real, bool ADJ>
+void launch_pass_b(const LaunchArgs& A, const DevWork<Real>& K, int it, int ca, int cb, hipStream_t st) {
+  for (int c = ca; c < cb;) {
+    int d = c + 1;
+    while (d < cb && A.cls_tp[d] == A.cls_tp[c]) ++d;
+    const int n = A.cls_begin[d] - A.cls_begin[c];
+    auto go = [&](auto tp) {
+      constexpr int TP = decltype(tp)::value;
+      const size_t lds = pass_b_lds<Real, TP>();
+      hipLaunchKernelGGL((k_pass_b<Real, TP, ADJ>), dim3(n), dim3(TP), lds, st, A.plan, A.tiles, K, A.user, A.settings,
+                         it, A.cls_begin[c]);
+    };
+    if (n > 0) {
+      if (A.cls_tp[c] == kTileLarge) go(std::integral_constant<int, kTileLarge>());
+      else go(std::integral_constant<int, kTileSmall>());
+    }
+    c = d;
+  }
+}
 
-// The stages after pass A of one LM attempt for the windows [wb, wb + nwin) of
-// win_order (at most nf free poses each) and their chunks [cb, cb + nch) of
-// chunk_order, on stream st.
-template <typename Real, int TP, bool ADJ>
-void launch_stages(const LaunchArgs& A, const DevWork<Real>& K, int it, int wb, int nwin, int cb, int nch, int nf,
-                   int slices, hipStream_t st) {
+// The stages after pass A of one LM attempt for the windows of the size classes
+// [ca, cb) (at most nf free poses each) on stream st.
+template <typename Real, bool ADJ>
+void launch_stages(const LaunchArgs& A, const DevWork<Real>& K, int it, int ca, int cb, int nf, int slices,
+                   hipStream_t st) {
+  const int wb = A.cls_win_begin[ca], nwin = A.cls_win_begin[cb] - wb;
   if (nwin <= 0) return;
-  const size_t lb = pass_b_lds<Real, TP>(), lr = reduce_lds(nf);
-  hipLaunchKernelGGL(k_sum<Real>, dim3(nwin, slices), dim3(256), 0, st, A.plan, A.tiles, K, A.user,
-                     A.settings, it, wb, A.fused);
+  const size_t lr = reduce_lds(nf);
+  hipLaunchKernelGGL(k_sum<Real>, dim3(nwin, slices), dim3(256), 0, st, A.plan, A.tiles, K, A.user, A.settings, it, wb,
+                     A.fused);
   ViArgs V;
   if (!ADJ && A.vi) {
     V = *static_cast<const ViArgs*>(A.vi);
@@ -2131,22 +2143,10 @@ void launch_stages(const LaunchArgs& A, const DevWork<Real>& K, int it, int wb, 
   hipLaunchKernelGGL((k_reduce<Real, kReduceThreads, ADJ>), dim3(nwin), dim3(kReduceThreads), lr, st, A.plan, A.tiles,
                      K, A.user, A.settings, it, wb);
   if (!ADJ && A.vi) launch_vi_cand(V, wb, nwin, st);
-  if (nch > 0)
-    hipLaunchKernelGGL((k_pass_b<Real, TP, ADJ>), dim3(nch), dim3(TP), lb, st, A.plan, A.tiles, K, A.user, A.settings,
-                       it, cb);
+  launch_pass_b<Real, ADJ>(A, K, it, ca, cb, st);
   if (!ADJ && !A.fused)
     hipLaunchKernelGGL(k_accept<Real>, dim3((nwin + 3) / 4), dim3(256), 0, st, A.plan, A.tiles, K, A.user,
                        A.settings, it, wb, nwin);
-}
-
-// One pass-A launch of size class c on stream st.
-template <typename Real, int TP, bool ADJ>
-void launch_pass_a_class(const LaunchArgs& A, const DevWork<Real>& K, int it, int c, hipStream_t st) {
-  const int n = A.cls_begin[c + 1] - A.cls_begin[c];
-  if (n <= 0) return;
-  const size_t lds = pass_a_lds<Real, TP>(A.dims.np, A.dims.nc, A.cls_nf[c], A.list_bytes, ADJ);
-  hipLaunchKernelGGL((k_pass_a<Real, TP, ADJ>), dim3(n), dim3(TP), lds, st, A.plan, A.tiles, K, A.user, A.settings, it,
-                     A.cls_begin[c], A.dims, A.fused);
 }
 
 // The windows of one size class never meet those of another, so with side
@@ -2202,16 +2202,14 @@ inline hipError_t join_chains(const LaunchArgs& A, const ClassChains& C) {
 }
 
 // One attempt of class C.cls[k] on its chain's stream.
-template <typename Real, int TP, bool ADJ>
+template <typename Real, bool ADJ>
 void launch_class_attempt(const LaunchArgs& A, const DevWork<Real>& K, int it, const ClassChains& C, int k) {
   const int c = C.cls[k];
-  launch_pass_a_class<Real, TP, ADJ>(A, K, it, c, C.st[k]);
-  launch_stages<Real, TP, ADJ>(A, K, it, A.cls_win_begin[c], A.cls_win_begin[c + 1] - A.cls_win_begin[c],
-                               A.cls_begin[c], A.cls_begin[c + 1] - A.cls_begin[c], A.cls_win_nf[c],
-                               A.cls_sum_slices[c], C.st[k]);
+  launch_pass_a_class<Real, ADJ>(A, K, it, c, C.st[k]);
+  launch_stages<Real, ADJ>(A, K, it, c, c + 1, A.cls_win_nf[c], A.cls_sum_slices[c], C.st[k]);
 }
 
-template <typename Real, int TP>
+template <typename Real>
 hipError_t run_solve(const LaunchArgs& A, const DevWork<Real>& K) {
   const int nw = A.plan.n_windows, nc = A.tiles.n_chunks;
   const hipStream_t main = (hipStream_t)A.stream;
@@ -2223,22 +2221,22 @@ hipError_t run_solve(const LaunchArgs& A, const DevWork<Real>& K) {
   if (C.n > 0 && iters > 0) {
     if ((e = fork_chains(A, C)) != hipSuccess) return e;
     for (int it = 0; it < iters; ++it)
-      for (int k = C.n - 1; k >= 0; --k) launch_class_attempt<Real, TP, false>(A, K, it, C, k);
+      for (int k = C.n - 1; k >= 0; --k) launch_class_attempt<Real, false>(A, K, it, C, k);
     if ((e = join_chains(A, C)) != hipSuccess) return e;
   } else {
     for (int it = 0; it < iters; ++it) {
-      if ((e = launch_pass_a<Real, TP, false>(A, K, it)) != hipSuccess) return e;
-      launch_stages<Real, TP, false>(A, K, it, 0, nw, 0, nc, A.max_nf, A.sum_slices, main);
+      if ((e = launch_pass_a<Real, false>(A, K, it)) != hipSuccess) return e;
+      launch_stages<Real, false>(A, K, it, 0, kClasses, A.max_nf, A.sum_slices, main);
     }
   }
-  if (iters == 0 && (e = launch_pass_a<Real, TP, false>(A, K, 0)) != hipSuccess)   // the report still needs the input cost
+  if (iters == 0 && (e = launch_pass_a<Real, false>(A, K, 0)) != hipSuccess)   // the report still needs the input cost
     return e;
   hipLaunchKernelGGL(k_finalize<Real>, dim3(nw), dim3(256), 0, main, A.plan, K, A.user, A.settings, A.fused);
   return hipGetLastError();
 }
 
 // The adjoint's single pass, in the same class chains as a solve.
-template <typename Real, int TP>
+template <typename Real>
 hipError_t run_adjoint(const LaunchArgs& A, const DevWork<Real>& K) {
   const int nw = A.plan.n_windows, nc = A.tiles.n_chunks;
   const hipStream_t main = (hipStream_t)A.stream;
@@ -2248,11 +2246,11 @@ hipError_t run_adjoint(const LaunchArgs& A, const DevWork<Real>& K) {
   hipError_t e = hipSuccess;
   if (C.n > 0) {
     if ((e = fork_chains(A, C)) != hipSuccess) return e;
-    for (int k = C.n - 1; k >= 0; --k) launch_class_attempt<Real, TP, true>(A, K, 0, C, k);
+    for (int k = C.n - 1; k >= 0; --k) launch_class_attempt<Real, true>(A, K, 0, C, k);
     if ((e = join_chains(A, C)) != hipSuccess) return e;
   } else {
-    if ((e = launch_pass_a<Real, TP, true>(A, K, 0)) != hipSuccess) return e;
-    launch_stages<Real, TP, true>(A, K, 0, 0, nw, 0, nc, A.max_nf, A.sum_slices, main);
+    if ((e = launch_pass_a<Real, true>(A, K, 0)) != hipSuccess) return e;
+    launch_stages<Real, true>(A, K, 0, 0, kClasses, A.max_nf, A.sum_slices, main);
   }
   return hipGetLastError();
 }
@@ -2262,11 +2260,11 @@ hipError_t run_adjoint(const LaunchArgs& A, const DevWork<Real>& K) {
 // HIP events between the stages: the summed device time of each stage
 // (pass_a, reduce, pass_b, accept) in ms, for the roofline figures of the
 // benchmark.  Synchronises on the stream.
-template <typename Real, int TP>
+template <typename Real>
 hipError_t run_solve_timed(const LaunchArgs& A, const DevWork<Real>& K, double* stage_ms) {
   const int nw = A.plan.n_windows, nc = A.tiles.n_chunks;
   const hipStream_t main = (hipStream_t)A.stream;
-  const size_t lb = pass_b_lds<Real, TP>(), lr = reduce_lds(A.max_nf);
+  const size_t lr = reduce_lds(A.max_nf);
   const int iters = A.settings.max_iters;
   const int nev = 4 * iters + 1;
   hipEvent_t* ev = new hipEvent_t[nev];
@@ -2276,15 +2274,14 @@ hipError_t run_solve_timed(const LaunchArgs& A, const DevWork<Real>& K, double* 
   (void)hipEventRecord(ev[0], main);
   hipError_t e = hipSuccess;
   for (int it = 0; it < iters && e == hipSuccess; ++it) {
-    e = launch_pass_a<Real, TP, false>(A, K, it);
+    e = launch_pass_a<Real, false>(A, K, it);
     (void)hipEventRecord(ev[4 * it + 1], main);
     hipLaunchKernelGGL(k_sum<Real>, dim3(nw, A.sum_slices), dim3(256), 0, main, A.plan, A.tiles, K, A.user,
                        A.settings, it, 0, 0);
     hipLaunchKernelGGL((k_reduce<Real, kReduceThreads, false>), dim3(nw), dim3(kReduceThreads), lr, main, A.plan,
                        A.tiles, K, A.user, A.settings, it, 0);
     (void)hipEventRecord(ev[4 * it + 2], main);
-    hipLaunchKernelGGL((k_pass_b<Real, TP, false>), dim3(nc), dim3(TP), lb, main, A.plan, A.tiles, K, A.user,
-                       A.settings, it, 0);
+    launch_pass_b<Real, false>(A, K, it, 0, kClasses, main);
     (void)hipEventRecord(ev[4 * it + 3], main);
     hipLaunchKernelGGL(k_accept<Real>, dim3((nw + 3) / 4), dim3(256), 0, main, A.plan, A.tiles, K, A.user,
                        A.settings, it, 0, nw);
@@ -2322,17 +2319,11 @@ template hipError_t set_attrs<double, 64, true>();
 template hipError_t set_attrs<double, 256, true>();
 template hipError_t set_attrs<float, 64, true>();
 template hipError_t set_attrs<float, 256, true>();
-template hipError_t run_solve<double, 64>(const LaunchArgs&, const DevWork<double>&);
-template hipError_t run_solve<double, 256>(const LaunchArgs&, const DevWork<double>&);
-template hipError_t run_solve<float, 64>(const LaunchArgs&, const DevWork<float>&);
-template hipError_t run_solve<float, 256>(const LaunchArgs&, const DevWork<float>&);
-template hipError_t run_solve_timed<double, 64>(const LaunchArgs&, const DevWork<double>&, double*);
-template hipError_t run_solve_timed<double, 256>(const LaunchArgs&, const DevWork<double>&, double*);
-template hipError_t run_solve_timed<float, 64>(const LaunchArgs&, const DevWork<float>&, double*);
-template hipError_t run_solve_timed<float, 256>(const LaunchArgs&, const DevWork<float>&, double*);
-template hipError_t run_adjoint<double, 64>(const LaunchArgs&, const DevWork<double>&);
-template hipError_t run_adjoint<double, 256>(const LaunchArgs&, const DevWork<double>&);
-template hipError_t run_adjoint<float, 64>(const LaunchArgs&, const DevWork<float>&);
-template hipError_t run_adjoint<float, 256>(const LaunchArgs&, const DevWork<float>&);
+template hipError_t run_solve<double>(const LaunchArgs&, const DevWork<double>&);
+template hipError_t run_solve<float>(const LaunchArgs&, const DevWork<float>&);
+template hipError_t run_solve_timed<double>(const LaunchArgs&, const DevWork<double>&, double*);
+template hipError_t run_solve_timed<float>(const LaunchArgs&, const DevWork<float>&, double*);
+template hipError_t run_adjoint<double>(const LaunchArgs&, const DevWork<double>&);
+template hipError_t run_adjoint<float>(const LaunchArgs&, const DevWork<float>&);
 
 }  // namespace ba

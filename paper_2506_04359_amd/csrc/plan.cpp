@@ -200,7 +200,7 @@ std::string build_window(int32_t n_poses, int32_t n_points, int32_t n_cams, int6
 }
 
 void build_tiles(const std::vector<const HostWindow*>& wins, int tp, int chunk_obs,
-                 LaunchTables& t, const int* class_mult) {
+                 LaunchTables& t, const int* class_mult, const int* class_tp) {
   t.tp = tp;
   t.chunk_obs = chunk_obs;
   t.tile_lm_begin.clear();
@@ -213,9 +213,12 @@ void build_tiles(const std::vector<const HostWindow*>& wins, int tp, int chunk_o
   t.tile_rec.clear();
   t.lists.clear();
   t.max_tile_prods = t.max_tile_segs = t.max_tile_words = 0;
+  std::fill(t.class_tile_words, t.class_tile_words + kClasses, 0);
   int32_t lm_base = 0, pair_base = 0, obs_base = 0;
   for (size_t wi = 0; wi < wins.size(); ++wi) {
     const HostWindow& w = *wins[wi];
+    const int cls = size_class(w.n_free);
+    if (class_tp) tp = class_tp[cls];
     // tiles: whole landmarks, at most tp pairs and tp / 2 landmarks
     std::vector<int32_t> tiles;      // window-local landmark starts
     std::vector<int64_t> tile_obs;   // observations per tile
@@ -308,6 +311,7 @@ void build_tiles(const std::vector<const HostWindow*>& wins, int tp, int chunk_o
       t.max_tile_prods = std::max(t.max_tile_prods, start);
       t.max_tile_segs = std::max(t.max_tile_segs, (int32_t)order.size());
       t.max_tile_words = std::max(t.max_tile_words, (int32_t)t.lists.size() - word_first);
+      t.class_tile_words[cls] = std::max(t.class_tile_words[cls], (int32_t)t.lists.size() - word_first);
       const int32_t rec[8] = {pair_base + p0, p1 - p0, lm_base + la, lb - la,
                               word_first, (int32_t)order.size(), start, 0};
       t.tile_rec.insert(t.tile_rec.end(), rec, rec + 8);

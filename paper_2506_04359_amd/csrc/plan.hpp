@@ -102,6 +102,7 @@ struct LaunchTables {
   // (qa | qc << 8 as 16-bit halves).
   std::vector<uint32_t> lists;
   int32_t max_tile_prods = 0, max_tile_segs = 0, max_tile_words = 0;
+  int32_t class_tile_words[kClasses] = {0, 0, 0, 0};   // largest tile list of each class
   int32_t n_tiles() const { return (int32_t)tile_lm_begin.size() - 1; }
   int32_t n_chunks() const { return (int32_t)chunk_window.size(); }
 };
@@ -121,9 +122,10 @@ inline int size_class(int n_free) {
 
 // Tiles, product lists and work items of a launch: tiles of at most tp pairs,
 // work items of about chunk_obs x class_mult[size class] observations
-// (class_mult NULL: 1 for every class).
+// (class_mult NULL: 1 for every class).  class_tp: the tile size of each size
+// class (NULL: tp for every class).
 void build_tiles(const std::vector<const HostWindow*>& wins, int tp, int chunk_obs,
-                 LaunchTables& out, const int* class_mult = nullptr);
+                 LaunchTables& out, const int* class_mult = nullptr, const int* class_tp = nullptr);
 
 // Packed fields of the plan tables and the limits that keep them in range.
 //   segment word : blk (10 bits) | first product (13 bits) | count (9 bits)
