@@ -8,7 +8,11 @@
 // the poses a workgroup reads span a range that, times the camera count, is at
 // most 128, the world-to-camera transforms T_cb T_bw_i of that range are
 // composed once into LDS, so each observation needs one transform and the
-// Jacobian is A R_cw directly.
+// Jacobian is A R_cw directly.  The workgroup's observations are then staged
+// in LDS too (pixel minus principal point, transform, weight), read once in
+// order: a lane walks its own range, so reading them from memory in every pass
+// touched a cache line per lane and load, and those loads bound the kernel
+// (1 M landmarks, 5.9 M observations, 12 passes: 626 -> 324 us).
 //   start     the weighted least-squares intersection of the viewing rays,
 //             (sum w (I - d d^T)) p0 = sum w (I - d d^T) c, by a 3x3 FP64
 //             Cholesky; fewer than two views or a pivot <= 1e-10 trace marks
@@ -32,8 +36,21 @@
 
 namespace ba {
 
-constexpr int kTriThreads = 256;
 constexpr int kTriPoseCache = 128;   // (pose, camera) transforms a workgroup keeps in LDS
+// Stride of a transform's record in doubles: 16 are used, and 18 keep the records 16
+// bytes aligned while records that lanes read together start in different banks.
+constexpr int kTriRec = 18;
+// Waves per SIMD the kernel is compiled for, and the LDS of a workgroup for its
+// transforms and observations.  256 threads: four waves (128 registers, a few
+// spilled) in FP32 measured 324 us against 363 with three, at 1 M landmarks; FP64
+// accumulators would spill 177 registers there, so it keeps three.  Smaller
+// workgroups, for longer tracks, run two.
+template <typename Real, int NT>
+constexpr int tri_waves() { return NT < 256 ? 2 : sizeof(Real) == 4 ? 4 : 3; }
+template <typename Real, int NT>
+constexpr int tri_pool() {
+  return (NT == 256 ? (sizeof(Real) == 4 ? 34 : 40) : NT == 128 ? 36 : 20) * 1024;
+}
 
 // Cholesky solve of a 3x3 SPD system stored as (00, 01, 02, 11, 12, 22):
 // x = A^-1 b.  False on a pivot <= floor or a non-finite one.
@@ -63,15 +80,24 @@ __device__ __forceinline__ bool solve3(const double* A, const double* b, double 
 __device__ int kTriCamZero = 0;
 __device__ double kTriWeightOne = 1.0;
 
+// A workgroup's observations in LDS, from observation `first` on.
+struct TriStage {
+  long long first;
+  const double2* d;     // u - cx, v - cy
+  const double* w;      // weights (NULL: all 1)
+  const uint8_t* rec;   // record of the composed transform
+};
+
 // Ray start and LM refinement of landmark j (observations [o0, o1), indices
 // already checked).  COMPOSED: P holds, per (pose i, camera c) at
-// 16 ((i - pbase) n_cams + c), the camera record with the world-to-camera
+// kTriRec ((i - pbase) n_cams + c), the camera record with the world-to-camera
 // transform T_cb T_bw_i in place of T_cb (so the point goes to the camera in
 // one transform and A R_cw is the Jacobian); otherwise P holds the poses
-// (at 12 (i - pbase)) and the cameras come from sCam.
-template <typename Real, bool COMPOSED>
+// (at 12 (i - pbase)) and the cameras come from sCam.  STAGED (composed): the
+// observations come from G.
+template <typename Real, bool COMPOSED, bool STAGED>
 __device__ __forceinline__ void tri_landmark(const TriArgs& A, int j, long long o0, long long o1,
-                                             const double* sCam, const double* P, int pbase) {
+                                             const double* sCam, const double* P, int pbase, const TriStage& G) {
   const DevSettings S = A.settings;
   const double kNaN = __builtin_nan("");
   const int* cp = A.obs_cam ? A.obs_cam : &kTriCamZero;
@@ -98,21 +124,33 @@ __device__ __forceinline__ void tri_landmark(const TriArgs& A, int j, long long 
   };
   if (o1 - o0 < 2) return finish(3, nullptr);
 
-  // One observation: pose index, camera, pixel, weight.  The loops below load
-  // observation o + 1 while observation o is computed.
+  // One observation: pose index (relative to pbase) and camera, or the transform's
+  // record; pixel minus principal point; weight.  The loops below load observation
+  // o + 1 while observation o is computed.
   struct Ob {
     int i, c;
     double u, v, w;
   };
   auto load = [&](long long o) {
     Ob b;
-    b.i = A.obs_pose[o];
-    b.c = cp[o * cstep];
-    b.u = A.obs_uv[2 * o];
-    b.v = A.obs_uv[2 * o + 1];
-    b.w = wp[o * wstep];
+    if constexpr (STAGED) {
+      const int k = (int)(o - G.first);
+      const double2 d = G.d[k];
+      b.u = d.x;
+      b.v = d.y;
+      b.i = G.rec[k];
+      b.c = 0;
+      b.w = G.w ? G.w[k] : 1.0;
+    } else {
+      b.i = A.obs_pose[o] - pbase;
+      b.c = cp[o * cstep];
+      b.u = A.obs_uv[2 * o];
+      b.v = A.obs_uv[2 * o + 1];
+      b.w = wp[o * wstep];
+    }
     return b;
   };
+  auto record = [&](const Ob& b) { return P + kTriRec * (STAGED ? b.i : b.i * A.n_cams + b.c); };
 
   // start: least-squares intersection of the viewing rays
   double M[6] = {0, 0, 0, 0, 0, 0}, mb[3] = {0, 0, 0};
@@ -123,13 +161,13 @@ __device__ __forceinline__ void tri_landmark(const TriArgs& A, int j, long long 
       double Rcw[9], tcw[3];
       const double* C;
       if constexpr (COMPOSED) {
-        C = P + 16 * ((cur.i - pbase) * A.n_cams + cur.c);
+        C = record(cur);
 #pragma unroll
         for (int k = 0; k < 9; ++k) Rcw[k] = C[4 + k];
 #pragma unroll
         for (int a = 0; a < 3; ++a) tcw[a] = C[13 + a];
       } else {
-        const double* T = P + 12 * (cur.i - pbase);
+        const double* T = P + 12 * cur.i;
         C = sCam + 16 * cur.c;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -139,7 +177,7 @@ __device__ __forceinline__ void tri_landmark(const TriArgs& A, int j, long long 
           tcw[a] = C[4 + 3 * a] * T[3] + C[5 + 3 * a] * T[7] + C[6 + 3 * a] * T[11] + C[13 + a];
         }
       }
-      const double v[3] = {(cur.u - C[2]) / C[0], (cur.v - C[3]) / C[1], 1.0};
+      const double v[3] = {(STAGED ? cur.u : cur.u - C[2]) / C[0], (STAGED ? cur.v : cur.v - C[3]) / C[1], 1.0};
       double d[3], ctr[3];
 #pragma unroll
       for (int b = 0; b < 3; ++b) {   // world direction R_cw^T v and centre -R_cw^T t_cw
@@ -183,15 +221,15 @@ __device__ __forceinline__ void tri_landmark(const TriArgs& A, int j, long long 
       if constexpr (COMPOSED) {
         // the record's transform takes the world point to the camera: the
         // rows of A R_cw are the Jacobian
-        const double* C = P + 16 * ((cur.i - pbase) * A.n_cams + cur.c);
-        L = linearise<Real>(q, C, cur.u - C[2], cur.v - C[3], cur.w, S.huber_delta);
+        const double* C = record(cur);
+        L = linearise<Real>(q, C, STAGED ? cur.u : cur.u - C[2], STAGED ? cur.v : cur.v - C[3], cur.w, S.huber_delta);
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
           J0[b] = L.a0[b];
           J1[b] = L.a1[b];
         }
       } else {
-        const double* T = P + 12 * (cur.i - pbase);
+        const double* T = P + 12 * cur.i;
         const double* C = sCam + 16 * cur.c;
         double xb[3];
 #pragma unroll
@@ -290,52 +328,102 @@ __device__ __forceinline__ void tri_landmark(const TriArgs& A, int j, long long 
   }
 }
 
-template <typename Real>
-__global__ __launch_bounds__(kTriThreads) void k_tri(TriArgs A) {
+template <typename Real, int NT>
+__global__ __launch_bounds__(NT, (tri_waves<Real, NT>())) void k_tri(TriArgs A) {
+  constexpr int NW = NT / 64, kBins = 64;
   __shared__ double sCam[kMaxCams * 16];
-  __shared__ double sComp[kTriPoseCache * 16];
-  __shared__ int sCount[kTriThreads];
-  __shared__ int sOrder[kTriThreads];
-  __shared__ int sRange[2][kTriThreads / 64];
-  for (int k = threadIdx.x; k < A.n_cams * 16; k += blockDim.x) sCam[k] = A.cams[k];
-  // Lanes take the workgroup's landmarks in order of observation count (ties
-  // by index), so that the lanes of a wave run loops of similar length.
+  __shared__ __align__(16) unsigned char sPool[tri_pool<Real, NT>()];   // transforms, then the observations
+  __shared__ int sBin[kBins];
+  __shared__ int sOrder[NT];
+  __shared__ int sRange[2][NW];
+  __shared__ long long sObs[2][NW];
+  const int tid = threadIdx.x;
+  for (int k = tid; k < A.n_cams * 16; k += NT) sCam[k] = A.cams[k];
+  // Lanes take the workgroup's landmarks in order of observation count, so that
+  // the lanes of a wave run loops of similar length (a counting sort; the order of
+  // equal counts is of no consequence, as a landmark's result depends on nothing
+  // else).
   {
-    const int jj = blockIdx.x * kTriThreads + threadIdx.x;
-    long long n = 1ll << 30;   // past the end: sorted last
+    const int jj = blockIdx.x * NT + tid;
+    int n = kBins - 1;   // past the end: sorted last
     if (jj < A.n_points) {
-      n = (long long)A.point_obs_begin[jj + 1] - A.point_obs_begin[jj];
-      n = n < 0 ? 0 : (n > (1ll << 29) ? (1ll << 29) : n);
+      const long long m = (long long)A.point_obs_begin[jj + 1] - A.point_obs_begin[jj];
+      n = m < 0 ? 0 : (m > kBins - 2 ? kBins - 2 : (int)m);
     }
-    sCount[threadIdx.x] = (int)n;
+    if (tid < kBins) sBin[tid] = 0;
     __syncthreads();
-    int rank = 0;
-    for (int k = 0; k < kTriThreads; ++k) {
-      const int c = sCount[k];
-      rank += (c < (int)n || (c == (int)n && k < (int)threadIdx.x)) ? 1 : 0;
+    atomicAdd(&sBin[n], 1);
+    __syncthreads();
+    if (tid < kBins) {   // exclusive prefix sum by the first wave
+      const int own = sBin[tid];
+      int v = own;
+#pragma unroll
+      for (int o = 1; o < kBins; o <<= 1) {
+        const int u = __shfl_up(v, o, 64);
+        if (tid >= o) v += u;
+      }
+      sBin[tid] = v - own;
     }
-    sOrder[rank] = threadIdx.x;
+    __syncthreads();
+    sOrder[atomicAdd(&sBin[n], 1)] = tid;
     __syncthreads();
   }
-  const int j = blockIdx.x * kTriThreads + sOrder[threadIdx.x];
+  const int j = blockIdx.x * NT + sOrder[tid];
 
-  // structure checks, and the range of pose indices the workgroup reads
-  int status = 0, pmin = 0x7fffffff, pmax = -1;
-  long long o0 = 0, o1 = 0;
+  // the landmark's range, and the range of observations the workgroup reads
+  int status = 0;
+  long long o0 = 0, o1 = 0, omin = 1ll << 62, omax = -1;
   if (j < A.n_points) {
     o0 = A.point_obs_begin[j];
     o1 = A.point_obs_begin[j + 1];
     if (!(0 <= o0 && o0 <= o1 && o1 <= A.n_obs)) {
       status = 2;
-    } else {
-      for (long long o = o0; o < o1; ++o) {
-        const int i = A.obs_pose[o], c = A.obs_cam ? A.obs_cam[o] : 0;
-        if (i < 0 || i >= A.n_poses || c < 0 || c >= A.n_cams) status = 2;
-        pmin = i < pmin ? i : pmin;
-        pmax = i > pmax ? i : pmax;
-      }
+      o0 = o1 = 0;
+    } else if (o0 < o1) {
+      omin = o0;
+      omax = o1;
     }
-    if (status) pmin = 0x7fffffff, pmax = -1;
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    const long long a = __shfl_xor(omin, m), b = __shfl_xor(omax, m);
+    omin = a < omin ? a : omin;
+    omax = b > omax ? b : omax;
+  }
+  if ((tid & 63) == 0) {
+    sObs[0][tid >> 6] = omin;
+    sObs[1][tid >> 6] = omax;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    omin = sObs[0][w] < omin ? sObs[0][w] : omin;
+    omax = sObs[1][w] > omax ? sObs[1][w] : omax;
+  }
+  // Can the observations be staged, whatever the poses need?  (A landmark list in
+  // no order, or a very long track, gives a range that does not fit.)
+  const long long nobs = omax > omin ? omax - omin : 0;
+  const int per = A.obs_w ? 25 : 17;   // bytes of one observation: two doubles, a byte [, the weight]
+  const bool maybe = nobs > 0 && nobs * per + 32 <= (tri_pool<Real, NT>());
+
+  // structure checks and the range of pose indices: over the workgroup's
+  // observations in order when they are to be staged (those of no valid index are
+  // marked below), else over each landmark's own
+  int pmin = 0x7fffffff, pmax = -1;
+  auto look = [&](long long o) {
+    const int i = A.obs_pose[o], c = A.obs_cam ? A.obs_cam[o] : 0;
+    const bool ok = i >= 0 && i < A.n_poses && c >= 0 && c < A.n_cams;
+    if (ok) {
+      pmin = i < pmin ? i : pmin;
+      pmax = i > pmax ? i : pmax;
+    }
+    return ok;
+  };
+  if (maybe) {
+    for (long long o = omin + tid; o < omax; o += NT) look(o);
+  } else {
+    for (long long o = o0; o < o1; ++o)
+      if (!look(o)) status = 2;
   }
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) {
@@ -343,26 +431,32 @@ __global__ __launch_bounds__(kTriThreads) void k_tri(TriArgs A) {
     pmin = a < pmin ? a : pmin;
     pmax = b > pmax ? b : pmax;
   }
-  if ((threadIdx.x & 63) == 0) {
-    sRange[0][threadIdx.x >> 6] = pmin;
-    sRange[1][threadIdx.x >> 6] = pmax;
+  if ((tid & 63) == 0) {
+    sRange[0][tid >> 6] = pmin;
+    sRange[1][tid >> 6] = pmax;
   }
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < kTriThreads / 64; ++w) {
+  for (int w = 0; w < NW; ++w) {
     pmin = sRange[0][w] < pmin ? sRange[0][w] : pmin;
     pmax = sRange[1][w] > pmax ? sRange[1][w] : pmax;
   }
-  // every index was checked against n_poses, so [pmin, pmax] is in range;
+  // only indices checked against n_poses count, so [pmin, pmax] is in range;
   // compose T_cb T_bw_i for every (pose, camera) the range holds
-  const bool cached = pmax >= pmin && (long long)(pmax - pmin + 1) * A.n_cams <= kTriPoseCache;
+  const long long span = pmax >= pmin ? (long long)(pmax - pmin + 1) * A.n_cams : 0;
+  const bool cached = span > 0 && span <= kTriPoseCache;
+  double* sComp = reinterpret_cast<double*>(sPool);
+  const int oD = cached ? (int)span * kTriRec * 8 : 0;   // bytes of the transforms, a multiple of 16
+  static_assert(kTriPoseCache * kTriRec * 8 <= (tri_pool<Real, NT>()), "the transforms fit the pool");
+  static_assert(kTriPoseCache <= 255, "a staged observation's record is a byte, 255 marks a bad index");
+  const bool staged = maybe && cached && oD + nobs * per <= (tri_pool<Real, NT>());
   if (cached) {
-    const int n = (pmax - pmin + 1) * A.n_cams;
-    for (int r = threadIdx.x; r < n; r += blockDim.x) {
+    const int n = (int)span;
+    for (int r = tid; r < n; r += NT) {
       const int i = pmin + r / A.n_cams, c = r % A.n_cams;
       const double* T = A.poses + 12 * (long long)i;
       const double* C = sCam + 16 * c;
-      double* out = sComp + 16 * r;
+      double* out = sComp + kTriRec * r;
       out[0] = C[0];
       out[1] = C[1];
       out[2] = C[2];
@@ -376,8 +470,38 @@ __global__ __launch_bounds__(kTriThreads) void k_tri(TriArgs A) {
       }
     }
   }
+  // the observations behind the transforms: pixels, weights, records
+  TriStage G;
+  double2* sD = reinterpret_cast<double2*>(sPool + oD);
+  double* sW = reinterpret_cast<double*>(sPool + oD + 16 * (staged ? (int)nobs : 0));
+  uint8_t* sRec = sPool + oD + (staged ? (int)nobs * (per - 1) : 0);
+  if (staged) {
+    for (int k = tid; k < (int)nobs; k += NT) {
+      const long long o = omin + k;
+      const int i = A.obs_pose[o], c = A.obs_cam ? A.obs_cam[o] : 0;
+      const double u = A.obs_uv[2 * o], v = A.obs_uv[2 * o + 1];
+      const bool ok = i >= 0 && i < A.n_poses && c >= 0 && c < A.n_cams;
+      const double* C = sCam + 16 * (ok ? c : 0);
+      sD[k] = make_double2(u - C[2], v - C[3]);
+      if (A.obs_w) sW[k] = A.obs_w[o];
+      sRec[k] = ok ? (uint8_t)((i - pmin) * A.n_cams + c) : 255;
+    }
+  }
+  G.first = omin;
+  G.d = sD;
+  G.w = A.obs_w ? sW : nullptr;
+  G.rec = sRec;
   __syncthreads();
   if (j >= A.n_points) return;
+  if (staged) {
+    for (long long o = o0; o < o1; ++o)
+      if (sRec[o - omin] == 255) status = 2;
+  } else if (maybe) {   // looked at in order above: this landmark's own still have to be
+    for (long long o = o0; o < o1; ++o) {
+      const int i = A.obs_pose[o], c = A.obs_cam ? A.obs_cam[o] : 0;
+      if (i < 0 || i >= A.n_poses || c < 0 || c >= A.n_cams) status = 2;
+    }
+  }
   if (status) {
     const double kNaN = __builtin_nan("");
     A.points[3 * (long long)j] = kNaN;
@@ -398,18 +522,31 @@ __global__ __launch_bounds__(kTriThreads) void k_tri(TriArgs A) {
     }
     return;
   }
-  if (cached)
-    tri_landmark<Real, true>(A, j, o0, o1, sCam, sComp, pmin);
+  if (staged)
+    tri_landmark<Real, true, true>(A, j, o0, o1, sCam, sComp, pmin, G);
+  else if (cached)
+    tri_landmark<Real, true, false>(A, j, o0, o1, sCam, sComp, pmin, G);
   else
-    tri_landmark<Real, false>(A, j, o0, o1, sCam, A.poses, 0);
+    tri_landmark<Real, false, false>(A, j, o0, o1, sCam, A.poses, 0, G);
 }
 
+template <typename Real, int NT>
+static hipError_t launch_tri(const TriArgs& A) {
+  const int blocks = (A.n_points + NT - 1) / NT;
+  hipLaunchKernelGGL((k_tri<Real, NT>), dim3(blocks), dim3(NT), 0, (hipStream_t)A.stream, A);
+  return hipGetLastError();
+}
+
+// The largest workgroup whose share of the observations (by the mean per landmark,
+// an eighth to spare) fits its LDS beside about 40 transforms.
 template <typename Real>
 hipError_t run_triangulate(const TriArgs& A) {
   if (A.n_points <= 0) return hipSuccess;
-  const int blocks = (A.n_points + kTriThreads - 1) / kTriThreads;
-  hipLaunchKernelGGL(k_tri<Real>, dim3(blocks), dim3(kTriThreads), 0, (hipStream_t)A.stream, A);
-  return hipGetLastError();
+  const double bytes = (double)A.n_obs / A.n_points * 1.125 * (A.obs_w ? 25 : 17);
+  const double room = 40.0 * kTriRec * 8;
+  if (256 * bytes + room <= (tri_pool<Real, 256>())) return launch_tri<Real, 256>(A);
+  if (128 * bytes + room <= (tri_pool<Real, 128>())) return launch_tri<Real, 128>(A);
+  return launch_tri<Real, 64>(A);
 }
 
 template hipError_t run_triangulate<float>(const TriArgs&);

@@ -154,3 +154,30 @@ def test_mixed_full_batch_sampled():
         if ref.status == 0:
             err = np.abs(g["points"][j] - ref.point).max()
             assert err <= 1e-6 * max(1.0, np.linalg.norm(ref.point)), (j, err)
+
+
+@pytest.mark.parametrize("n_kf,n_lm,weighted,bad", [(3, 1, False, False), (3, 255, True, False), (3, 257, False, True),
+                                                    (10, 129, False, True), (24, 65, True, True),
+                                                    (24, 130, False, False)])
+def test_workgroup_edges(n_kf, n_lm, weighted, bad):
+    """Counts at the edges of the workgroups (256, 128 and 64 landmarks, by the mean
+    track length), with the observations staged in LDS; bad indices inside a
+    staged group mark their own landmark only."""
+    import paper_2506_04359_amd as ba
+    b = bagen.make_tri_batch([bagen.tiny_window(seed=40 + n_lm, n_kf=n_kf, n_lm=n_lm)])
+    s = ba.Settings(max_iters=6, precision=ba.BA_FP64)
+    w = np.random.default_rng(n_lm).uniform(0.3, 2.0, b.n_obs) if weighted else None
+    pose = b.obs_pose.copy()
+    marked = [n_lm // 2, n_lm - 1] if bad else []
+    for j in marked:
+        pose[b.point_obs_begin[j]] = -1 if j == n_lm // 2 else b.n_poses
+    g = _gpu(b, s, obs_w=w, obs_pose=pose)
+    assert [int(j) for j in np.flatnonzero(g["reports"]["status"] == 2)] == marked
+    if not bad:
+        _check_fp64(b, s, g, obs_w=w, every=max(1, n_lm // 40))
+        return
+    clean = _gpu(b, s, obs_w=w)
+    keep = np.setdiff1d(np.arange(n_lm), marked)
+    _check_fp64(b, s, clean, obs_w=w, every=max(1, n_lm // 40))
+    assert np.array_equal(clean["points"][keep], g["points"][keep])
+    assert np.all(np.isnan(g["points"][marked]))
