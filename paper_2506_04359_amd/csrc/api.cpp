@@ -937,15 +937,13 @@ ba_status ba_graph_create(int32_t n_poses, int32_t n_edges, const int32_t* edge_
     return BA_OK;
   }
   Blob blob;
-  const size_t o_cop = blob.add(P.col_of_pose), o_poc = blob.add(P.pose_of_col),
-               o_lev = blob.add(P.lev_ptr), o_bp = blob.add(P.blk_ptr), o_br = blob.add(P.blk_row),
-               o_up = blob.add(P.upd_ptr), o_ua = blob.add(P.upd_a), o_ub = blob.add(P.upd_b),
-               o_fp = blob.add(P.fwd_ptr), o_fb = blob.add(P.fwd_blk), o_fc = blob.add(P.fwd_col),
+  const size_t o_cop = blob.add(P.col_of_pose), o_bp = blob.add(P.blk_ptr), o_br = blob.add(P.blk_row),
                o_ap = blob.add(P.asm_ptr), o_ae = blob.add(P.asm_edge), o_rp = blob.add(P.rhs_ptr),
                o_re = blob.add(P.rhs_edge), o_ei = blob.add(P.edge_i), o_ej = blob.add(P.edge_j),
-               o_bc = blob.add(P.blk_col), o_cp = blob.add(P.chunk_ptr), o_cb = blob.add(P.chunk_blk),
-               o_fcp = blob.add(P.fchunk_ptr), o_fcc = blob.add(P.fchunk_col),
-               o_cab = blob.add(P.chunk_ab), o_fbc = blob.add(P.fchunk_bc);
+               o_cp = blob.add(P.chunk_ptr), o_fcp = blob.add(P.fchunk_ptr), o_cab = blob.add(P.chunk_ab),
+               o_fbc = blob.add(P.fchunk_bc), o_gp = blob.add(P.grp_ptr), o_st = blob.add(P.steps),
+               o_sc = blob.add(P.step_col), o_sb = blob.add(P.step_blk), o_sab = blob.add(P.step_ab),
+               o_sbc = blob.add(P.step_bc);
   hipError_t e = hipGetDevice(&g->device);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
   e = hipMalloc(&g->mem, blob.size);
@@ -953,46 +951,33 @@ ba_status ba_graph_create(int32_t n_poses, int32_t n_edges, const int32_t* edge_
     g->mem = nullptr;
     return set_error(BA_ERR_OOM, "graph plan: hipMalloc failed");
   }
-  for (auto& part : blob.parts)
-    if (!part.second.empty()) {
-      e = hipMemcpy((char*)g->mem + part.first, part.second.data(), part.second.size(),
-                    hipMemcpyHostToDevice);
-      if (e != hipSuccess) return hip_fail(e, "graph plan upload");
-    }
+  if ((e = blob.upload(g->mem)) != hipSuccess) return hip_fail(e, "graph plan upload");
   auto at = [&](size_t off) { return (const int32_t*)((char*)g->mem + off); };
   PgoDev& D = g->dev;
   D.n_poses = P.n_poses;
   D.n_edges = P.n_edges;
   D.n_free = P.n_free;
-  D.n_levels = P.n_levels;
   D.n_blocks = P.n_blocks();
   D.col_of_pose = at(o_cop);
-  D.pose_of_col = at(o_poc);
-  D.lev_ptr = at(o_lev);
   D.blk_ptr = at(o_bp);
   D.blk_row = at(o_br);
-  D.upd_ptr = at(o_up);
-  D.upd_a = at(o_ua);
-  D.upd_b = at(o_ub);
-  D.fwd_ptr = at(o_fp);
-  D.fwd_blk = at(o_fb);
-  D.fwd_col = at(o_fc);
   D.asm_ptr = at(o_ap);
   D.asm_edge = at(o_ae);
   D.rhs_ptr = at(o_rp);
   D.rhs_edge = at(o_re);
   D.edge_i = at(o_ei);
   D.edge_j = at(o_ej);
-  D.blk_col = at(o_bc);
   D.chunk_ptr = at(o_cp);
-  D.chunk_blk = at(o_cb);
   D.fchunk_ptr = at(o_fcp);
-  D.fchunk_col = at(o_fcc);
   D.chunk_ab = at(o_cab);
   D.fchunk_bc = at(o_fbc);
+  D.grp_ptr = at(o_gp);
+  D.steps = at(o_st);
+  D.step_col = at(o_sc);
+  D.step_blk = at(o_sb);
+  D.step_ab = at(o_sab);
+  D.step_bc = at(o_sbc);
   D.n_chunks = (int)P.chunk_blk.size();
-  D.n_fchunks = (int)P.fchunk_col.size();
-  D.n_wide = P.n_wide;
   *out = g.release();
   return BA_OK;
 }
@@ -1051,7 +1036,8 @@ ba_status ba_pgo_solve(ba_graph g, const ba_settings* s, double* poses, const do
   A.traces = traces;
   A.settings = dev_settings(s);
   A.stream = stream;
-  A.wide_tasks = g->plan.wide_tasks.data();
+  A.tier_ptr = g->plan.tier_ptr.data();
+  A.n_tiers = g->plan.n_tiers();
   e = run_pgo(A);
   if (e != hipSuccess) return hip_fail(e, "pose-graph launch");
   return BA_OK;

@@ -1,8 +1,7 @@
 // gfx950 pose-graph optimisation (paper Sec. 2.3, Eq. 15): LM over the
 // world-from-base poses T_i minimising 1/2 sum_e w_e |Log(D_ij^-1 T_i^-1 T_j)|^2.
 //
-// Per LM attempt (besides one k_pgo_wide launch per wide level of the
-// elimination tree):
+// Per LM attempt:
 //   k_pgo_edges  one thread per edge at the candidate poses: r = Log(E),
 //                E = D^-1 T_i^-1 T_j, B = J_l(r)^-1 Ad(D^-1 T_i^-1) (so dr/dxi_j
 //                = B, dr/dxi_i = -B for the left perturbation), and w B^T B,
@@ -12,11 +11,12 @@
 //                    accept iff it strictly drops, lambda, trace
 //   k_pgo_assemble   the damped normal equations gathered from the current
 //                    edge buffer into the factor's blocks, -g into y
-//   k_pgo_wide       the wide levels of the sparse block Cholesky (see below)
-//   k_pgo_factor     one 1024-thread workgroup: the narrow levels (left-
-//                    looking: each column gathers its updates, factors its
-//                    diagonal block in registers, solves its panel; the
-//                    forward substitution rides along), then back substitution
+//   k_pgo_tree       the sparse block Cholesky, one launch per tier of the
+//                    elimination tree (left-looking: each column gathers its
+//                    updates, factors its diagonal block in registers, solves its
+//                    panel; the forward substitution rides along); the last tier's
+//                    one workgroup starts the back substitution
+//   k_pgo_back       the back substitution of the earlier tiers
 //   k_pgo_candidate  the next candidate Exp(d_i) T_i
 // Every sum has a fixed order and nothing uses atomics.
 #include <hip/hip_runtime.h>
@@ -349,16 +349,22 @@ __global__ __launch_bounds__(kPgoEdgeThreads) void k_pgo_assemble(PgoArgs A) {
   }
 }
 
-// Sparse block Cholesky by levels of the elimination tree.  Per level:
-// (1) every chunk of at most kPgoChunk updates L_rk L_ck^T of a block (and of
-// forward updates L_ck y_k of a right-hand side) is summed by its own thread
-// into a partial; (2) one wave per column subtracts its partials in chunk
-// order, factors the diagonal block in registers, finishes the forward step
-// and solves the column's panel rows.  A wide level is one launch with a
-// workgroup per column (its chunks, then its first wave does the rest); the
-// narrow ones run in one workgroup, where the partials are first subtracted
-// entry-parallel.  A failed pivot sets istate[4].  Back substitution from the
-// top level down, six threads per column.
+// Sparse block Cholesky by tiers of the elimination tree (see PgoPlan): a tier is one
+// launch, a workgroup per group of subtrees, which it works through step by step (a
+// step: columns of one level).  Per step: (1) every chunk of at most kPgoChunk
+// updates L_rk L_ck^T of a block (and of forward updates L_ck y_k of a right-hand
+// side) is summed by its own thread into a partial in LDS; (2) the partials are
+// subtracted in chunk order, one entry per thread; (3) one wave per column factors the
+// diagonal block in registers and solves the panel's rows and the right-hand side's.
+// Back substitution tier by tier from the top.  A failed pivot sets istate[4].
+//
+// The solve is a chain of 33 levels (1500-pose helix), each a few dependent steps:
+// latency bounds it.  With a launch per level for the lower 21 (10 us each: a chain of
+// index reads, partials through memory) and one workgroup for the narrow levels
+// above and the whole back substitution (287 us) an attempt's factorisation took 498 us;
+// with the step's records read in one go, partials and blocks in LDS, four tiers and
+// the back substitution in the same groups it takes 258 us.  Same sums in the same
+// order.
 // Phase (1) over the update chunks [q0, q1) and forward chunks [f0, f1).
 __device__ __forceinline__ void pgo_phase1_range(const PgoDev& G, const PgoWork& W, int q0, int q1, int f0, int f1,
                                                  int t0, int stride) {
@@ -413,297 +419,405 @@ __device__ __forceinline__ void pgo_phase1_range(const PgoDev& G, const PgoWork&
   }
 }
 
-// Index ranges of level l: columns, blocks, update chunks, forward chunks.
-struct PgoLevel {
-  int c0, c1, b0, b1, q0, q1, f0, f1;
-};
-__device__ __forceinline__ PgoLevel pgo_level(const PgoDev& G, int l) {
-  PgoLevel v;
-  v.c0 = G.lev_ptr[l];
-  v.c1 = G.lev_ptr[l + 1];
-  v.b0 = G.blk_ptr[v.c0];
-  v.b1 = G.blk_ptr[v.c1];
-  v.q0 = G.chunk_ptr[v.b0];
-  v.q1 = G.chunk_ptr[v.b1];
-  v.f0 = G.fchunk_ptr[v.c0];
-  v.f1 = G.fchunk_ptr[v.c1];
-  return v;
-}
-
-// Phase (1) of a level (all its columns' chunks).
-__device__ __forceinline__ void pgo_phase1(const PgoDev& G, const PgoWork& W, const PgoLevel& v, int t0, int stride) {
-  pgo_phase1_range(G, W, v.q0, v.q1, v.f0, v.f1, t0, stride);
-}
-
-// The level's partials subtracted from its blocks and right-hand sides, one
-// entry per thread, in chunk order (the narrow levels' variant of the sums
-// that phases 2 and 3 otherwise do per column / row).
-__device__ __forceinline__ void pgo_phase1b(const PgoDev& G, const PgoWork& W, const PgoLevel& v, int t0,
-                                            int stride) {
-  const int c0 = v.c0, c1 = v.c1, b0 = v.b0, b1 = v.b1;
+// Columns too large for a step: the partials go through memory.  Subtracts column c's
+// from its blocks and right-hand side, one entry per thread, in chunk order.
+__device__ __forceinline__ void pgo_big_subtract(const PgoDev& G, const PgoWork& W, int c, int t0, int stride) {
   const double* fpart = W.part + 36 * (long long)G.n_chunks;
-  const int nb = (b1 - b0) * 36;
-  for (int t = t0; t < nb + (c1 - c0) * 6; t += stride) {
+  const int b0 = G.blk_ptr[c], nb = (G.blk_ptr[c + 1] - b0) * 36;
+  for (int t = t0; t < nb + 6; t += stride) {
     if (t < nb) {
       const int b = b0 + t / 36, e = t % 36;
-      const int q0 = G.chunk_ptr[b], q1 = G.chunk_ptr[b + 1];
-      if (q0 == q1) continue;
       double v = W.L[36 * (long long)b + e];
-      int q = q0;
-      for (; q + 4 <= q1; q += 4) {   // four reads in flight, subtracted in order
-        double p[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) p[k] = W.part[36 * (long long)(q + k) + e];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v -= p[k];
-      }
-      for (; q < q1; ++q) v -= W.part[36 * (long long)q + e];
+      for (int q = G.chunk_ptr[b]; q < G.chunk_ptr[b + 1]; ++q) v -= W.part[36 * (long long)q + e];
       W.L[36 * (long long)b + e] = v;
     } else {
-      const int c = c0 + (t - nb) / 6, a = (t - nb) % 6;
-      const int q0 = G.fchunk_ptr[c], q1 = G.fchunk_ptr[c + 1];
-      if (q0 == q1) continue;
+      const int a = t - nb;
       double v = W.y[6 * c + a];
-      int q = q0;
-      for (; q + 4 <= q1; q += 4) {
-        double p[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) p[k] = fpart[6 * (long long)(q + k) + a];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v -= p[k];
-      }
-      for (; q < q1; ++q) v -= fpart[6 * (long long)q + a];
+      for (int q = G.fchunk_ptr[c]; q < G.fchunk_ptr[c + 1]; ++q) v -= fpart[6 * (long long)q + a];
       W.y[6 * c + a] = v;
     }
   }
 }
 
-// Phases 2 and 3 of a level with one wave per column: every lane factors the
-// column's diagonal block in registers (the same arithmetic in each lane) and
-// finishes the forward step, then the lanes solve the column's panel rows.
-// With SUM the chunk partials are subtracted here (the wide levels).
-template <bool SUM>
-__device__ __forceinline__ void pgo_phase23(const PgoDev& G, const PgoWork& W, int c0, int c1, int w0, int nw,
-                                            int lane, int* sfail = nullptr) {
-  const double* fpart = W.part + 36 * (long long)G.n_chunks;
-  for (int c = c0 + w0; c < c1; c += nw) {
-    const int bd = G.blk_ptr[c];
-    double* Lc = W.L + 36 * (long long)bd;
-    double m[36], yc[6];
+// Cholesky of a 6x6 block in registers (lower part), the same in every lane.
+__device__ __forceinline__ bool pgo_chol6(double (&m)[36]) {
+  bool ok = true;
 #pragma unroll
-    for (int k = 0; k < 36; ++k) m[k] = Lc[k];
+  for (int k = 0; k < 6; ++k) {
+    double d = m[7 * k];
 #pragma unroll
-    for (int a = 0; a < 6; ++a) yc[a] = W.y[6 * c + a];
-    if constexpr (SUM) {
-      // two chunks' partials read before either is subtracted (in order)
-      const int q1 = G.chunk_ptr[bd + 1];
-      int q = G.chunk_ptr[bd];
-      for (; q + 2 <= q1; q += 2) {
-        double p0[36], p1[36];
+    for (int q = 0; q < k; ++q) d -= m[6 * k + q] * m[6 * k + q];
+    ok = ok && d > 0.0 && isfinite(d);
+    const double lk = sqrt(fmax(d, 1e-300)), il = 1.0 / lk;
+    m[7 * k] = lk;
 #pragma unroll
-        for (int k = 0; k < 36; ++k) {
-          p0[k] = W.part[36 * (long long)q + k];
-          p1[k] = W.part[36 * (long long)(q + 1) + k];
-        }
+    for (int i = k + 1; i < 6; ++i) {
+      double v = m[6 * i + k];
 #pragma unroll
-        for (int k = 0; k < 36; ++k) m[k] = (m[k] - p0[k]) - p1[k];
-      }
-      for (; q < q1; ++q)
-#pragma unroll
-        for (int k = 0; k < 36; ++k) m[k] -= W.part[36 * (long long)q + k];
-      for (int q = G.fchunk_ptr[c]; q < G.fchunk_ptr[c + 1]; ++q)
-#pragma unroll
-        for (int a = 0; a < 6; ++a) yc[a] -= fpart[6 * (long long)q + a];
+      for (int q = 0; q < k; ++q) v -= m[6 * i + q] * m[6 * k + q];
+      m[6 * i + k] = v * il;
     }
-    bool ok = true;
+  }
+  return ok;
+}
+
+// One wave factors a column whose diagonal block and rows (updates subtracted) are at
+// blk (36 per block, the diagonal first) and rhs, and stores the factor and y.  The
+// right-hand side is solved as one more row.
+__device__ __forceinline__ void pgo_column(const PgoWork& W, int c, int bd, int nblk, const double* blk,
+                                           const double* rhs, int lane, int* sfail) {
+  double m[36];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      double d = m[7 * k];
+  for (int i = 0; i < 6; ++i)
 #pragma unroll
-      for (int q = 0; q < k; ++q) d -= m[6 * k + q] * m[6 * k + q];
-      ok = ok && d > 0.0 && isfinite(d);
-      const double lk = sqrt(fmax(d, 1e-300)), il = 1.0 / lk;
-      m[7 * k] = lk;
-#pragma unroll
-      for (int i = k + 1; i < 6; ++i) {
-        double v = m[6 * i + k];
-#pragma unroll
-        for (int q = 0; q < k; ++q) v -= m[6 * i + q] * m[6 * k + q];
-        m[6 * i + k] = v * il;
-      }
-    }
-    if (!ok) {
-      if (lane == 0) {
-        W.istate[4] = 1;
-        if (sfail) *sfail = 1;
-      }
-      continue;
-    }
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      double v = yc[k];
-#pragma unroll
-      for (int q = 0; q < k; ++q) v -= m[6 * k + q] * yc[q];
-      yc[k] = v / m[7 * k];
-    }
-    // panel rows (every lane has read the diagonal block above)
-    const int nrow = (G.blk_ptr[c + 1] - bd - 1) * 6;
-    for (int t = lane; t < nrow; t += 64) {
-      const int b = bd + 1 + t / 6, a = t % 6;
-      double* row = W.L + 36 * (long long)b + 6 * a;
-      double x[6];
-#pragma unroll
-      for (int k = 0; k < 6; ++k) x[k] = row[k];
-      if constexpr (SUM) {
-        const int q1 = G.chunk_ptr[b + 1];
-        int q = G.chunk_ptr[b];
-        for (; q + 4 <= q1; q += 4) {   // four chunks' rows in flight, in order
-          double p[4][6];
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int k = 0; k < 6; ++k) p[j][k] = W.part[36 * (long long)(q + j) + 6 * a + k];
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int k = 0; k < 6; ++k) x[k] -= p[j][k];
-        }
-        for (; q < q1; ++q)
-#pragma unroll
-          for (int k = 0; k < 6; ++k) x[k] -= W.part[36 * (long long)q + 6 * a + k];
-      }
-#pragma unroll
-      for (int k = 0; k < 6; ++k) {
-        double v = x[k];
-#pragma unroll
-        for (int q = 0; q < k; ++q) v -= x[q] * m[6 * k + q];
-        x[k] = v / m[7 * k];
-      }
-#pragma unroll
-      for (int k = 0; k < 6; ++k) row[k] = x[k];
-    }
+    for (int k = 0; k <= i; ++k) m[6 * i + k] = blk[6 * i + k];
+  if (!pgo_chol6(m)) {
     if (lane == 0) {
-#pragma unroll
-      for (int k = 0; k < 36; ++k) Lc[k] = m[k];
-#pragma unroll
-      for (int a = 0; a < 6; ++a) W.y[6 * c + a] = yc[a];
+      W.istate[4] = 1;
+      *sfail = 1;
     }
+    return;
+  }
+  const int nrow = (nblk - 1) * 6;
+  for (int t = lane; t <= nrow; t += 64) {
+    const double* row = t < nrow ? blk + 36 + 6 * t : rhs;
+    double* out = t < nrow ? W.L + 36 * (long long)(bd + 1) + 6 * t : W.y + 6 * c;
+    double x[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) x[k] = row[k];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      double v = x[k];
+#pragma unroll
+      for (int q = 0; q < k; ++q) v -= x[q] * m[6 * k + q];
+      x[k] = v / m[7 * k];
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) out[k] = x[k];
+  }
+  if (lane == 0) {
+    double* Lc = W.L + 36 * (long long)bd;
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+      for (int k = 0; k <= i; ++k) Lc[6 * i + k] = m[6 * i + k];
   }
 }
 
-// One wide level, one workgroup per column: its update and forward chunks
-// (phase 1), then its first wave subtracts them, factors and solves the
-// panel (phases 2 and 3).  Columns of a level are independent, so a level is
-// one launch.
-__global__ __launch_bounds__(kPgoEdgeThreads) void k_pgo_wide(PgoArgs A, int l) {
-  const PgoDev& G = A.G;
-  const int c = G.lev_ptr[l] + blockIdx.x;
-  const int bA = G.blk_ptr[c], bB = G.blk_ptr[c + 1];
-  pgo_phase1_range(G, A.W, G.chunk_ptr[bA], G.chunk_ptr[bB], G.fchunk_ptr[c], G.fchunk_ptr[c + 1], threadIdx.x,
-                   kPgoEdgeThreads);
-  __syncthreads();
-  if (threadIdx.x < 64)
-    pgo_phase23<true>(G, A.W, G.lev_ptr[l], G.lev_ptr[l + 1], blockIdx.x, gridDim.x, threadIdx.x);
+constexpr int kTreeThreads = 512;
+
+struct TreeLds {
+  double part[kStepChunks * kPgoChunk * 36];   // a chunk's products, pair by pair
+  double fwd[kStepFwd * kPgoChunk * 6];
+  double blk[kStepBlks * 36];   // blocks, updates subtracted; back substitution: a block's products
+  double rhs[kStepCols * 6];
+  double v[kTreeThreads];
+  int fail;
+};
+
+// What a thread reads of a step before it can start, nothing of it written by the
+// steps before, in two parts so that no wave waits for the first to issue the second:
+// (a) the step's counts, its first task's block pairs, the records of the entries it
+// subtracts from, read during the step before's sums; (b) those entries, read while
+// that step's columns are factored.
+constexpr int kStepEntries = (kStepBlks * 36 + kTreeThreads - 1) / kTreeThreads;   // per thread
+struct StepRegs {
+  int q0, nq, f0, nf, b0, nb, c0, nc;
+  int4 blk[kStepEntries];
+  int ia, ib, c, h0, h1;
+};
+struct StepVals {
+  double v[kStepEntries], hv;
+};
+
+// Tasks of a step: per pair of an update chunk four, of 3 x 3 entries of L_rk L_ck^T
+// each, and per pair of a forward chunk six, a row of L_ck y_k each.  A thread reads
+// three rows of each block once for nine entries: with one entry of all four pairs
+// per thread the reads (13.8 kB a chunk through the vector cache against 4.6 kB)
+// bound the sums, 4.6 k cycles per 512 tasks; all pairs of a tile in one thread
+// need more registers than there are.
+constexpr int kUpdTasks = 4 * kPgoChunk, kFwdTasks = 6 * kPgoChunk;   // per chunk
+
+// The block pair of task t of a step (update chunks first, then forward chunks), -1
+// past a chunk's end.
+__device__ __forceinline__ void step_pair(const PgoDev& G, const StepRegs& R, int t, int& ia, int& ib) {
+  const int nu = R.nq * kUpdTasks, u = t - nu;
+  const int32_t* p = t < nu ? G.step_ab + 2 * kPgoChunk * ((long long)R.q0 + t / kUpdTasks) + (t >> 2) % kPgoChunk
+                            : G.step_bc + 2 * kPgoChunk * ((long long)R.f0 + u / kFwdTasks) + u / 6 % kPgoChunk;
+  ia = p[0];
+  ib = p[kPgoChunk];
 }
 
-// Levels [l0, n_levels) in one workgroup, then the back substitution.
-__global__ __launch_bounds__(kPgoStepThreads) void k_pgo_factor(PgoArgs A, int l0) {
+__device__ __forceinline__ void step_fetch(const PgoDev& G, int s, StepRegs& R) {
   const int tid = threadIdx.x;
+  const int32_t* st = G.steps + 8 * (long long)s;
+  R.q0 = st[0];
+  R.nq = st[1];
+  R.f0 = st[2];
+  R.nf = st[3];
+  R.b0 = st[4];
+  R.nb = st[5];
+  R.c0 = st[6];
+  R.nc = st[7];
+  if (R.nq < 0) return;   // a large column
+  const int4* blks = reinterpret_cast<const int4*>(G.step_blk) + R.b0;
+#pragma unroll
+  for (int k = 0; k < kStepEntries; ++k) {
+    const int t = tid + k * kTreeThreads;
+    R.blk[k] = blks[t < R.nb * 36 ? t / 36 : 0];
+  }
+  const int32_t* col = G.step_col + 8 * ((long long)R.c0 + (tid < R.nc * 6 ? tid / 6 : 0));
+  R.c = col[0];
+  R.h0 = col[4];
+  R.h1 = col[5];
+  if (tid < R.nq * kUpdTasks + R.nf * kFwdTasks) step_pair(G, R, tid, R.ia, R.ib);
+}
+
+__device__ __forceinline__ void step_values(const PgoWork& W, const StepRegs& R, StepVals& V) {
+  if (R.nq < 0) return;
+#pragma unroll
+  for (int k = 0; k < kStepEntries; ++k)
+    V.v[k] = W.L[36 * (long long)R.blk[k].x + (threadIdx.x + k * kTreeThreads) % 36];
+  V.hv = W.y[6 * R.c + threadIdx.x % 6];
+}
+
+// One task of a step into LDS; a pair past its chunk's end counts as zero.
+__device__ __forceinline__ void step_task(const PgoWork& W, TreeLds& S, int t, int nu, int ia, int ib) {
+  if (t < nu) {
+    const int r0 = (t & 2) ? 3 : 0, c0 = (t & 1) ? 3 : 0;
+    double la[18], lb[18];
+    const double* La = W.L + 36 * (long long)max(ia, 0) + 6 * r0;
+    const double* Lb = W.L + 36 * (long long)max(ib, 0) + 6 * c0;
+#pragma unroll
+    for (int m = 0; m < 18; ++m) {
+      la[m] = La[m];
+      lb[m] = Lb[m];
+    }
+    double* out = S.part + 36 * (t >> 2) + 6 * r0 + c0;
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        double x = 0.0;
+#pragma unroll
+        for (int m = 0; m < 6; ++m) x += la[6 * r + m] * lb[6 * c + m];
+        out[6 * r + c] = ia >= 0 ? x : 0.0;
+      }
+  } else {
+    const int u = t - nu;
+    const double* La = W.L + 36 * (long long)max(ia, 0) + 6 * (u % 6);
+    const double* yk = W.y + 6 * max(ib, 0);
+    double x = 0.0;
+#pragma unroll
+    for (int m = 0; m < 6; ++m) x += La[m] * yk[m];
+    S.fwd[u] = ia >= 0 ? x : 0.0;
+  }
+}
+
+// v minus the chunks q0 .. q1 - 1 in order, each the sum of its kPgoChunk pairs'
+// products in order (pair stride `stride`); two chunks' reads in flight.
+__device__ __forceinline__ double minus_chunks(double v, const double* p, int stride, int q0, int q1) {
+  for (int q = q0; q < q1; q += 2) {
+    double x[2][kPgoChunk];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int k = 0; k < kPgoChunk; ++k) x[j][k] = p[stride * (kPgoChunk * min(q + j, q1 - 1) + k)];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      double acc = 0.0;
+#pragma unroll
+      for (int k = 0; k < kPgoChunk; ++k) acc += x[j][k];
+      if (q + j < q1) v -= acc;
+    }
+  }
+  return v;
+}
+
+// The steps [s0, s1) of the factorisation.
+__device__ __forceinline__ void pgo_tree_factor(const PgoDev& G, const PgoWork& W, int s0, int s1, TreeLds& S) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (s0 >= s1) return;
+  StepRegs R, N;
+  StepVals V;
+  step_fetch(G, s0, R);
+  step_values(W, R, V);
+  for (int s = s0; s < s1; ++s) {
+    if (S.fail) break;
+    const int32_t* cols = G.step_col + 8 * (long long)R.c0;
+    const int nc = R.nc;
+    if (s + 1 < s1) step_fetch(G, s + 1, N);
+    if (R.nq < 0) {   // one large column, through memory
+      const int c = cols[0], bd = cols[1], n = cols[2];
+      pgo_phase1_range(G, W, G.chunk_ptr[bd], G.chunk_ptr[bd + n], G.fchunk_ptr[c], G.fchunk_ptr[c + 1], tid,
+                       kTreeThreads);
+      __syncthreads();
+      pgo_big_subtract(G, W, c, tid, kTreeThreads);
+      __syncthreads();
+      if (s + 1 < s1) step_values(W, N, V);
+      if (wave == 0) pgo_column(W, c, bd, n, W.L + 36 * (long long)bd, W.y + 6 * c, lane, &S.fail);
+    } else {
+      // (1) the chunks' sums
+      const int nu = R.nq * kUpdTasks, nt = nu + R.nf * kFwdTasks;
+      if (tid < nt) step_task(W, S, tid, nu, R.ia, R.ib);
+      for (int t = tid + kTreeThreads; t < nt; t += kTreeThreads) {
+        int ia, ib;
+        step_pair(G, R, t, ia, ib);
+        step_task(W, S, t, nu, ia, ib);
+      }
+      __syncthreads();
+      // (2) subtracted in chunk order
+#pragma unroll
+      for (int k = 0; k < kStepEntries; ++k) {
+        const int t = tid + k * kTreeThreads;
+        if (t < R.nb * 36) S.blk[t] = minus_chunks(V.v[k], S.part + t % 36, 36, R.blk[k].y, R.blk[k].z);
+      }
+      if (tid < nc * 6) S.rhs[tid] = minus_chunks(V.hv, S.fwd + tid % 6, 6, R.h0, R.h1);
+      __syncthreads();
+      // (3) one wave per column
+      if (s + 1 < s1) step_values(W, N, V);
+      for (int i = wave; i < nc; i += kTreeThreads / 64) {
+        const int32_t* col = cols + 8 * i;
+        pgo_column(W, col[0], col[1], col[2], S.blk + 36 * col[3], S.rhs + 6 * i, lane, &S.fail);
+      }
+    }
+    __syncthreads();
+    R = N;
+  }
+}
+
+// What a thread reads of a step of the back substitution that the later steps do not
+// change: a block's product row, and (six neighbouring lanes per column, ten columns
+// per wave) a column's record, right-hand side and diagonal block.
+struct BackRegs {
+  int nb, nc, row;
+  bool big;
+  int c, bd, n, b0;
+  double l[6], y, d[21];
+};
+static_assert(kStepBlks * 6 <= kTreeThreads && kStepCols <= 10 * (kTreeThreads / 64),
+              "a step's block rows and columns have a thread each");
+
+__device__ __forceinline__ void back_fetch(const PgoDev& G, const PgoWork& W, int s, BackRegs& R) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int32_t* st = G.steps + 8 * (long long)s;
+  R.big = st[1] < 0;
+  R.nb = st[5];
+  R.nc = st[7];
+  R.row = -1;
+  if (!R.big && tid < R.nb * 6) {
+    const int4 b = reinterpret_cast<const int4*>(G.step_blk)[st[4] + tid / 6];
+    R.row = b.w;
+    const double* L = W.L + 36 * (long long)b.x + tid % 6;
+#pragma unroll
+    for (int m = 0; m < 6; ++m) R.l[m] = L[6 * m];
+  }
+  const int i = 10 * wave + lane / 6;
+  R.c = -1;
+  if (lane < 60 && i < R.nc) {
+    const int32_t* col = G.step_col + 8 * ((long long)st[6] + i);
+    R.c = col[0];
+    R.bd = col[1];
+    R.n = col[2];
+    R.b0 = col[3];
+    R.y = W.y[6 * R.c + lane % 6];
+    const double* D = W.L + 36 * (long long)R.bd;
+#pragma unroll
+    for (int p = 0, e = 0; p < 6; ++p)
+#pragma unroll
+      for (int q = 0; q <= p; ++q, ++e) R.d[e] = D[6 * p + q];
+  }
+}
+
+// The back substitution of the steps [s0, s1), last step first: x_c = L_cc^-T (y_c -
+// sum over the column's off-diagonal blocks of L_rc^T x_r).  Every block's product
+// row has its own thread; six neighbouring lanes per column subtract them in order,
+// exchange the sums and solve the 6x6 triangle, each keeping its own row.
+__device__ __forceinline__ void pgo_tree_back(const PgoDev& G, const PgoWork& W, int s0, int s1, TreeLds& S) {
+  const int tid = threadIdx.x, a = (tid & 63) % 6;
+  if (s0 >= s1) return;
+  BackRegs R;
+  back_fetch(G, W, s1 - 1, R);
+  for (int s = s1 - 1; s >= s0; --s) {
+    if (!R.big) {
+      if (tid < R.nb * 6) {
+        double x = 0.0;
+        if (R.row >= 0) {
+#pragma unroll
+          for (int m = 0; m < 6; ++m) x += R.l[m] * W.x[6 * R.row + m];
+        }
+        S.blk[tid] = x;
+      }
+      __syncthreads();
+    }
+    double v = 0.0;
+    if (R.c >= 0) {
+      v = R.y;
+      for (int k = 1; k < R.n; ++k) {
+        double x = 0.0;
+        if (R.big) {
+          const int r = G.blk_row[R.bd + k];
+#pragma unroll
+          for (int m = 0; m < 6; ++m) x += W.L[36 * (long long)(R.bd + k) + 6 * m + a] * W.x[6 * r + m];
+        } else {
+          x = S.blk[6 * (R.b0 + k) + a];
+        }
+        v -= x;
+      }
+    }
+    S.v[tid] = v;
+    __builtin_amdgcn_wave_barrier();   // the six lanes are of one wave, whose LDS operations stay in order
+    if (R.c >= 0) {
+      double vv[6];
+#pragma unroll
+      for (int q = 0; q < 6; ++q) vv[q] = S.v[tid - a + q];
+#pragma unroll
+      for (int k = 5; k >= 0; --k) {
+        double t = vv[k];
+#pragma unroll
+        for (int q = k + 1; q < 6; ++q) t -= R.d[q * (q + 1) / 2 + k] * vv[q];
+        vv[k] = t / R.d[k * (k + 1) / 2 + k];
+      }
+      double mine = vv[0];
+#pragma unroll
+      for (int q = 1; q < 6; ++q) mine = a == q ? vv[q] : mine;
+      W.x[6 * R.c + a] = mine;
+    }
+    if (s > s0) back_fetch(G, W, s - 1, R);
+    __syncthreads();
+  }
+}
+
+// One tier's groups from g0 on; the last tier is one group, which goes on with the back
+// substitution of its own steps and says whether the candidate is valid.
+template <bool LAST>
+__global__ __launch_bounds__(kTreeThreads) void k_pgo_tree(PgoArgs A, int g0) {
+  __shared__ TreeLds S;
   const PgoDev& G = A.G;
   const PgoWork& W = A.W;
-  // a failed pivot of the wide levels (earlier launches) or of this one,
-  // mirrored in LDS so that the level loop reads no flag from memory
-  __shared__ int sFail;
-  // the narrow levels' index ranges, read once (level by level in parallel)
-  // instead of by every phase of every level
-  constexpr int kLevCache = 128;
-  __shared__ PgoLevel sLv[kLevCache];
-  const int nlv = G.n_levels - l0;
-  const bool cached = nlv <= kLevCache;
-  if (tid == 0) sFail = W.istate[4];
-  if (cached)
-    for (int i = tid; i < nlv; i += kPgoStepThreads) sLv[i] = pgo_level(G, l0 + i);
+  const int g = g0 + blockIdx.x, s0 = G.grp_ptr[g], s1 = G.grp_ptr[g + 1];
+  if (threadIdx.x == 0) S.fail = W.istate[4];   // a pivot of an earlier tier
   __syncthreads();
-  for (int l = l0; l < G.n_levels; ++l) {
-    if (sFail) break;
-    const PgoLevel lv = cached ? sLv[l - l0] : pgo_level(G, l);
-    pgo_phase1(G, W, lv, tid, kPgoStepThreads);
-    __syncthreads();
-    pgo_phase1b(G, W, lv, tid, kPgoStepThreads);
-    __syncthreads();
-    pgo_phase23<false>(G, W, lv.c0, lv.c1, tid >> 6, kPgoStepThreads / 64, tid & 63, &sFail);
-    __syncthreads();
-  }
-  if (sFail) {
-    if (tid == 0) {
+  pgo_tree_factor(G, W, s0, s1, S);
+  if (!LAST) return;
+  if (S.fail) {
+    if (threadIdx.x == 0) {
       W.istate[1] = 0;
       W.istate[3] += 1;
     }
     return;
   }
-  // back substitution, x_c = L_cc^-T (y_c - sum over the column's
-  // off-diagonal blocks of L_rc^T x_r), the blocks in order: six threads per
-  // column, one per row of x_c, each summing its row with two blocks' loads in
-  // flight; then every thread of the column's group solves the 6x6 triangle
-  // from the six sums (through LDS) and keeps its own row
-  __shared__ double sV[kPgoStepThreads];
-  constexpr int kCols = kPgoStepThreads / 6;   // columns per pass
-  for (int l = G.n_levels - 1; l >= 0; --l) {
-    const int c0 = G.lev_ptr[l], c1 = G.lev_ptr[l + 1];
-    for (int base = c0; base < c1; base += kCols) {
-      const int a = tid % 6, c = base + tid / 6;
-      const bool act = tid < 6 * kCols && c < c1;
-      double v = 0.0;
-      if (act) {
-        v = W.y[6 * c + a];
-        const int b0 = G.blk_ptr[c] + 1, b1 = G.blk_ptr[c + 1];
-        for (int b = b0; b < b1; b += 2) {
-          int bk[2], rk[2];
-#pragma unroll
-          for (int k = 0; k < 2; ++k) {
-            bk[k] = min(b + k, b1 - 1);
-            rk[k] = G.blk_row[bk[k]];
-          }
-          double lv[2][6], xv[2][6];
-#pragma unroll
-          for (int k = 0; k < 2; ++k)
-#pragma unroll
-            for (int m = 0; m < 6; ++m) {
-              lv[k][m] = W.L[36 * (long long)bk[k] + 6 * m + a];
-              xv[k][m] = W.x[6 * rk[k] + m];
-            }
-#pragma unroll
-          for (int k = 0; k < 2; ++k) {
-            double t = 0.0;
-#pragma unroll
-            for (int m = 0; m < 6; ++m) t += lv[k][m] * xv[k][m];
-            if (b + k < b1) v -= t;
-          }
-        }
-      }
-      sV[tid] = v;
-      __syncthreads();
-      if (act) {
-        double vv[6];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) vv[q] = sV[tid - a + q];
-        const double* Lc = W.L + 36 * (long long)G.blk_ptr[c];
-#pragma unroll
-        for (int k = 5; k >= 0; --k) {
-          double s = vv[k];
-#pragma unroll
-          for (int q = k + 1; q < 6; ++q) s -= Lc[6 * q + k] * vv[q];
-          vv[k] = s / Lc[7 * k];
-        }
-        double mine = vv[0];
-#pragma unroll
-        for (int q = 1; q < 6; ++q) mine = a == q ? vv[q] : mine;
-        W.x[6 * c + a] = mine;
-      }
-      __syncthreads();
-    }
-  }
-  if (tid == 0) W.istate[1] = 1;
+  pgo_tree_back(G, W, s0, s1, S);
+  if (threadIdx.x == 0) W.istate[1] = 1;
+}
+
+// The back substitution of one earlier tier's groups.
+__global__ __launch_bounds__(kTreeThreads) void k_pgo_back(PgoArgs A, int g0) {
+  __shared__ TreeLds S;
+  if (A.W.istate[1] == 0) return;
+  const int g = g0 + blockIdx.x;
+  pgo_tree_back(A.G, A.W, A.G.grp_ptr[g], A.G.grp_ptr[g + 1], S);
 }
 
 // Candidate poses Exp(d_i) T_i for the free poses (the others copied); a
@@ -734,11 +848,15 @@ hipError_t run_pgo(const PgoArgs& A) {
     // the assembly also clears the pivot-failure flag, so it runs even when
     // there is nothing to gather
     hipLaunchKernelGGL(k_pgo_assemble, dim3(ab > 0 ? ab : 1), dim3(kPgoEdgeThreads), 0, s, A);
-    for (int l = 0; l < A.G.n_wide; ++l) {
-      const int* w = A.wide_tasks + 3 * l;   // w[1]: the level's columns
-      if (w[1] > 0) hipLaunchKernelGGL(k_pgo_wide, dim3(w[1]), dim3(kPgoEdgeThreads), 0, s, A, l);
+    for (int t = 0; t < A.n_tiers; ++t) {
+      const int g0 = A.tier_ptr[t], ng = A.tier_ptr[t + 1] - g0;
+      if (t + 1 == A.n_tiers) hipLaunchKernelGGL(k_pgo_tree<true>, dim3(ng), dim3(kTreeThreads), 0, s, A, g0);
+      else hipLaunchKernelGGL(k_pgo_tree<false>, dim3(ng), dim3(kTreeThreads), 0, s, A, g0);
     }
-    hipLaunchKernelGGL(k_pgo_factor, dim3(1), dim3(kPgoStepThreads), 0, s, A, A.G.n_wide);
+    for (int t = A.n_tiers - 2; t >= 0; --t) {
+      const int g0 = A.tier_ptr[t], ng = A.tier_ptr[t + 1] - g0;
+      hipLaunchKernelGGL(k_pgo_back, dim3(ng), dim3(kTreeThreads), 0, s, A, g0);
+    }
     hipLaunchKernelGGL(k_pgo_candidate, dim3(pb), dim3(kPgoEdgeThreads), 0, s, A);
   };
   if (eb > 0) hipLaunchKernelGGL(k_pgo_edges, dim3(eb), dim3(kPgoEdgeThreads), 0, s, A, 1);

@@ -13,14 +13,12 @@ namespace ba {
 
 // Device copy of the plan's tables.
 struct PgoDev {
-  int n_poses, n_edges, n_free, n_levels, n_blocks;
-  const int32_t *col_of_pose, *pose_of_col, *lev_ptr, *blk_ptr, *blk_row;
-  const int32_t *upd_ptr, *upd_a, *upd_b, *fwd_ptr, *fwd_blk, *fwd_col;
+  int n_poses, n_edges, n_free, n_blocks;
+  const int32_t *col_of_pose, *blk_ptr, *blk_row;
   const int32_t *asm_ptr, *asm_edge, *rhs_ptr, *rhs_edge, *edge_i, *edge_j;
-  const int32_t *blk_col, *chunk_ptr, *chunk_blk, *fchunk_ptr, *fchunk_col;
-  const int32_t *chunk_ab, *fchunk_bc;
-  int n_chunks, n_fchunks;
-  int n_wide;
+  const int32_t *chunk_ptr, *fchunk_ptr, *chunk_ab, *fchunk_bc;
+  const int32_t *grp_ptr, *steps, *step_col, *step_blk, *step_ab, *step_bc;
+  int n_chunks;
 };
 
 struct PgoArgs {
@@ -33,7 +31,8 @@ struct PgoArgs {
   ba_iter_trace* traces;  // max_iters or NULL
   DevSettings settings;
   void* stream;
-  const int* wide_tasks;  // HOST, 3 * G.n_wide launch sizes
+  const int32_t* tier_ptr;   // HOST, n_tiers + 1: groups of each tier
+  int n_tiers;
 };
 
 hipError_t run_pgo(const PgoArgs& A);

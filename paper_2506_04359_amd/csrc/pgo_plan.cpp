@@ -123,6 +123,117 @@ void symbolic(const std::vector<std::vector<int>>& adj, const std::vector<int>& 
 
 }  // namespace
 
+// Tiers, groups and steps (see PgoPlan).  A tier takes the maximal subtrees of at most
+// `cap` columns among those left; neighbouring small ones share a group.  Where
+// fewer than four groups would come out, or few columns are left, the rest is the
+// last tier.
+void build_schedule(PgoPlan& P) {
+  const int n = P.n_free;
+  std::vector<int32_t> parent(n, -1), tier(n, -1), group(n, -1);
+  for (int c = 0; c < n; ++c)
+    if (P.blk_ptr[c + 1] - P.blk_ptr[c] > 1) parent[c] = P.blk_row[P.blk_ptr[c] + 1];
+  const int cap = std::max(16, n / 256);
+  std::vector<std::vector<std::vector<int32_t>>> tiers;   // tier, group, columns (increasing)
+  std::vector<int32_t> left(n);
+  for (int c = 0; c < n; ++c) left[c] = c;
+  std::vector<int32_t> size(n), root(n);
+  while ((int)left.size() > 2 * cap) {
+    for (int32_t c : left) size[c] = 1;
+    for (int32_t c : left)   // children come before their parents
+      if (parent[c] >= 0) size[parent[c]] += size[c];
+    std::vector<std::vector<int32_t>> groups;
+    std::vector<int32_t> rest, roots;
+    for (int32_t c : left)
+      if (size[c] <= cap && (parent[c] < 0 || size[parent[c]] > cap)) roots.push_back(c);
+    // group of each root: roots in column order, together while they stay within cap
+    std::vector<int32_t> grp_of(n, -1);
+    int ng = 0, fill = 0;
+    for (int32_t r : roots) {
+      if (ng == 0 || fill + size[r] > cap) {
+        ++ng;
+        fill = 0;
+      }
+      grp_of[r] = ng - 1;
+      fill += size[r];
+    }
+    if (ng < 4) break;
+    groups.resize(ng);
+    for (auto it = left.rbegin(); it != left.rend(); ++it) {   // parents first: inherit the group
+      const int32_t c = *it;
+      if (grp_of[c] < 0 && parent[c] >= 0 && size[c] <= cap) grp_of[c] = grp_of[parent[c]];
+    }
+    for (int32_t c : left) {
+      if (grp_of[c] >= 0) groups[grp_of[c]].push_back(c);
+      else rest.push_back(c);
+    }
+    tiers.push_back(std::move(groups));
+    left = std::move(rest);
+  }
+  tiers.push_back({left});
+  // steps: the columns of a group by their level within it, cut to the LDS
+  P.tier_ptr.assign(1, 0);
+  P.grp_ptr.assign(1, 0);
+  std::vector<int32_t> lev(n, 0);
+  for (auto& groups : tiers) {
+    for (auto& cols : groups) {
+      int nl = 0;
+      for (int32_t c : cols) lev[c] = 0;
+      for (int32_t c : cols) {
+        nl = std::max(nl, lev[c] + 1);
+        if (parent[c] >= 0) lev[parent[c]] = std::max(lev[parent[c]], lev[c] + 1);
+      }
+      std::vector<std::vector<int32_t>> by(nl);
+      for (int32_t c : cols) by[lev[c]].push_back(c);
+      for (auto& level : by) {
+        int32_t st[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        auto open = [&]() {
+          const int32_t v[8] = {(int32_t)(P.step_ab.size() / (2 * kPgoChunk)), 0,
+                                (int32_t)(P.step_bc.size() / (2 * kPgoChunk)), 0, (int32_t)(P.step_blk.size() / 4), 0,
+                                (int32_t)(P.step_col.size() / 8), 0};
+          std::copy(v, v + 8, st);
+        };
+        auto close = [&]() {
+          if (st[7]) P.steps.insert(P.steps.end(), st, st + 8);
+        };
+        open();
+        for (int32_t c : level) {
+          const int b0 = P.blk_ptr[c], b1 = P.blk_ptr[c + 1], q0 = P.chunk_ptr[b0], q1 = P.chunk_ptr[b1];
+          const int f0 = P.fchunk_ptr[c], f1 = P.fchunk_ptr[c + 1];
+          const bool big = q1 - q0 > kStepChunks || f1 - f0 > kStepFwd || b1 - b0 > kStepBlks;
+          if (big || st[1] + q1 - q0 > kStepChunks || st[3] + f1 - f0 > kStepFwd || st[5] + b1 - b0 > kStepBlks ||
+              st[7] + 1 > kStepCols) {
+            close();
+            open();
+          }
+          const int32_t col[8] = {c, b0, b1 - b0, st[5], st[3], st[3] + f1 - f0, 0, 0};
+          P.step_col.insert(P.step_col.end(), col, col + 8);
+          st[7]++;
+          if (big) {
+            st[1] = -1;
+            close();
+            open();
+            continue;
+          }
+          for (int b = b0; b < b1; ++b) {
+            const int32_t blk[4] = {b, st[1] + P.chunk_ptr[b] - q0, st[1] + P.chunk_ptr[b + 1] - q0,
+                                    b == b0 ? -1 : P.blk_row[b]};
+            P.step_blk.insert(P.step_blk.end(), blk, blk + 4);
+          }
+          const auto ab = P.chunk_ab.begin(), bc = P.fchunk_bc.begin();
+          P.step_ab.insert(P.step_ab.end(), ab + 2 * kPgoChunk * (size_t)q0, ab + 2 * kPgoChunk * (size_t)q1);
+          P.step_bc.insert(P.step_bc.end(), bc + 2 * kPgoChunk * (size_t)f0, bc + 2 * kPgoChunk * (size_t)f1);
+          st[1] += q1 - q0;
+          st[3] += f1 - f0;
+          st[5] += b1 - b0;
+        }
+        close();
+      }
+      P.grp_ptr.push_back((int32_t)(P.steps.size() / 8));
+    }
+    P.tier_ptr.push_back((int32_t)P.grp_ptr.size() - 1);
+  }
+}
+
 std::string build_pgo_plan(int32_t n_poses, int32_t n_edges, const int32_t* edge_i,
                            const int32_t* edge_j, const uint8_t* pose_fixed, PgoPlan& P) {
   if (n_poses < 1) return "n_poses < 1";
@@ -310,18 +421,7 @@ std::string build_pgo_plan(int32_t n_poses, int32_t n_edges, const int32_t* edge
         P.fchunk_bc[(size_t)2 * kPgoChunk * q + kPgoChunk + k] = P.fwd_col[g0 + k];
       }
     }
-  // leading levels whose update phase has at least 4096 tasks run as
-  // launches over the whole GPU
-  for (int l = 0; l < P.n_levels; ++l) {
-    const int c0 = P.lev_ptr[l], c1 = P.lev_ptr[l + 1];
-    const int b0 = P.blk_ptr[c0], b1 = P.blk_ptr[c1];
-    const int t1 = (P.chunk_ptr[b1] - P.chunk_ptr[b0]) * 36 + (P.fchunk_ptr[c1] - P.fchunk_ptr[c0]) * 6;
-    if (t1 < 4096 && l > 0) break;
-    P.wide_tasks.push_back(t1);
-    P.wide_tasks.push_back(c1 - c0);
-    P.wide_tasks.push_back((b1 - b0) * 6);
-    P.n_wide = l + 1;
-  }
+  build_schedule(P);
   return "";
 }
 

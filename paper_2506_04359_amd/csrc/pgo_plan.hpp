@@ -35,19 +35,32 @@ struct PgoPlan {
   // chunk_ptr[b+1]), chunk_blk the block of a chunk; the same for the forward
   // lists of the columns
   std::vector<int32_t> blk_col;       // n_blocks: column of each block
-  // the first n_wide levels run each phase over the whole GPU; wide_tasks
-  // holds their task counts (phase 1, 2, 3) per level
-  int n_wide = 0;
-  std::vector<int32_t> wide_tasks;
   std::vector<int32_t> chunk_ptr, chunk_blk, fchunk_ptr, fchunk_col;
   // per chunk its kPgoChunk block pairs (L_rk ids, then L_ck ids) and per
   // forward chunk its (block, column) pairs, -1 past the list's end: a
   // chunk's thread reads its whole list at once
   std::vector<int32_t> chunk_ab, fchunk_bc;
+  // The factorisation's schedule.  A tier is a set of groups that do not depend on
+  // each other: subtrees of the elimination tree (without the earlier tiers'
+  // columns), each a workgroup's; the last tier is one group, the rest.  A group is a
+  // run of steps, a step a set of columns of one level, small enough for the
+  // workgroup's LDS.  tier_ptr: groups of each tier; grp_ptr: steps of each group.
+  std::vector<int32_t> tier_ptr, grp_ptr;
+  // Per step 8 ints: first chunk record and count, first forward record and count,
+  // first block record and count, first column record and count.  A column too large
+  // for a step has one of its own, with chunk count -1.
+  std::vector<int32_t> steps;
+  // Per column {column, first block, blocks, its first block in the step, first and
+  // end forward chunk in the step, 0, 0}; per block {block, first and end chunk in
+  // the step, row, -1 for the diagonal}; chunk_ab and fchunk_bc in step order.
+  std::vector<int32_t> step_col, step_blk, step_ab, step_bc;
+  int n_tiers() const { return (int)tier_ptr.size() - 1; }
   int n_blocks() const { return (int)blk_row.size(); }
 };
 
 constexpr int kPgoChunk = 4;
+// Largest step: update chunks, forward chunks, blocks and columns (the LDS of k_pgo_tree).
+constexpr int kStepChunks = 80, kStepFwd = 64, kStepBlks = 42, kStepCols = 42;
 
 // Builds the plan; returns an error message (empty on success).
 std::string build_pgo_plan(int32_t n_poses, int32_t n_edges, const int32_t* edge_i,

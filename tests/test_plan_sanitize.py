@@ -28,3 +28,18 @@ def test_plan_builders_under_asan_ubsan(tmp_path):
     r = subprocess.run([exe, "60"], capture_output=True, text=True, env=env, timeout=600)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-4000:])
     assert "0 failures" in r.stdout and "windows" in r.stdout, r.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host C++ compiler")
+def test_pose_graph_schedule_under_asan_ubsan(tmp_path):
+    """Tiers, groups and steps of the pose-graph factorisation on chains, laps,
+    complete, star, random and disconnected graphs (tests/native/pgo_schedule_check.cpp)."""
+    exe = str(tmp_path / "pgo_schedule_check")
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+           os.path.join(ROOT, "tests", "native", "pgo_schedule_check.cpp"), os.path.join(CSRC, "pgo_plan.cpp"),
+           "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-4000:])
+    assert r.stdout.count("columns") == 16
