@@ -246,12 +246,22 @@ __global__ __launch_bounds__(kPgoStepThreads) void k_pgo_decide(PgoArgs A, int m
   const int ev = mode == 0 ? 0 : 1 - cur0;
   double s = 0.0;
   for (int e = tid; e < G.n_edges; e += kPgoStepThreads) s += W.edge[ev][28 * (long long)e + 27];
+  // halving tree over the threads, from 64 partial sums on within a wave: with a barrier
+  // per halving and the poses' copy here the launch took 9.8 us at 3k edges, now 5.9
   sRed[tid] = s;
   __syncthreads();
-  for (int h = kPgoStepThreads / 2; h > 0; h >>= 1) {
-    if (tid < h) sRed[tid] += sRed[tid + h];
-    __syncthreads();
+  if (tid < 64) {
+    double v[kPgoStepThreads / 64];
+#pragma unroll
+    for (int k = 0; k < kPgoStepThreads / 64; ++k) v[k] = sRed[tid + 64 * k];
+#pragma unroll
+    for (int h = kPgoStepThreads / 128; h > 0; h >>= 1)
+#pragma unroll
+      for (int k = 0; k < h; ++k) v[k] += v[k + h];
+    const double t = wave_sum(v[0]);
+    if (tid == 0) sRed[0] = t;
   }
+  __syncthreads();
   const double Fe = 0.5 * sRed[0];
   double F, lam;
   if (mode == 0) {
@@ -264,6 +274,7 @@ __global__ __launch_bounds__(kPgoStepThreads) void k_pgo_decide(PgoArgs A, int m
       ist[0] = 0;
       ist[2] = 0;
       ist[3] = 0;
+      ist[5] = 0;
     }
   } else {
     F = st[0];
@@ -280,13 +291,16 @@ __global__ __launch_bounds__(kPgoStepThreads) void k_pgo_decide(PgoArgs A, int m
       A.traces[it] = tr;
     }
     if (accept) {
-      for (int k = tid; k < 12 * G.n_poses; k += kPgoStepThreads) A.poses[k] = W.cand[k];
+      // the accepted poses, here after the last attempt and otherwise by the assembly
+      if (last)
+        for (int k = tid; k < 12 * G.n_poses; k += kPgoStepThreads) A.poses[k] = W.cand[k];
       F = Fe;
     }
     lam = accept ? fmax(lam / S.lambda_down, S.lambda_min) : fmin(lam * S.lambda_up, S.lambda_max);
     if (tid == 0) {
       st[0] = F;
       st[1] = lam;
+      ist[5] = accept ? 1 : 0;
       if (accept) {
         ist[0] = 1 - cur0;
         ist[2] += 1;
@@ -315,6 +329,8 @@ __global__ __launch_bounds__(kPgoEdgeThreads) void k_pgo_assemble(PgoArgs A) {
   const PgoWork& W = A.W;
   const int t = blockIdx.x * kPgoEdgeThreads + threadIdx.x;
   const double* EB = W.edge[W.istate[0]];
+  if (W.istate[5])   // the last attempt's poses were accepted
+    for (int k = t; k < 12 * G.n_poses; k += gridDim.x * kPgoEdgeThreads) A.poses[k] = W.cand[k];
   if (t == 0) W.istate[4] = 0;   // pivot failure flag of the factorisation that follows
   const int nb6 = G.n_blocks * 6;
   if (t < nb6) {
@@ -363,7 +379,7 @@ __global__ __launch_bounds__(kPgoEdgeThreads) void k_pgo_assemble(PgoArgs A) {
 // index reads, partials through memory) and one workgroup for the narrow levels
 // above and the whole back substitution (287 us) an attempt's factorisation took 498 us;
 // with the step's records read in one go, partials and blocks in LDS, four tiers and
-// the back substitution in the same groups it takes 258 us.  Same sums in the same
+// the back substitution in the same groups it takes 254 us.  Same sums in the same
 // order.
 // Phase (1) over the update chunks [q0, q1) and forward chunks [f0, f1).
 __device__ __forceinline__ void pgo_phase1_range(const PgoDev& G, const PgoWork& W, int q0, int q1, int f0, int f1,
@@ -521,9 +537,12 @@ struct TreeLds {
 // subtracts from, read during the step before's sums; (b) those entries, read while
 // that step's columns are factored.
 constexpr int kStepEntries = (kStepBlks * 36 + kTreeThreads - 1) / kTreeThreads;   // per thread
-struct StepRegs {
+struct StepHead {   // a record of G.steps, read two steps ahead
   int q0, nq, f0, nf, b0, nb, c0, nc;
-  int4 blk[kStepEntries];
+};
+static_assert(sizeof(StepHead) == 32, "a step's record is eight ints");
+struct StepRegs : StepHead {
+  int4 blk[kStepEntries], col;   // col: the record of this wave's (first) column
   int ia, ib, c, h0, h1;
 };
 struct StepVals {
@@ -548,17 +567,14 @@ __device__ __forceinline__ void step_pair(const PgoDev& G, const StepRegs& R, in
   ib = p[kPgoChunk];
 }
 
-__device__ __forceinline__ void step_fetch(const PgoDev& G, int s, StepRegs& R) {
+__device__ __forceinline__ StepHead step_head(const PgoDev& G, int s) {
+  return reinterpret_cast<const StepHead*>(G.steps)[s];
+}
+
+__device__ __forceinline__ void step_fetch(const PgoDev& G, const StepHead& H, int wave, StepRegs& R) {
   const int tid = threadIdx.x;
-  const int32_t* st = G.steps + 8 * (long long)s;
-  R.q0 = st[0];
-  R.nq = st[1];
-  R.f0 = st[2];
-  R.nf = st[3];
-  R.b0 = st[4];
-  R.nb = st[5];
-  R.c0 = st[6];
-  R.nc = st[7];
+  static_cast<StepHead&>(R) = H;
+  R.col = reinterpret_cast<const int4*>(G.step_col)[2 * ((long long)R.c0 + min(wave, R.nc - 1))];
   if (R.nq < 0) return;   // a large column
   const int4* blks = reinterpret_cast<const int4*>(G.step_blk) + R.b0;
 #pragma unroll
@@ -615,16 +631,16 @@ __device__ __forceinline__ void step_task(const PgoWork& W, TreeLds& S, int t, i
 }
 
 // v minus the chunks q0 .. q1 - 1 in order, each the sum of its kPgoChunk pairs'
-// products in order (pair stride `stride`); two chunks' reads in flight.
+// products in order (pair stride `stride`); four chunks' reads in flight.
 __device__ __forceinline__ double minus_chunks(double v, const double* p, int stride, int q0, int q1) {
-  for (int q = q0; q < q1; q += 2) {
-    double x[2][kPgoChunk];
+  for (int q = q0; q < q1; q += 4) {
+    double x[4][kPgoChunk];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int k = 0; k < kPgoChunk; ++k) x[j][k] = p[stride * (kPgoChunk * min(q + j, q1 - 1) + k)];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < 4; ++j) {
       double acc = 0.0;
 #pragma unroll
       for (int k = 0; k < kPgoChunk; ++k) acc += x[j][k];
@@ -641,15 +657,18 @@ __device__ __forceinline__ void pgo_tree_factor(const PgoDev& G, const PgoWork& 
   if (s0 >= s1) return;
   StepRegs R, N;
   StepVals V;
-  step_fetch(G, s0, R);
+  StepHead H = step_head(G, min(s0 + 1, s1 - 1));
+  step_fetch(G, step_head(G, s0), wave, R);
   step_values(W, R, V);
   for (int s = s0; s < s1; ++s) {
     if (S.fail) break;
-    const int32_t* cols = G.step_col + 8 * (long long)R.c0;
     const int nc = R.nc;
-    if (s + 1 < s1) step_fetch(G, s + 1, N);
+    if (s + 1 < s1) {
+      step_fetch(G, H, wave, N);
+      H = step_head(G, min(s + 2, s1 - 1));
+    }
     if (R.nq < 0) {   // one large column, through memory
-      const int c = cols[0], bd = cols[1], n = cols[2];
+      const int c = R.col.x, bd = R.col.y, n = R.col.z;
       pgo_phase1_range(G, W, G.chunk_ptr[bd], G.chunk_ptr[bd + n], G.fchunk_ptr[c], G.fchunk_ptr[c + 1], tid,
                        kTreeThreads);
       __syncthreads();
@@ -678,8 +697,9 @@ __device__ __forceinline__ void pgo_tree_factor(const PgoDev& G, const PgoWork& 
       // (3) one wave per column
       if (s + 1 < s1) step_values(W, N, V);
       for (int i = wave; i < nc; i += kTreeThreads / 64) {
-        const int32_t* col = cols + 8 * i;
-        pgo_column(W, col[0], col[1], col[2], S.blk + 36 * col[3], S.rhs + 6 * i, lane, &S.fail);
+        int4 col = R.col;
+        if (i != wave) col = reinterpret_cast<const int4*>(G.step_col)[2 * ((long long)R.c0 + i)];
+        pgo_column(W, col.x, col.y, col.z, S.blk + 36 * col.w, S.rhs + 6 * i, lane, &S.fail);
       }
     }
     __syncthreads();

@@ -75,7 +75,7 @@ struct PgoWork {
   double* x;          // n_free * 6 step
   double* part;       // n_chunks * 36 + n_fchunks * 6 partial sums of the update chunks
   double* state;      // 8: F, lambda, F0, ...
-  int32_t* istate;    // 8: current edge buffer, candidate valid, accepted, chol failures, pivot failed
+  int32_t* istate;    // 8: current edge buffer, candidate valid, accepted, chol failures, pivot failed, last accepted
 };
 
 size_t pgo_workspace_bytes(const PgoPlan& P);
