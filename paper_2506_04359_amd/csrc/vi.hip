@@ -512,99 +512,73 @@ __global__ __launch_bounds__(64) void k_vi_fac(ViArgs V, int wbase) {
 __device__ inline int hx_row(int q) { return q < 6 ? q : 9 + q; }
 __device__ inline int hy_col(int c) { return c < 9 ? 6 + c : 12 + c; }
 
-// Cholesky of a 9x9 block held in registers (lower part), the pivots by the
-// refined rsqrt: L_jj = d rsqrt(d) and inv_j = rsqrt(d) (no square root or
-// division on the pivot chain).  False on a non-positive or non-finite pivot.
-__device__ __forceinline__ bool chol9_regs(double (&A)[81], double (&inv)[9]) {
-#pragma unroll
-  for (int j = 0; j < 9; ++j) {
-    double d = A[10 * j];
-#pragma unroll
-    for (int k = 0; k < j; ++k) d -= A[9 * j + k] * A[9 * j + k];
-    if (!(d > 0.0) || !isfinite(d)) return false;
-    const double ir = rsqrt(d);
-    A[10 * j] = d * ir;
-    inv[j] = ir;
-#pragma unroll
-    for (int i = j + 1; i < 9; ++i) {
-      double v = A[9 * i + j];
-#pragma unroll
-      for (int k = 0; k < j; ++k) v -= A[9 * i + k] * A[9 * j + k];
-      A[9 * i + j] = v * ir;
-    }
-  }
-  return true;
+// A double of another lane of the wave, as a wave-uniform value.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readlane((int)b, lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | lo);
 }
 
-// Waits for the LDS reads that produced v before anything that uses v (the
-// reads are issued together and waited for once).
-template <int N>
-__device__ __forceinline__ void vi_lds_fence(double (&v)[N]) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) __asm__ volatile("" : "+v"(v[i]));
-}
-
-// A 9x9 Cholesky factor's strictly lower entries (row i, column k < i at
-// i (i - 1) / 2 + k) and reciprocal diagonal, read from LDS together and
-// waited for once, then the two triangular solves on registers.
-struct L9 {
-  double l[36], inv[9];
-};
-__device__ __forceinline__ void load_l9(const double* L, const double* inv, L9& F) {
-#pragma unroll
-  for (int i = 1, q = 0; i < 9; ++i)
-#pragma unroll
-    for (int k = 0; k < i; ++k, ++q) F.l[q] = L[9 * i + k];
-#pragma unroll
-  for (int i = 0; i < 9; ++i) F.inv[i] = inv[i];
-  vi_lds_fence(F.l);
-  vi_lds_fence(F.inv);
-}
-__device__ __forceinline__ void lsolve9r(const L9& F, double (&x)[9]) {
-#pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    double v = x[i];
-#pragma unroll
-    for (int k = 0; k < i; ++k) v -= F.l[i * (i - 1) / 2 + k] * x[k];
-    x[i] = v * F.inv[i];
-  }
-}
-__device__ __forceinline__ void ltsolve9r(const L9& F, double (&x)[9]) {
-#pragma unroll
-  for (int i = 8; i >= 0; --i) {
-    double v = x[i];
-#pragma unroll
-    for (int k = i + 1; k < 9; ++k) v -= F.l[k * (k - 1) / 2 + i] * x[k];
-    x[i] = v * F.inv[i];
-  }
-}
-
-constexpr int kViLinThreads = 256;   // threads of the elimination workgroup
+// The elimination: one workgroup per window.  Its chain over the states (factor, then
+// the forward and the backward substitution of all columns) is what it takes; the bytes
+// are few.  Forward, a wave holds one row per lane of the 9-wide panel
+//   lanes 0-8    A_k (damped, less C_k C_k^T): becomes L_k
+//   lanes 9-17   A_{k,k+1}^T: becomes C_{k+1}
+//   the rest     kViCols columns of u_k - C_k w_{k-1}: become w_k
+// and factors it column by column, right-looking, with the pivot rows' entries read
+// across lanes: no barrier, and one pass of 45 steps for the factor, its panel and the
+// substitution (an entry's updates keep their order, so the values are those of the
+// left-looking loops).  Every wave repeats the 18 panel rows for its own columns.
+// The last waves add the pose-pose terms into the reduced system meanwhile.  Backward,
+// a lane holds a column.  At 10 keyframes (9 free): 72 us with the factor on one thread
+// and two barriers a state in each of three loops, XXX us so.
+constexpr int kViLinThreads = 512;                     // threads of the elimination workgroup
+constexpr int kViPanel = 18, kViCols = 64 - kViPanel;  // panel rows, columns of a wave
+constexpr int kViSweepWaves = 4;                       // forward waves; the others: pose-pose terms
+constexpr int kViPoseThreads = kViLinThreads - 64 * kViSweepWaves;
+static_assert(kViSweepWaves * kViCols >= 6 * kViMaxStates + 1 && 64 * kViSweepWaves >= 6 * kViMaxStates + 1,
+              "a lane per column");
 
 template <bool XL>
 __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
-  extern __shared__ __align__(16) double sXd[];     // X when it fits in LDS (XL)
-  __shared__ double sA[kViMaxStates * 81];          // A_kk (damped), then its Cholesky factor L_k
-  __shared__ double sO[(kViMaxStates - 1) * 81];    // A_{k,k+1}
-  __shared__ double sC[kViMaxStates * 81];          // C_k = A_{k,k-1} L_{k-1}^-T, k >= 1
-  __shared__ double sH[(kViMaxStates - 1) * 216];   // H_xy per factor
-  __shared__ double sG[kViMaxStates * 9];           // g_y
-  __shared__ double sInv[kViMaxStates * 9];         // 1 / diag(L_k)
-  __shared__ int sPose[kViMaxStates];               // pose of each free slot
+  extern __shared__ __align__(16) double sXd[];   // X when it fits in LDS (XL)
+  // A_kk (damped; the factor reads its lower part), and L_k's strictly lower entries
+  // transposed above the diagonal: a wave behind still reads A_k below it
+  constexpr int oA = 0;
+  constexpr int oO = oA + kViMaxStates * 81;                   // A_{k,k+1}
+  constexpr int oC = oO + (kViMaxStates - 1) * 81;             // C_k = A_{k,k-1} L_{k-1}^-T, k >= 1
+  constexpr int oH = oC + kViMaxStates * 81;                   // H_xy per factor
+  constexpr int oG = oH + (kViMaxStates - 1) * 216;            // g_y
+  constexpr int oInv = oG + kViMaxStates * 9;                  // 1 / diag(L_k)
+  constexpr int oCw = oInv + kViMaxStates * 9;                 // C_k of the forward waves after the first
+  constexpr int oZero = oCw + (kViSweepWaves - 1) * 81;        // nine zeros
+  __shared__ double sM[oZero + 9];
+  __shared__ int sPose[kViMaxStates];   // pose of each free slot
   __shared__ int sOk;
+  double* const sA = sM + oA;
+  double* const sO = sM + oO;
+  double* const sC = sM + oC;
+  double* const sH = sM + oH;
+  double* const sG = sM + oG;
+  double* const sInv = sM + oInv;
   const int wi = V.win_order[wbase + blockIdx.x];
   const WinDev W = V.win[wi];
   const WinState& st = V.state[wi];
   const int tid = threadIdx.x;
   const int N = W.n_poses, nf = N - 1, nS = 6 * W.n_free, ncol = nS + 1;
   const double* F = V.rec;                           // per factor records
-  // 9N x (nS + 1): A^-1 H_yx, then z = A^-1 g_y; worked on in LDS when it
-  // fits (XL) and copied out at the end, since k_vi_cand reads it
+  // 9N x (nS + 1): A^-1 H_yx, then z = A^-1 g_y; row-major in LDS when it
+  // fits (XL) and copied out at the end, since k_vi_cand reads it column by
+  // column; otherwise column-major in the workspace throughout
   double* Xg = V.rec + (size_t)kViFactorStride * nf;
   double* X = XL ? sXd : Xg;
+  const int xrow = XL ? ncol : 1, xcol = XL ? 1 : 9 * N;   // strides of X
   const int* fs = V.free_slot + W.pose_off;
   if (tid < N && fs[tid] >= 0) sPose[fs[tid]] = tid;
   if (tid == 0) sOk = 1;
+  if (tid < 9) sM[oZero + tid] = 0.0;
+  const int wave = tid >> 6, lane = tid & 63;
   // 1. stage A = H_yy + damping (block tridiagonal), A_{k,k+1}, H_xy and g_y:
   //    one index space over the four arrays, eight elements per thread and
   //    round, a round's reads (two per element, unconditional: an unused one
@@ -659,8 +633,14 @@ __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
       }
     }
   }
-  // 2. the IMU cost at the current state (fixed order), for the first attempt
-  if (tid == 0) {
+  __syncthreads();
+  const int nblk = W.n_free * (W.n_free + 1) / 2;
+  double* S = V.ssum + W.sum_off;
+  double* sB = S + nblk * kBS;   // the reduced right-hand side (global)
+  const int ptid = tid - 64 * kViSweepWaves;
+  // 2. the last waves: the IMU cost at the current state (fixed order), for
+  //    the first attempt, and the pose-pose terms
+  if (ptid == 0) {
     double cf[kViMaxStates - 1];   // every factor's cost read before the sum
 #pragma unroll
     for (int f = 0; f < kViMaxStates - 1; ++f) cf[f] = f < nf ? F[(size_t)kViFactorStride * f + kFc] : 0.0;
@@ -674,16 +654,13 @@ __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
   // diagonal blocks, whole off-diagonal blocks (a, a + 1), -g into the rhs,
   // the diagonal into diag(U) (the damping uses the whole diagonal); every
   // read of a thread's elements goes out before its first update
-  const int nblk = W.n_free * (W.n_free + 1) / 2;
-  double* S = V.ssum + W.sum_off;
-  double* sB = S + nblk * kBS;   // the reduced right-hand side (global)
-  for (int base = 0; base < N * 36; base += 2 * blockDim.x) {
+  for (int base = 0; ptid >= 0 && base < N * 36; base += 2 * kViPoseThreads) {
     double fv[2][5], sv[2][4];
     long long so[2][4];
     int sa_[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-      const int e = base + tid + r * (int)blockDim.x;
+      const int e = base + ptid + r * kViPoseThreads;
       const bool in = e < N * 36;
       const int a = in ? e / 36 : 0, rr = (e % 36) / 6, c = e % 6;
       const int sa = in ? fs[a] : -1;
@@ -708,7 +685,7 @@ __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
     }
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-      const int e = base + tid + r * (int)blockDim.x;
+      const int e = base + ptid + r * kViPoseThreads;
       const int sa = sa_[r];
       if (e >= N * 36 || sa < 0) continue;
       const int a = e / 36, rr = (e % 36) / 6, c = e % 6;
@@ -726,146 +703,120 @@ __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
       }
     }
   }
-  __syncthreads();
-  // 3. block tridiagonal Cholesky of A, state by state
-  for (int k = 0; k < N; ++k) {
-    if (k >= 1) {
-      if (tid < 9) {   // row tid of C_k: L_{k-1} c = column tid of A_{k-1,k}
-        L9 F;
-        load_l9(sA + 81 * (k - 1), sInv + 9 * (k - 1), F);
-        double row[9];
-#pragma unroll
-        for (int y = 0; y < 9; ++y) row[y] = sO[81 * (k - 1) + 9 * y + tid];
-        vi_lds_fence(row);
-        lsolve9r(F, row);
-#pragma unroll
-        for (int y = 0; y < 9; ++y) sC[81 * k + 9 * tid + y] = row[y];
+  // 3. factor and forward sweep w_k = L_k^-1 (u_k - C_k w_{k-1}), state by state
+  if (wave < kViSweepWaves && kViCols * wave < ncol) {
+    const int col = kViCols * wave + lane - kViPanel;
+    const bool arow = lane < 9, crow = !arow && lane < kViPanel, wcol = !arow && !crow && col < ncol;
+    const int pa = wcol && col < nS ? sPose[col / 6] : -1, pr = col % 6;
+    // the lane's entries of state k: sM[p0 + step y] + sM[p1 + y]
+    const int step = crow ? 9 : 1;
+    auto entry = [&](int k, double (&v)[9]) {
+      int p0 = oZero, p1 = oZero, sp = 1;
+      if (arow) {
+        p0 = oA + 81 * k + 9 * lane;
+      } else if (crow) {
+        if (k + 1 < N) {
+          p0 = oO + 81 * k + lane - 9;
+          sp = step;
+        }
+      } else if (wcol && col == nS) {
+        p0 = oG + 9 * k;
+      } else if (pa >= 0) {
+        // factor a - 1 holds pose a as x_j (rows 6 + r), factor a as x_i (rows r)
+        if (pa >= 1 && (k == pa - 1 || k == pa)) p0 = oH + 216 * (pa - 1) + 18 * (6 + pr) + (k == pa ? 9 : 0);
+        if (pa < nf && (k == pa || k == pa + 1)) p1 = oH + 216 * pa + 18 * pr + (k == pa ? 0 : 9);
       }
-      __syncthreads();
-      if (tid < 81) {
-        const int x = tid / 9, y = tid % 9;
-        double v = 0.0;
-        for (int m = 0; m < 9; ++m) v += sC[81 * k + 9 * x + m] * sC[81 * k + 9 * y + m];
-        sA[81 * k + tid] -= v;
+#pragma unroll
+      for (int y = 0; y < 9; ++y) v[y] = sM[p0 + sp * y] + sM[p1 + y];
+    };
+    double w[9], nx[9];
+    entry(0, w);
+    bool ok = true;
+    for (int k = 0; k < N; ++k) {
+      const int ck = wave == 0 ? oC + 81 * k : oCw + 81 * (wave - 1);   // C_k
+      if (k >= 1) {
+        // A_k less C_k C_k^T (the sum first), u_k less C_k w_{k-1}
+        double m[9];
+#pragma unroll
+        for (int y = 0; y < 9; ++y) m[y] = arow ? sM[ck + 9 * lane + y] : -w[y];
+#pragma unroll
+        for (int x = 0; x < 9; ++x) {
+          double v = arow ? 0.0 : nx[x];
+#pragma unroll
+          for (int y = 0; y < 9; ++y) v = fma(sM[ck + 9 * x + y], m[y], v);
+          w[x] = arow ? nx[x] - v : crow ? nx[x] : v;
+        }
       }
-      __syncthreads();
+      if (k + 1 < N) entry(k + 1, nx);
+      double iv[9];
+#pragma unroll
+      for (int j = 0; j < 9; ++j) {
+        const double d = lane_value(w[j], j);
+        ok = ok && d > 0.0 && isfinite(d);
+        iv[j] = rsqrt(d);
+        w[j] *= iv[j];
+#pragma unroll
+        for (int c = j + 1; c < 9; ++c) w[c] -= w[j] * lane_value(w[j], c);
+      }
+      if (!ok) break;   // the same in every wave
+      if (wave == 0 && arow) {
+#pragma unroll
+        for (int y = 0; y < 8; ++y)
+          if (y < lane) sA[81 * k + 9 * y + lane] = w[y];
+        if (lane == 0)
+#pragma unroll
+          for (int y = 0; y < 9; ++y) sInv[9 * k + y] = iv[y];
+      }
+      if (crow && k + 1 < N) {
+        const int cn = wave == 0 ? oC + 81 * (k + 1) : oCw + 81 * (wave - 1);
+#pragma unroll
+        for (int y = 0; y < 9; ++y) sM[cn + 9 * (lane - 9) + y] = w[y];
+      }
+      if (wcol)
+#pragma unroll
+        for (int x = 0; x < 9; ++x) X[(size_t)xrow * (9 * k + x) + (size_t)xcol * col] = w[x];
+      // C_{k+1} is read by the wave's other lanes
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    if (tid == 0) {
-      double Ak[81], iv[9];
-#pragma unroll
-      for (int e = 0; e < 81; ++e) Ak[e] = sA[81 * k + e];
-      vi_lds_fence(Ak);
-      if (chol9_regs(Ak, iv)) {
-#pragma unroll
-        for (int e = 0; e < 81; ++e) sA[81 * k + e] = Ak[e];
-#pragma unroll
-        for (int x = 0; x < 9; ++x) sInv[9 * k + x] = iv[x];
-      } else {
-        sOk = 0;
-      }
-    }
-    __syncthreads();
-    if (!sOk) break;
+    if (!ok && tid == 0) sOk = 0;
   }
+  __syncthreads();
   if (!sOk) {
     if (tid == 0) V.part_flag_a[W.chunk_begin] = 1;   // the reduce rejects the attempt
     return;
   }
-  // 4. X = A^-1 [H_yx | g_y] by a forward sweep w_k = L_k^-1 (u_k - C_k w_{k-1})
-  //    and a backward sweep u_k = L_k^-T (w_k - C_{k+1}^T u_{k+1}) over the
-  //    states, all columns at once: per state, the coupling product (one
-  //    entry per thread) and then the triangular solve (one column per
-  //    thread), a barrier after each.  Columns above a pose's first state
-  //    stay exactly zero.  sO (A_{k,k+1}) is no longer needed and holds the
-  //    9 x ncol products.
-  double* sT = sO;
-  auto u_entry = [&](int k, int x, int col) -> double {
-    double v = 0.0;
-    if (col == nS) {
-      v = sG[9 * k + x];
-    } else {
-      // factor a - 1 holds pose a as x_j (rows 6 + r), factor a as x_i (rows r)
-      const int a = sPose[col / 6], r = col % 6;
-      if (a >= 1 && k == a - 1) v += sH[216 * (a - 1) + 18 * (6 + r) + x];
-      if (a >= 1 && k == a) v += sH[216 * (a - 1) + 18 * (6 + r) + 9 + x];
-      if (a < nf && k == a) v += sH[216 * a + 18 * r + x];
-      if (a < nf && k == a + 1) v += sH[216 * a + 18 * r + 9 + x];
-    }
-    return v;
-  };
-  for (int k = 0; k < N; ++k) {
-    for (int e = tid; e < 9 * ncol; e += blockDim.x) {
-      const int x = e / ncol, col = e - ncol * x;
-      double v = u_entry(k, x, col);
-      if (k >= 1) {
-        double c[9], wp[9];
+  // 4. backward sweep u_k = L_k^-T (w_k - C_{k+1}^T u_{k+1}), a column per lane
+  if (tid < ncol) {
+    double u[9], t[9];
+    double* x = X + (size_t)xcol * tid;
 #pragma unroll
-        for (int m = 0; m < 9; ++m) {
-          c[m] = sC[81 * k + 9 * x + m];
-          wp[m] = X[(size_t)ncol * (9 * (k - 1) + m) + col];
-        }
-        vi_lds_fence(c);
-        vi_lds_fence(wp);
+    for (int y = 0; y < 9; ++y) t[y] = x[(size_t)xrow * (9 * (N - 1) + y)];
+    for (int k = N - 1; k >= 0; --k) {
+      if (k + 1 < N)
 #pragma unroll
-        for (int m = 0; m < 9; ++m) v -= c[m] * wp[m];
+        for (int y = 0; y < 9; ++y)
+#pragma unroll
+          for (int m = 0; m < 9; ++m) t[y] -= sC[81 * (k + 1) + 9 * m + y] * u[m];
+#pragma unroll
+      for (int i = 8; i >= 0; --i) {
+        double v = t[i];
+#pragma unroll
+        for (int m = i + 1; m < 9; ++m) v -= sA[81 * k + 9 * i + m] * u[m];
+        u[i] = v * sInv[9 * k + i];
       }
-      sT[e] = v;
-    }
-    __syncthreads();
-    for (int col = tid; col < ncol; col += blockDim.x) {
-      L9 F;
-      load_l9(sA + 81 * k, sInv + 9 * k, F);
-      double w[9];
+      if (k >= 1)
 #pragma unroll
-      for (int x = 0; x < 9; ++x) w[x] = sT[ncol * x + col];
-      vi_lds_fence(w);
-      lsolve9r(F, w);
+        for (int y = 0; y < 9; ++y) t[y] = x[(size_t)xrow * (9 * (k - 1) + y)];
 #pragma unroll
-      for (int x = 0; x < 9; ++x) X[(size_t)ncol * (9 * k + x) + col] = w[x];
+      for (int y = 0; y < 9; ++y) x[(size_t)xrow * (9 * k + y)] = u[y];
     }
-    __syncthreads();
   }
-  for (int k = N - 1; k >= 0; --k) {
-    for (int e = tid; e < 9 * ncol; e += blockDim.x) {
-      const int x = e / ncol, col = e - ncol * x;
-      double t = X[(size_t)ncol * (9 * k + x) + col];
-      if (k + 1 < N) {
-        double c[9], un[9];
-#pragma unroll
-        for (int m = 0; m < 9; ++m) {
-          c[m] = sC[81 * (k + 1) + 9 * m + x];
-          un[m] = X[(size_t)ncol * (9 * (k + 1) + m) + col];
-        }
-        vi_lds_fence(c);
-        vi_lds_fence(un);
-#pragma unroll
-        for (int m = 0; m < 9; ++m) t -= c[m] * un[m];
-      }
-      sT[e] = t;
-    }
-    __syncthreads();
-    for (int col = tid; col < ncol; col += blockDim.x) {
-      L9 F;
-      load_l9(sA + 81 * k, sInv + 9 * k, F);
-      double v[9];
-#pragma unroll
-      for (int x = 0; x < 9; ++x) v[x] = sT[ncol * x + col];
-      vi_lds_fence(v);
-      ltsolve9r(F, v);
-#pragma unroll
-      for (int x = 0; x < 9; ++x) X[(size_t)ncol * (9 * k + x) + col] = v[x];
-    }
-    __syncthreads();
-  }
+  __syncthreads();
   // 5. S <- S - H_xy X (upper blocks), rhs <- rhs + H_xy z; one row of a block
   //    (or of the rhs) per task
-  auto hxy = [&](int a, int r, int k, int x) -> double {   // H(x_a row r, y_k component x)
-    double v = 0.0;
-    if (a >= 1 && (k == a - 1 || k == a)) v += sH[216 * (a - 1) + 18 * (6 + r) + (k == a - 1 ? x : 9 + x)];
-    if (a < nf && (k == a || k == a + 1)) v += sH[216 * a + 18 * r + (k == a ? x : 9 + x)];
-    return v;
-  };
-  for (int e = tid; e < (nblk + W.n_free) * 6; e += blockDim.x) {
+  for (int e = tid; e < (nblk + W.n_free) * 6; e += kViLinThreads) {
     const int b = e / 6, r = e % 6;
     int sa, sb = 0;
     const bool rhs = b >= nblk;
@@ -874,25 +825,33 @@ __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
     else
       upper_pair(b, W.n_free, sa, sb);
     const int a = sPose[sa];
-    const int k1 = a + 1 < N ? a + 1 : N - 1;
-    if (rhs) {
-      double v = 0.0;
-      for (int k = (a >= 1 ? a - 1 : 0); k <= k1; ++k)
-        for (int x = 0; x < 9; ++x) v += hxy(a, r, k, x) * X[(size_t)ncol * (9 * k + x) + nS];
-      sB[6 * sa + r] += v;
-      continue;
-    }
+    // H(x_a row r, y_k) of the states k = a - 1, a, a + 1
+    const double* h0 = sM + (a >= 1 ? oH + 216 * (a - 1) + 18 * (6 + r) : oZero);
+    const double* h1 = sM + (a < nf ? oH + 216 * a + 18 * r : oZero);
+    const int n0 = a >= 1 ? 9 : 0;
     double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int k = (a >= 1 ? a - 1 : 0); k <= k1; ++k)
+    const double* x0 = X + (size_t)xcol * (rhs ? nS : 6 * sb);
+    const int nc = rhs ? 1 : 6;
+#pragma unroll
+    for (int j = -1; j <= 1; ++j) {
+      if ((j < 0 && a < 1) || (j > 0 && a >= nf)) continue;
+      const double* xr = x0 + (size_t)xrow * (9 * (a + j));
+#pragma unroll
       for (int x = 0; x < 9; ++x) {
-        const double h = hxy(a, r, k, x);
-        const double* xr = X + (size_t)ncol * (9 * k + x) + 6 * sb;
-        for (int c = 0; c < 6; ++c) acc[c] += h * xr[c];
+        const double h = j < 0 ? h0[x] : j > 0 ? h1[9 + x] : h0[n0 + x] + h1[x];
+#pragma unroll
+        for (int c = 0; c < 6; ++c)
+          if (c < nc) acc[c] += h * xr[(size_t)xrow * x + (size_t)xcol * c];
       }
-    for (int c = (sa == sb ? r : 0); c < 6; ++c) S[kBS * b + 6 * r + c] -= acc[c];
+    }
+    if (rhs) {
+      sB[6 * sa + r] += acc[0];
+    } else {
+      for (int c = (sa == sb ? r : 0); c < 6; ++c) S[kBS * b + 6 * r + c] -= acc[c];
+    }
   }
   if (XL)
-    for (int e = tid; e < 9 * N * ncol; e += blockDim.x) Xg[e] = sXd[e];
+    for (int e = tid; e < 9 * N * ncol; e += kViLinThreads) Xg[e] = sXd[ncol * (e % (9 * N)) + e / (9 * N)];
 }
 
 // ---------------------------------------------------------------------------
@@ -917,8 +876,10 @@ __global__ __launch_bounds__(256) void k_vi_cand(ViArgs V, int wbase) {
   const double* dx = V.dp + kDpStride * wi;
   // dy = -z - X dx
   for (int e = tid; e < 9 * N; e += blockDim.x) {
-    double v = -X[(size_t)ncol * e + nS];
-    for (int c = 0; c < nS; ++c) v -= X[(size_t)ncol * e + c] * dx[c];
+    const double* x = X + e;   // column-major: the lanes' reads are contiguous
+    double v = -x[(size_t)9 * N * nS];
+#pragma unroll 6
+    for (int c = 0; c < nS; ++c) v -= x[(size_t)9 * N * c] * dx[c];
     cstates[e] = states[e] + v;
   }
   __syncthreads();
