@@ -23,6 +23,7 @@
 
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "device.hpp"
 #include "geometry.hpp"
@@ -520,48 +521,159 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
   return __longlong_as_double(((long long)hi << 32) | lo);
 }
 
+// a -= b(s, C) m with b(s, C) the s of lane C of the own row of sixteen lanes: one
+// v_fmac_f64 with a row broadcast instead of two lane reads and an fma.  The compiler
+// does not see the DPP reads, so the two wait states that they need after a VALU write
+// of s lead each block (nothing else in the kernels that use it reads by DPP).
+#define BA_FMAC_ROW(d, s, m, c) "v_fmac_f64_dpp %" #d ", -%" #s ", %" #m " row_newbcast:%" #c " row_mask:0xf bank_mask:0xf\n"
+// one broadcast column over two accumulators: a0 -= b(s, C) m0, a1 -= b(s, C) m1
+template <int C>
+__device__ __forceinline__ void sub_row(double& a0, double& a1, double s, double m0, double m1) {
+  __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 2, 3, 5) BA_FMAC_ROW(1, 2, 4, 5)
+                   : "+&v"(a0), "+&v"(a1)
+                   : "v"(s), "v"(m0), "v"(m1), "n"(C));
+}
+template <int C>
+__device__ __forceinline__ void sub_row2(double& a0, double& a1, double& b0, double& b1, double s, double m0,
+                                         double m1) {
+  __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 4, 5, 7) BA_FMAC_ROW(1, 4, 6, 7) BA_FMAC_ROW(2, 4, 5, 8)
+                       BA_FMAC_ROW(3, 4, 6, 8)
+                   : "+&v"(a0), "+&v"(a1), "+&v"(b0), "+&v"(b1)
+                   : "v"(s), "v"(m0), "v"(m1), "n"(C), "n"(C + 1));
+}
+// columns C .. C + 3 of x and y
+template <int C>
+__device__ __forceinline__ void sub_row4(double (&x)[9], double (&y)[9], double s, double m0, double m1) {
+  __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 8, 9, 11) BA_FMAC_ROW(1, 8, 10, 11) BA_FMAC_ROW(2, 8, 9, 12)
+                       BA_FMAC_ROW(3, 8, 10, 12) BA_FMAC_ROW(4, 8, 9, 13) BA_FMAC_ROW(5, 8, 10, 13)
+                           BA_FMAC_ROW(6, 8, 9, 14) BA_FMAC_ROW(7, 8, 10, 14)
+                   : "+&v"(x[C]), "+&v"(y[C]), "+&v"(x[C + 1]), "+&v"(y[C + 1]), "+&v"(x[C + 2]), "+&v"(y[C + 2]),
+                     "+&v"(x[C + 3]), "+&v"(y[C + 3])
+                   : "v"(s), "v"(m0), "v"(m1), "n"(C), "n"(C + 1), "n"(C + 2), "n"(C + 3));
+}
+// columns C .. 8 of x and y
+template <int C>
+__device__ __forceinline__ void sub_rows(double (&x)[9], double (&y)[9], double s, double m0, double m1) {
+  if constexpr (C < 6) {
+    sub_row4<C>(x, y, s, m0, m1);
+    sub_rows<C + 4>(x, y, s, m0, m1);
+  } else if constexpr (C < 8) {
+    sub_row2<C>(x[C], y[C], x[C + 1], y[C + 1], s, m0, m1);
+    sub_rows<C + 2>(x, y, s, m0, m1);
+  } else if constexpr (C == 8) {
+    sub_row<C>(x[C], y[C], s, m0, m1);
+  }
+}
+// t[i] -= b(r[i], M) m for all nine
+template <int M>
+__device__ __forceinline__ void sub_col(double (&t)[9], const double (&r)[9], double m) {
+  __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 5, 10, 11) BA_FMAC_ROW(1, 6, 10, 11) BA_FMAC_ROW(2, 7, 10, 11)
+                       BA_FMAC_ROW(3, 8, 10, 11) BA_FMAC_ROW(4, 9, 10, 11)
+                   : "+&v"(t[0]), "+&v"(t[1]), "+&v"(t[2]), "+&v"(t[3]), "+&v"(t[4])
+                   : "v"(r[0]), "v"(r[1]), "v"(r[2]), "v"(r[3]), "v"(r[4]), "v"(m), "n"(M));
+  __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 4, 8, 9) BA_FMAC_ROW(1, 5, 8, 9) BA_FMAC_ROW(2, 6, 8, 9)
+                       BA_FMAC_ROW(3, 7, 8, 9)
+                   : "+&v"(t[5]), "+&v"(t[6]), "+&v"(t[7]), "+&v"(t[8])
+                   : "v"(r[5]), "v"(r[6]), "v"(r[7]), "v"(r[8]), "v"(m), "n"(M));
+}
+// v -= b(s, M) u[M], M + 1 .. 8 in order
+template <int M>
+__device__ __forceinline__ void sub_chain(double& v, double s, const double (&u)[9]) {
+  if constexpr (M < 8) {
+    __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 1, 2, 4) BA_FMAC_ROW(0, 1, 3, 5)
+                     : "+&v"(v)
+                     : "v"(s), "v"(u[M]), "v"(u[M + 1]), "n"(M), "n"(M + 1));
+    sub_chain<M + 2>(v, s, u);
+  } else if constexpr (M == 8) {
+    __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 1, 2, 3) : "+&v"(v) : "v"(s), "v"(u[8]), "n"(8));
+  }
+}
+#undef BA_FMAC_ROW
+
+__device__ __forceinline__ void pin(double& v) { __asm__ volatile("" : "+v"(v)); }   // not moved past a block above
+
+// Step j of the forward sweep (below): column j of the panels scaled by the pivot's
+// reciprocal root ir, then subtracted from the later columns and from the next state's.
+// The next pivot's root (an estimate and one third-order refinement, as rsqrt takes it)
+// is worked out between the products.  A pivot that is not positive and finite makes it
+// NaN and with it every later pivot; the last root is returned.
+template <int J>
+__device__ __forceinline__ double vi_panel_steps(double (&w)[9], double (&p)[9], double (&aw)[9], double (&ap)[9],
+                                                 int row, double ir) {
+  w[J] = row == J ? ir : w[J] * ir;
+  p[J] *= ir;
+  if constexpr (J < 8) {
+    sub_row<J + 1>(w[J + 1], p[J + 1], w[J], w[J], p[J]);
+    const double d = lane_value(w[J + 1], J + 1);
+    double y = __builtin_amdgcn_rsq(d);
+    pin(y);
+    sub_row4<0>(aw, ap, p[J], w[J], p[J]);
+    double t = y * -d;
+    pin(t);
+    sub_row<4>(aw[4], ap[4], p[J], w[J], p[J]);
+    double e = fma(t, y, 1.0);
+    pin(e);
+    sub_row4<5>(aw, ap, p[J], w[J], p[J]);
+    double m = y * e;
+    pin(m);
+    double q = fma(e, 0.375, 0.5);
+    pin(q);
+    double in = fma(m, q, y);
+    pin(in);
+    sub_rows<J + 2>(w, p, w[J], w[J], p[J]);
+    return vi_panel_steps<J + 1>(w, p, aw, ap, row, in);
+  } else {
+    sub_rows<0>(aw, ap, p[J], w[J], p[J]);
+    return ir;
+  }
+}
+template <int I>
+__device__ __forceinline__ void vi_back_steps(const double (&t)[9], const double (&r)[9], double (&u)[9]) {
+  double v = t[I];
+  sub_chain<I + 1>(v, r[I], u);
+  u[I] = v * lane_value(r[I], I);
+  if constexpr (I > 0) vi_back_steps<I - 1>(t, r, u);
+}
+
 // The elimination: one workgroup per window.  Its chain over the states (factor, then
 // the forward and the backward substitution of all columns) is what it takes; the bytes
-// are few.  Forward, a wave holds one row per lane of the 9-wide panel
-//   lanes 0-8    A_k (damped, less C_k C_k^T): becomes L_k
-//   lanes 9-17   A_{k,k+1}^T: becomes C_{k+1}
-//   the rest     kViCols columns of u_k - C_k w_{k-1}: become w_k
-// and factors it column by column, right-looking, with the pivot rows' entries read
-// across lanes: no barrier, and one pass of 45 steps for the factor, its panel and the
-// substitution (an entry's updates keep their order, so the values are those of the
-// left-looking loops).  Every wave repeats the 18 panel rows for its own columns.
-// The last waves add the pose-pose terms into the reduced system meanwhile.  Backward,
-// a lane holds a column.  At 10 keyframes (9 free): 72 us with the factor on one thread
-// and two barriers a state in each of three loops, XXX us so.
+// are few.  Forward, each row of sixteen lanes holds two 9-wide panels in registers,
+// w and p; its lanes 0-8 the rows of
+//   w  A_k (damped, less C_k C_k^T): becomes L_k
+//   p  A_{k,k+1}^T: becomes C_{k+1}
+// and lanes 9-15 a column each of u_k - C_k w_{k-1}: becomes w_k.  The panels are
+// factored column by column, right-looking, the pivot rows' entries broadcast within the
+// sixteen lanes; as a column of C_{k+1} is done its products with C_{k+1}^T and w_k are
+// added up for the next state.  No barrier, no LDS on the chain, and one pass for the
+// factor, its panel and the substitution; an entry's updates keep their order, so the
+// values are those of left-looking loops.  The panels are repeated for every seven
+// lanes of columns.  The last waves add the pose-pose terms into the reduced system
+// meanwhile.  Backward, a lane holds a column and reads L_k and C_{k+1} the same way.
+// At 10 keyframes (9 free): 72 us with the factor on one thread and two barriers a state
+// in each of three loops; 44 us with a wave's panel and the products' operands from LDS;
+// 40 us with all operands by lane reads (issue: three instructions a product); 35 us so.
 constexpr int kViLinThreads = 512;                     // threads of the elimination workgroup
-constexpr int kViPanel = 18, kViCols = 64 - kViPanel;  // panel rows, columns of a wave
-constexpr int kViSweepWaves = 4;                       // forward waves; the others: pose-pose terms
+constexpr int kViCols = 4 * 2 * (16 - 9);              // columns of a forward wave
+constexpr int kViSweepWaves = 3;                       // forward waves; the others: pose-pose terms
 constexpr int kViPoseThreads = kViLinThreads - 64 * kViSweepWaves;
+// LDS doubles of the elimination beside X, for N states (the offsets in the kernel).
+constexpr int vi_lin_doubles(int N) { return 81 * (4 * N - 1) + 216 * (N - 1) + 9 * N + 9; }
 static_assert(kViSweepWaves * kViCols >= 6 * kViMaxStates + 1 && 64 * kViSweepWaves >= 6 * kViMaxStates + 1,
               "a lane per column");
 
 template <bool XL>
 __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
-  extern __shared__ __align__(16) double sXd[];   // X when it fits in LDS (XL)
-  // A_kk (damped; the factor reads its lower part), and L_k's strictly lower entries
-  // transposed above the diagonal: a wave behind still reads A_k below it
-  constexpr int oA = 0;
-  constexpr int oO = oA + kViMaxStates * 81;                   // A_{k,k+1}
-  constexpr int oC = oO + (kViMaxStates - 1) * 81;             // C_k = A_{k,k-1} L_{k-1}^-T, k >= 1
-  constexpr int oH = oC + kViMaxStates * 81;                   // H_xy per factor
-  constexpr int oG = oH + (kViMaxStates - 1) * 216;            // g_y
-  constexpr int oInv = oG + kViMaxStates * 9;                  // 1 / diag(L_k)
-  constexpr int oCw = oInv + kViMaxStates * 9;                 // C_k of the forward waves after the first
-  constexpr int oZero = oCw + (kViSweepWaves - 1) * 81;        // nine zeros
-  __shared__ double sM[oZero + 9];
+  // the arrays of vi_lin_doubles(N), then X when both fit in LDS (XL)
+  extern __shared__ __align__(16) double sDyn[];
+  double* sM;
+  if constexpr (XL) {
+    sM = sDyn;
+  } else {
+    __shared__ double sStat[vi_lin_doubles(kViMaxStates)];
+    sM = sStat;
+  }
   __shared__ int sPose[kViMaxStates];   // pose of each free slot
   __shared__ int sOk;
-  double* const sA = sM + oA;
-  double* const sO = sM + oO;
-  double* const sC = sM + oC;
-  double* const sH = sM + oH;
-  double* const sG = sM + oG;
-  double* const sInv = sM + oInv;
   const int wi = V.win_order[wbase + blockIdx.x];
   const WinDev W = V.win[wi];
   const WinState& st = V.state[wi];
@@ -572,8 +684,14 @@ __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
   // fits (XL) and copied out at the end, since k_vi_cand reads it column by
   // column; otherwise column-major in the workspace throughout
   double* Xg = V.rec + (size_t)kViFactorStride * nf;
-  double* X = XL ? sXd : Xg;
+  double* X = XL ? sM + vi_lin_doubles(N) : Xg;
   const int xrow = XL ? ncol : 1, xcol = XL ? 1 : 9 * N;   // strides of X
+  const int oO = 81 * N;               // after A_kk (damped): A_{k,k+1}
+  const int oL = oO + 81 * (N - 1);    // L_k, the diagonal's reciprocals in its place
+  const int oC = oL + 81 * N;          // C_{k+1} = A_{k+1,k} L_k^-T
+  const int oH = oC + 81 * N;          // H_xy per factor
+  const int oG = oH + 216 * (N - 1);   // g_y
+  const int oZero = oG + 9 * N;        // nine zeros
   const int* fs = V.free_slot + W.pose_off;
   if (tid < N && fs[tid] >= 0) sPose[fs[tid]] = tid;
   if (tid == 0) sOk = 1;
@@ -622,13 +740,11 @@ __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
         if (e < nA) {
           const int x = (e % 81) / 9, y = e % 9;
           if (x == y) v += lam * fmax(v, 1e-9);
-          sA[e] = v;
+          sM[e] = v;
         } else if (e < nA + nO) {
-          sO[e - nA] = v;
-        } else if (e < nA + nO + nH) {
-          sH[e - nA - nO] = v;
-        } else if (e < ntot) {
-          sG[e - nA - nO - nH] = v;
+          sM[oO + e - nA] = v;
+        } else if (e < ntot) {   // H_xy, g_y
+          sM[oH + e - nA - nO] = v;
         }
       }
     }
@@ -704,81 +820,85 @@ __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
     }
   }
   // 3. factor and forward sweep w_k = L_k^-1 (u_k - C_k w_{k-1}), state by state
+  const int row = lane & 15;   // lane of its sixteen: panel rows 0-8, columns 9-15
   if (wave < kViSweepWaves && kViCols * wave < ncol) {
-    const int col = kViCols * wave + lane - kViPanel;
-    const bool arow = lane < 9, crow = !arow && lane < kViPanel, wcol = !arow && !crow && col < ncol;
-    const int pa = wcol && col < nS ? sPose[col / 6] : -1, pr = col % 6;
-    // the lane's entries of state k: sM[p0 + step y] + sM[p1 + y]
-    const int step = crow ? 9 : 1;
-    auto entry = [&](int k, double (&v)[9]) {
-      int p0 = oZero, p1 = oZero, sp = 1;
-      if (arow) {
-        p0 = oA + 81 * k + 9 * lane;
-      } else if (crow) {
-        if (k + 1 < N) {
-          p0 = oO + 81 * k + lane - 9;
-          sp = step;
-        }
-      } else if (wcol && col == nS) {
-        p0 = oG + 9 * k;
-      } else if (pa >= 0) {
+    // of the panels w and p: the lane's column, and where its entries of state k
+    // stand: sM[q0 + step y] + sM[q1 + y]
+    int col[2], lin[2], per[2], step[2], pa[2], h0[2], h1[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      col[q] = row < 9 ? ncol : kViCols * wave + 14 * (lane >> 4) + 7 * q + row - 9;
+      lin[q] = oZero;
+      per[q] = 0;
+      step[q] = 1;
+      pa[q] = -2;
+      h0[q] = h1[q] = oZero;
+      if (row < 9) {   // row of A_kk, row of A_{k,k+1}^T (past the last one: never used)
+        lin[q] = q == 0 ? 9 * row : oO + row;
+        per[q] = 81;
+        step[q] = q == 0 ? 1 : 9;
+      } else if (col[q] == nS) {
+        lin[q] = oG;
+        per[q] = 9;
+      } else if (col[q] < nS) {
         // factor a - 1 holds pose a as x_j (rows 6 + r), factor a as x_i (rows r)
-        if (pa >= 1 && (k == pa - 1 || k == pa)) p0 = oH + 216 * (pa - 1) + 18 * (6 + pr) + (k == pa ? 9 : 0);
-        if (pa < nf && (k == pa || k == pa + 1)) p1 = oH + 216 * pa + 18 * pr + (k == pa ? 0 : 9);
+        pa[q] = sPose[col[q] / 6];
+        const int r = col[q] % 6;
+        if (pa[q] >= 1) h0[q] = oH + 216 * (pa[q] - 1) + 18 * (6 + r);
+        if (pa[q] < nf) h1[q] = oH + 216 * pa[q] + 18 * r;
       }
+    }
+    auto entry = [&](int k, int q, double (&v)[9]) {
+      int q0 = lin[q] + per[q] * k, q1 = oZero;
+      const int d = k - pa[q];   // only next to the column's pose
+      if (pa[q] >= 1 && (d == -1 || d == 0)) q0 = h0[q] + (d == 0 ? 9 : 0);
+      if (pa[q] >= 0 && pa[q] < nf && (d == 0 || d == 1)) q1 = h1[q] + (d == 0 ? 0 : 9);
 #pragma unroll
-      for (int y = 0; y < 9; ++y) v[y] = sM[p0 + sp * y] + sM[p1 + y];
+      for (int y = 0; y < 9; ++y) v[y] = sM[q0 + step[q] * y] + sM[q1 + y];
     };
-    double w[9], nx[9];
-    entry(0, w);
+    double w[9], p[9];
+    entry(0, 0, w);
+    entry(0, 1, p);
+    double nw[9], np[9];
+    entry(min(1, N - 1), 0, nw);
+    entry(min(1, N - 1), 1, np);
     bool ok = true;
+#pragma unroll 2
     for (int k = 0; k < N; ++k) {
-      const int ck = wave == 0 ? oC + 81 * k : oCw + 81 * (wave - 1);   // C_k
-      if (k >= 1) {
-        // A_k less C_k C_k^T (the sum first), u_k less C_k w_{k-1}
-        double m[9];
+      const int kn = min(k + 2, N - 1);
+      double nw2[9], np2[9], aw[9], ap[9];   // the entries of the state after the next
+      entry(kn, 0, nw2);
+      entry(kn, 1, np2);
+      // minus the sum for A_{k+1} (added to it whole), u_{k+1} less the products
 #pragma unroll
-        for (int y = 0; y < 9; ++y) m[y] = arow ? sM[ck + 9 * lane + y] : -w[y];
+      for (int y = 0; y < 9; ++y) {
+        aw[y] = nw[y];
+        ap[y] = row < 9 ? 0.0 : np[y];
+      }
+      const double ir = vi_panel_steps<0>(w, p, aw, ap, row, rsqrt(lane_value(w[0], 0)));
+      ok = __builtin_amdgcn_readfirstlane(ir > 0.0 && isfinite(ir));   // the same in every lane and wave
+      if (!ok) break;
+      if (tid < 9) {
 #pragma unroll
-        for (int x = 0; x < 9; ++x) {
-          double v = arow ? 0.0 : nx[x];
-#pragma unroll
-          for (int y = 0; y < 9; ++y) v = fma(sM[ck + 9 * x + y], m[y], v);
-          w[x] = arow ? nx[x] - v : crow ? nx[x] : v;
+        for (int y = 0; y < 9; ++y) {
+          sM[oL + 81 * k + 9 * tid + y] = w[y];
+          sM[oC + 81 * k + 9 * tid + y] = p[y];
         }
       }
-      if (k + 1 < N) entry(k + 1, nx);
-      double iv[9];
+      double* o = X + (size_t)xrow * (9 * k);
+      if (col[0] < ncol)
 #pragma unroll
-      for (int j = 0; j < 9; ++j) {
-        const double d = lane_value(w[j], j);
-        ok = ok && d > 0.0 && isfinite(d);
-        iv[j] = rsqrt(d);
-        w[j] *= iv[j];
+        for (int y = 0; y < 9; ++y) o[(size_t)xrow * y + (size_t)xcol * col[0]] = w[y];
+      if (col[1] < ncol)
 #pragma unroll
-        for (int c = j + 1; c < 9; ++c) w[c] -= w[j] * lane_value(w[j], c);
+        for (int y = 0; y < 9; ++y) o[(size_t)xrow * y + (size_t)xcol * col[1]] = p[y];
+#pragma unroll
+      for (int y = 0; y < 9; ++y) {
+        w[y] = row < 9 ? nw[y] + ap[y] : aw[y];
+        p[y] = row < 9 ? np[y] : ap[y];
+        nw[y] = nw2[y];
+        np[y] = np2[y];
       }
-      if (!ok) break;   // the same in every wave
-      if (wave == 0 && arow) {
-#pragma unroll
-        for (int y = 0; y < 8; ++y)
-          if (y < lane) sA[81 * k + 9 * y + lane] = w[y];
-        if (lane == 0)
-#pragma unroll
-          for (int y = 0; y < 9; ++y) sInv[9 * k + y] = iv[y];
-      }
-      if (crow && k + 1 < N) {
-        const int cn = wave == 0 ? oC + 81 * (k + 1) : oCw + 81 * (wave - 1);
-#pragma unroll
-        for (int y = 0; y < 9; ++y) sM[cn + 9 * (lane - 9) + y] = w[y];
-      }
-      if (wcol)
-#pragma unroll
-        for (int x = 0; x < 9; ++x) X[(size_t)xrow * (9 * k + x) + (size_t)xcol * col] = w[x];
-      // C_{k+1} is read by the wave's other lanes
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
     if (!ok && tid == 0) sOk = 0;
   }
@@ -788,70 +908,113 @@ __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
     return;
   }
   // 4. backward sweep u_k = L_k^-T (w_k - C_{k+1}^T u_{k+1}), a column per lane
-  if (tid < ncol) {
-    double u[9], t[9];
-    double* x = X + (size_t)xcol * tid;
+  //    and, in lanes 0-8 of each sixteen, a row of C_{k+1} and of L_k
+  if (64 * wave < ncol) {
+    double* x = X + (size_t)xcol * min(tid, ncol - 1);
+    const int lr = 9 * min(row, 8);
+    double u[9], t[9], rc[9], rl[9];
 #pragma unroll
-    for (int y = 0; y < 9; ++y) t[y] = x[(size_t)xrow * (9 * (N - 1) + y)];
+    for (int y = 0; y < 9; ++y) {
+      t[y] = x[(size_t)xrow * (9 * (N - 1) + y)];
+      rl[y] = sM[oL + lr + 81 * (N - 1) + y];
+      rc[y] = 0.0;
+      u[y] = 0.0;
+    }
+#pragma unroll 2
     for (int k = N - 1; k >= 0; --k) {
-      if (k + 1 < N)
+      const int kn = max(k - 1, 0);
+      double tn[9], rcn[9], rln[9];   // the next state's
 #pragma unroll
-        for (int y = 0; y < 9; ++y)
-#pragma unroll
-          for (int m = 0; m < 9; ++m) t[y] -= sC[81 * (k + 1) + 9 * m + y] * u[m];
-#pragma unroll
-      for (int i = 8; i >= 0; --i) {
-        double v = t[i];
-#pragma unroll
-        for (int m = i + 1; m < 9; ++m) v -= sA[81 * k + 9 * i + m] * u[m];
-        u[i] = v * sInv[9 * k + i];
+      for (int y = 0; y < 9; ++y) {
+        tn[y] = x[(size_t)xrow * (9 * kn + y)];
+        rcn[y] = sM[oC + lr + 81 * kn + y];
+        rln[y] = sM[oL + lr + 81 * kn + y];
       }
-      if (k >= 1)
+      {   // the last state has no C: its rc and u are zeros
+        sub_col<0>(t, rc, u[0]);
+        sub_col<1>(t, rc, u[1]);
+        sub_col<2>(t, rc, u[2]);
+        sub_col<3>(t, rc, u[3]);
+        sub_col<4>(t, rc, u[4]);
+        sub_col<5>(t, rc, u[5]);
+        sub_col<6>(t, rc, u[6]);
+        sub_col<7>(t, rc, u[7]);
+        sub_col<8>(t, rc, u[8]);
+      }
+      vi_back_steps<8>(t, rl, u);
 #pragma unroll
-        for (int y = 0; y < 9; ++y) t[y] = x[(size_t)xrow * (9 * (k - 1) + y)];
-#pragma unroll
-      for (int y = 0; y < 9; ++y) x[(size_t)xrow * (9 * k + y)] = u[y];
+      for (int y = 0; y < 9; ++y) {
+        if (tid < ncol) x[(size_t)xrow * (9 * k + y)] = u[y];
+        t[y] = tn[y];
+        rc[y] = rcn[y];
+        rl[y] = rln[y];
+      }
     }
   }
   __syncthreads();
   // 5. S <- S - H_xy X (upper blocks), rhs <- rhs + H_xy z; one row of a block
   //    (or of the rhs) per task
-  for (int e = tid; e < (nblk + W.n_free) * 6; e += kViLinThreads) {
-    const int b = e / 6, r = e % 6;
-    int sa, sb = 0;
-    const bool rhs = b >= nblk;
-    if (rhs)
-      sa = b - nblk;
-    else
-      upper_pair(b, W.n_free, sa, sb);
+  // H(x_a row r, y_k) of the state k = a + J
+  auto hrow = [&](int a, int r, auto J, double (&h)[9]) {
+    const double* h0 = sM + (a >= 1 ? oH + 216 * (a - 1) + 18 * (6 + r) + (J < 0 ? 0 : 9) : oZero);
+    const double* h1 = sM + (a < nf ? oH + 216 * a + 18 * r + (J > 0 ? 9 : 0) : oZero);
+#pragma unroll
+    for (int x = 0; x < 9; ++x) h[x] = J < 0 ? h0[x] : J > 0 ? h1[x] : h0[x] + h1[x];
+  };
+  const std::integral_constant<int, -1> kBefore;
+  const std::integral_constant<int, 0> kAt;
+  const std::integral_constant<int, 1> kAfter;
+  // three rows of a block per thread: LDS reads bound it, and an entry of X is read
+  // once for the three
+  for (int e = tid; e < nblk * 2; e += kViLinThreads) {
+    const int b = e / 2, r0 = 3 * (e % 2);
+    int sa, sb;
+    upper_pair(b, W.n_free, sa, sb);
     const int a = sPose[sa];
-    // H(x_a row r, y_k) of the states k = a - 1, a, a + 1
-    const double* h0 = sM + (a >= 1 ? oH + 216 * (a - 1) + 18 * (6 + r) : oZero);
-    const double* h1 = sM + (a < nf ? oH + 216 * a + 18 * r : oZero);
-    const int n0 = a >= 1 ? 9 : 0;
-    double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    const double* x0 = X + (size_t)xcol * (rhs ? nS : 6 * sb);
-    const int nc = rhs ? 1 : 6;
+    double* so = S + kBS * b + 6 * r0;
+    double acc[18], sv[18];
 #pragma unroll
-    for (int j = -1; j <= 1; ++j) {
-      if ((j < 0 && a < 1) || (j > 0 && a >= nf)) continue;
-      const double* xr = x0 + (size_t)xrow * (9 * (a + j));
-#pragma unroll
-      for (int x = 0; x < 9; ++x) {
-        const double h = j < 0 ? h0[x] : j > 0 ? h1[9 + x] : h0[n0 + x] + h1[x];
-#pragma unroll
-        for (int c = 0; c < 6; ++c)
-          if (c < nc) acc[c] += h * xr[(size_t)xrow * x + (size_t)xcol * c];
-      }
+    for (int c = 0; c < 18; ++c) {
+      acc[c] = 0.0;
+      sv[c] = so[c];
     }
-    if (rhs) {
-      sB[6 * sa + r] += acc[0];
-    } else {
-      for (int c = (sa == sb ? r : 0); c < 6; ++c) S[kBS * b + 6 * r + c] -= acc[c];
-    }
+    auto add = [&](auto J) {
+      double h[3][9];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) hrow(a, r0 + r, J, h[r]);
+      const double* xr = X + (size_t)xcol * (6 * sb) + (size_t)xrow * (9 * (a + J));
+#pragma unroll
+      for (int x = 0; x < 9; ++x)
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+          const double v = xr[(size_t)xrow * x + (size_t)xcol * c];
+#pragma unroll
+          for (int r = 0; r < 3; ++r) acc[6 * r + c] += h[r][x] * v;
+        }
+    };
+    if (a >= 1) add(kBefore);
+    add(kAt);
+    if (a < nf) add(kAfter);
+#pragma unroll
+    for (int c = 0; c < 18; ++c)
+      if (sa != sb || c % 6 >= r0 + c / 6) so[c] = sv[c] - acc[c];
+  }
+  for (int e = kViLinThreads - 1 - tid; e < nS; e += kViLinThreads) {   // from the last wave on
+    const int a = sPose[e / 6], r = e % 6;
+    double v = 0.0;
+    auto add = [&](auto J) {
+      double h[9];
+      hrow(a, r, J, h);
+#pragma unroll
+      for (int x = 0; x < 9; ++x) v += h[x] * X[(size_t)xcol * nS + (size_t)xrow * (9 * (a + J) + x)];
+    };
+    if (a >= 1) add(kBefore);
+    add(kAt);
+    if (a < nf) add(kAfter);
+    sB[e] += v;
   }
   if (XL)
-    for (int e = tid; e < 9 * N * ncol; e += kViLinThreads) Xg[e] = sXd[ncol * (e % (9 * N)) + e / (9 * N)];
+    for (int e = tid; e < 9 * N * ncol; e += kViLinThreads) Xg[e] = X[ncol * (e % (9 * N)) + e / (9 * N)];
 }
 
 // ---------------------------------------------------------------------------
@@ -910,27 +1073,20 @@ hipError_t launch_vi_preint(int n_factors, const int32_t* sample_begin, const do
 void launch_vi_lin(const ViArgs& V, int wbase, int nwin, hipStream_t st) {
   if (nwin <= 0 || V.max_factors <= 0) return;
   hipLaunchKernelGGL(k_vi_fac, dim3(V.max_factors, nwin), dim3(64), 0, st, V, wbase);
-  // X (9N x (6 n_free + 1) doubles, n_free <= N) in LDS beside the static
-  // arrays when the CU's 160 KB hold both.  The static size is the compiled
-  // kernel's own (asked once per process, when its dynamic LDS limit is
-  // raised, as for the other kernels); if either call fails, X stays in the
-  // workspace.
-  constexpr size_t kLds = 160 * 1024;
+  // X (9N x (6 n_free + 1) doubles, n_free <= N) in LDS beside the other
+  // arrays when the CU's 160 KB hold both (N <= 14; the limit is raised once
+  // per process, as for the other kernels); otherwise, or if that fails, X
+  // stays in the workspace.
+  constexpr size_t kLds = 160 * 1024 - 1024;   // less the kernel's static LDS
   const int N = V.max_factors + 1;
-  const size_t xb = sizeof(double) * 9 * (size_t)N * (6 * (size_t)N + 1);
+  const size_t xb = sizeof(double) * (vi_lin_doubles(N) + 9 * (size_t)N * (6 * (size_t)N + 1));
   static std::once_flag once;
   static bool attr = false;
-  static size_t kStatic = kLds;
   std::call_once(once, [] {
-    hipFuncAttributes fa;
-    if (hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(&k_vi_lin<true>)) != hipSuccess ||
-        fa.sharedSizeBytes >= kLds)
-      return;
-    kStatic = fa.sharedSizeBytes;
     attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vi_lin<true>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLds - kStatic)) == hipSuccess;
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds) == hipSuccess;
   });
-  if (attr && kStatic + xb <= kLds)
+  if (attr && xb <= kLds)
     hipLaunchKernelGGL(k_vi_lin<true>, dim3(nwin), dim3(kViLinThreads), xb, st, V, wbase);
   else
     hipLaunchKernelGGL(k_vi_lin<false>, dim3(nwin), dim3(kViLinThreads), 0, st, V, wbase);
