@@ -5,7 +5,7 @@
 // of the samples between them (the model of Forster et al. 2017 that the
 // paper cites).  The visual part of the window solve is unchanged; per LM
 // attempt and window this file adds
-//   k_vi_fac   one wave per IMU factor at the current state: residual,
+//   k_vi_fac   one workgroup per IMU factor at the current state: residual,
 //              Jacobian, J^T Lambda J and J^T Lambda r (FP64) into the
 //              factor's record;
 //   k_vi_lin   the pose-pose terms added into the summed reduced system and
@@ -288,6 +288,23 @@ __device__ void imu_factor(const double* Pi, const double* si, const double* Pj,
     }
 }
 
+// A double of lane L of the own four lanes.
+template <int L>
+__device__ __forceinline__ double quad_value(double v) {
+  const long long b = __double_as_longlong(v);
+  constexpr int ctrl = L * 0x55;   // quad_perm L, L, L, L
+  const unsigned lo = __builtin_amdgcn_mov_dpp((int)b, ctrl, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), ctrl, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | lo);
+}
+
+// LDS of one wave: its accesses above done before those below.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ double imu_cost1(const double* r, const double* Info) {
   double c = 0.0;
   for (int a = 0; a < 15; ++a) {
@@ -301,12 +318,283 @@ __device__ double imu_cost1(const double* r, const double* Info) {
 }  // namespace
 
 // ---------------------------------------------------------------------------
-// preintegration: one thread per factor, samples in time order
+// preintegration: one workgroup per factor, samples in time order
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(64) void k_vi_preint(int n_factors, const int32_t* sample_begin, const double* gyro,
-                                                  const double* accel, double dt, const double* bias_bar, double sg,
-                                                  double sa, double sbg, double sba, double* out) {
+// Four chains run over a factor's samples: the rotation dR, the 9x9 covariance, the
+// gyroscope bias' Jacobians, and those of the accelerometer bias with the velocity and
+// position.  A thread per factor took 3 us a sample (148 us for nine factors of 50
+// samples): about a thousand instructions in one lane.  Here what a sample needs by itself (Exp,
+// J_r, the noise products) is worked out a sample per lane, the rotation chain by three
+// lanes, and the other chains each by a wave of its own, an entry's (or a row's)
+// products per lane: 27 us.  Every entry keeps its sums' order, the fused products
+// written out where the order of the terms leaves the choice.
+constexpr int kPreThreads = 256, kPreSamples = 64;   // samples staged at a time
+constexpr int kPsE = 0, kPsJr = 9, kPsGG = 18, kPsR = 27, kPsX = 36, kPsB = 45, kPsAA = 54, kPsA = 63, kPsRa = 66,
+              kPsRec = 69;   // a sample's record: Exp, J_r, J_r J_r^T, dR, dR [a]x, -dR [a]x dt, dR dR^T, a, dR a
+// odd, so that the lanes of a wave (a sample each) meet no bank twice in a row
+static_assert(kPsRec % 2 == 1, "record stride");
+
+// a0 b0 + a1 b1 + a2 b2
+__device__ __forceinline__ double dot3(double a0, double b0, double a1, double b1, double a2, double b2) {
+  return fma(a2, b2, fma(a0, b0, a1 * b1));
+}
+
+__global__ __launch_bounds__(kPreThreads) void k_vi_preint(const int32_t* sample_begin, const double* gyro,
+                                                           const double* accel, double dt,
+                                                           const double* bias_bar, double sg, double sa, double sbg,
+                                                           double sba, double* out) {
+  __shared__ double sS[kPreSamples * kPsRec];
+  __shared__ double sP[81];   // covariance of the errors (dphi, dv, dp): 3x3 blocks P_ij, i <= j, 9 (3 i + j)
+  const int f = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  double* pre = out + (size_t)kPreStride * f;
+  const double ba[3] = {bias_bar[6 * f], bias_bar[6 * f + 1], bias_bar[6 * f + 2]};
+  const double bg[3] = {bias_bar[6 * f + 3], bias_bar[6 * f + 4], bias_bar[6 * f + 5]};
+  const double qg = sg * sg / dt, qa = sa * sa / dt, h = 0.5 * dt;
+  const int s0 = sample_begin[f], s1 = sample_begin[f + 1];
+  if (tid < 81) sP[tid] = 0.0;
+  // wave 0: lanes 0-2 a row of dR in its first phase; then lane 4 (3 i + x) + j row x of
+  // the blocks (A P)_ij and, i <= j, P_ij
+  double dR[3] = {lane == 0 ? 1.0 : 0.0, lane == 1 ? 1.0 : 0.0, lane == 2 ? 1.0 : 0.0};
+  const int pj = lane & 3, pi = (lane >> 2) / 3, px = (lane >> 2) % 3;
+  const bool pact = pj < 3 && pi < 3;
+  // wave 1, lanes 0-2: a column of J_Rg, J_vg, J_pg; wave 2, lanes 0-8: an entry of J_va,
+  // J_pa; wave 3, lanes 0-2: an entry of dv, dp
+  double J[3] = {}, Jv[3] = {}, Jp[3] = {};
+  for (int base = s0; base < s1; base += kPreSamples) {
+    const int ns = min(kPreSamples, s1 - base);
+    if (tid < ns) {
+      const int s = base + tid;
+      double* R = sS + kPsRec * tid;
+      double w[3], a[3], Ek[9], Jr[9];
+      for (int k = 0; k < 3; ++k) {
+        w[k] = (gyro[3 * s + k] - bg[k]) * dt;
+        a[k] = accel[3 * s + k] - ba[k];
+      }
+      exp_so3_jr(w, Ek, Jr);
+      for (int k = 0; k < 9; ++k) {
+        R[kPsE + k] = Ek[k];
+        R[kPsJr + k] = Jr[k];
+      }
+      for (int k = 0; k < 3; ++k) R[kPsA + k] = a[k];
+      for (int x = 0; x < 3; ++x)
+        for (int y = 0; y < 3; ++y) {
+          double gg = 0.0;
+          for (int k = 0; k < 3; ++k) gg += Jr[3 * x + k] * Jr[3 * y + k];
+          R[kPsGG + 3 * x + y] = gg;
+        }
+    }
+    __syncthreads();
+    if (tid < 3) {   // dR before each sample
+      double E[9];
+      for (int k = 0; k < 9; ++k) E[k] = sS[kPsE + k];
+      for (int s = 0; s < ns; ++s) {
+        double* R = sS + kPsRec * s;
+        const double* Rn = sS + kPsRec * min(s + 1, ns - 1);
+        double En[9];
+        for (int k = 0; k < 9; ++k) En[k] = Rn[kPsE + k];
+        for (int k = 0; k < 3; ++k) R[kPsR + 3 * tid + k] = dR[k];
+        double nR[3];
+        for (int k = 0; k < 3; ++k) nR[k] = dot3(dR[0], E[k], dR[1], E[3 + k], dR[2], E[6 + k]);
+        for (int k = 0; k < 3; ++k) dR[k] = nR[k];
+        for (int k = 0; k < 9; ++k) E[k] = En[k];
+      }
+    }
+    __syncthreads();
+    if (tid < ns) {
+      double* R = sS + kPsRec * tid;
+      double r[9], a[3], Ax[9], X[9], Ra[3];
+      for (int k = 0; k < 9; ++k) r[k] = R[kPsR + k];
+      for (int k = 0; k < 3; ++k) a[k] = R[kPsA + k];
+      skew3(a, Ax);
+      mul33(r, Ax, X);
+      for (int k = 0; k < 3; ++k) Ra[k] = dot3(r[3 * k], a[0], r[3 * k + 1], a[1], r[3 * k + 2], a[2]);
+      for (int k = 0; k < 9; ++k) {
+        R[kPsX + k] = X[k];
+        R[kPsB + k] = -X[k] * dt;
+      }
+      for (int k = 0; k < 3; ++k) R[kPsRa + k] = Ra[k];
+      for (int x = 0; x < 3; ++x)
+        for (int y = 0; y < 3; ++y) {
+          double aa = 0.0;
+          for (int k = 0; k < 3; ++k) aa += r[3 * x + k] * r[3 * y + k];
+          R[kPsAA + 3 * x + y] = aa;
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {
+      // P <- A P A^T + noise with A = [[E^T, 0, 0], [B, I, 0], [B dt/2, dt I, I]] and
+      // B = -dR [a]x dt: T = A P, then T A^T.  Row x of T_ij is the products with block
+      // row 0 of P, plus rows of block rows 1 and 2; P_ij's are products with T_i0 (the
+      // first lane of the four), plus rows of T_i1 and T_ij.
+      const int i = pact ? pi : 0, j = pact ? pj : 0, x = px;
+      // row x of P_1j and P_2j (a column of the block above the diagonal)
+      const int a1 = j >= 1 ? 9 * (3 + j) + 3 * x : 9 * 1 + x, t1 = j >= 1 ? 1 : 3;
+      const int a2 = j == 2 ? 9 * 8 + 3 * x : 9 * (3 * j + 2) + x, t2 = j == 2 ? 1 : 3;
+      // the sample's coefficients: q of T, c of P, the noise term
+      const int aq = i == 0 ? kPsE + x : kPsB + 3 * x, tq = i == 0 ? 3 : 1;
+      const int ac = j == 0 ? kPsE : kPsB, tm = j == 0 ? 3 : 1, tb = j == 0 ? 1 : 3;
+      const int an = (i == 0 ? kPsGG : kPsAA) + 3 * x;
+      const bool noise = (i == 0 && j == 0) || i >= 1;
+      const double cn = i == 0   ? qg * dt * dt
+                        : j == 1 ? qa * dt * dt
+                        : i == 1 ? qa * 0.5 * dt * dt * dt
+                                 : qa * 0.25 * dt * dt * dt * dt;
+      double q[3], c[9], n[3];
+      auto coef = [&](int s, double (&qq)[3], double (&cc)[9], double (&nn)[3]) {
+        const double* R = sS + kPsRec * s;
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+          qq[m] = R[aq + tq * m];
+          nn[m] = R[an + m];
+#pragma unroll
+          for (int b = 0; b < 3; ++b) cc[3 * m + b] = R[ac + tm * m + tb * b];
+        }
+      };
+      coef(0, q, c, n);
+      for (int s = 0; s < ns; ++s) {
+        double p0[9], p1[3], p2[3];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) p0[k] = sP[9 * j + k];
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          p1[b] = sP[a1 + t1 * b];
+          p2[b] = sP[a2 + t2 * b];
+        }
+        double qn[3], cc[9], nn[3];
+        coef(min(s + 1, ns - 1), qn, cc, nn);
+        double T[3], T0[3], T1[3], P[3];
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          const double v = dot3(q[0], p0[b], q[1], p0[3 + b], q[2], p0[6 + b]);
+          const double v2 = fma(h, v, dt * p1[b]) + p2[b];
+          T[b] = i == 0 ? v : i == 1 ? v + p1[b] : v2;
+        }
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          T0[b] = quad_value<0>(T[b]);
+          T1[b] = quad_value<1>(T[b]);
+        }
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          const double v = dot3(T0[0], c[b], T0[1], c[3 + b], T0[2], c[6 + b]);
+          const double v2 = fma(h, v, dt * T1[b]) + T[b];
+          P[b] = j == 0 ? v : j == 1 ? v + T[b] : v2;
+          if (noise) P[b] = fma(cn, n[b], P[b]);
+        }
+        wave_fence();   // the reads of sP above
+        if (pact && i <= j)
+#pragma unroll
+          for (int b = 0; b < 3; ++b) sP[9 * (3 * i + j) + 3 * x + b] = P[b];
+        wave_fence();
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+          q[m] = qn[m];
+          n[m] = nn[m];
+        }
+#pragma unroll
+        for (int k = 0; k < 9; ++k) c[k] = cc[k];
+      }
+    } else if (wave == 1) {
+      const int b = min(lane, 2);
+      for (int s = 0; s < ns; ++s) {
+        const double* R = sS + kPsRec * s;
+        double nJ[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const double m1 = dot3(R[kPsX + 3 * a], J[0], R[kPsX + 3 * a + 1], J[1], R[kPsX + 3 * a + 2], J[2]);
+          const double et = dot3(R[kPsE + a], J[0], R[kPsE + 3 + a], J[1], R[kPsE + 6 + a], J[2]);
+          Jp[a] += fma(Jv[a], dt, -(0.5 * m1 * dt * dt));
+          Jv[a] = fma(-m1, dt, Jv[a]);
+          nJ[a] = fma(-R[kPsJr + 3 * a + b], dt, et);
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) J[a] = nJ[a];
+      }
+    } else if (wave == 2) {
+      const int k = min(lane, 8);
+#pragma unroll 4
+      for (int s = 0; s < ns; ++s) {
+        const double r = sS[kPsRec * s + kPsR + k];
+        Jp[0] += fma(Jv[0], dt, -(0.5 * r * dt * dt));
+        Jv[0] = fma(-r, dt, Jv[0]);
+      }
+    } else {
+      const int k = min(lane, 2);
+#pragma unroll 4
+      for (int s = 0; s < ns; ++s) {
+        const double r = sS[kPsRec * s + kPsRa + k];
+        Jp[0] += fma(Jv[0], dt, 0.5 * r * dt * dt);
+        Jv[0] = fma(r, dt, Jv[0]);
+      }
+    }
+    __syncthreads();
+  }
+  const double dT = dt * (s1 - s0);
+  double* Info = pre + kPreInfo;
+  if (wave == 0) {
+    if (lane < 3)
+      for (int k = 0; k < 3; ++k) pre[kPreDR + 3 * lane + k] = dR[k];
+  } else if (wave == 1) {
+    if (lane < 3)
+      for (int a = 0; a < 3; ++a) {
+        pre[kPreJRg + 3 * a + lane] = J[a];
+        pre[kPreJvg + 3 * a + lane] = Jv[a];
+        pre[kPreJpg + 3 * a + lane] = Jp[a];
+      }
+  } else if (wave == 2) {
+    if (lane < 9) {
+      pre[kPreJva + lane] = Jv[0];
+      pre[kPreJpa + lane] = Jp[0];
+    }
+  } else {
+    if (lane < 3) {
+      pre[kPreDv + lane] = Jv[0];
+      pre[kPreDp + lane] = Jp[0];
+      pre[kPreBa + lane] = ba[lane];
+      pre[kPreBg + lane] = bg[lane];
+    }
+    if (lane == 0) pre[kPreDT] = dT;
+  }
+  // information: the inverse of the 9x9 covariance (Cholesky, a column per lane), the
+  // bias random walk 1 / (sigma^2 dT).  One sample's covariance has rank 6 (the
+  // same accelerometer noise moves velocity and position), so an interval of
+  // fewer than two samples gets NaN information.
+  for (int k = tid; k < 225; k += kPreThreads) {
+    const int r = k / 15, c = k % 15;
+    if (r < 9 && c < 9) continue;
+    double v = 0.0;
+    if (r == c) v = r < 12 ? 1.0 / (sba * sba * dT) : 1.0 / (sbg * sbg * dT);
+    Info[k] = v;
+  }
+  if (tid < 9) {
+    double cov[81];
+#pragma unroll
+    for (int r = 0; r < 9; ++r)
+#pragma unroll
+      for (int c = 0; c < 9; ++c)
+        cov[9 * r + c] = r / 3 <= c / 3 ? sP[9 * (3 * (r / 3) + c / 3) + 3 * (r % 3) + c % 3]
+                                        : sP[9 * (3 * (c / 3) + r / 3) + 3 * (c % 3) + r % 3];
+    const bool ok = s1 - s0 >= 2 && chol_n(cov, 9);
+    double e[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) e[k] = k == tid ? 1.0 : 0.0;
+    if (ok) {
+      lsolve(cov, 9, e);
+      ltsolve(cov, 9, e);
+    } else {
+      for (int k = 0; k < 9; ++k) e[k] = __builtin_nan("");
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) Info[15 * k + tid] = e[k];
+  }
+}
+
+// The same for many factors, one thread each: no lane idles.
+__global__ __launch_bounds__(64) void k_vi_preint_many(int n_factors, const int32_t* sample_begin,
+                                                       const double* gyro, const double* accel, double dt,
+                                                       const double* bias_bar, double sg, double sa, double sbg,
+                                                       double sba, double* out) {
   const int f = blockIdx.x * blockDim.x + threadIdx.x;
   if (f >= n_factors) return;
   double* pre = out + (size_t)kPreStride * f;
@@ -453,7 +741,7 @@ __global__ __launch_bounds__(64) void k_vi_preint(int n_factors, const int32_t* 
 }
 
 // ---------------------------------------------------------------------------
-// IMU factors at the current state: one wave per factor
+// IMU factors at the current state: one workgroup per factor
 // ---------------------------------------------------------------------------
 
 // Factor record in the workspace: H = J^T Lambda J (30 x 30), g = J^T Lambda r
@@ -461,7 +749,11 @@ __global__ __launch_bounds__(64) void k_vi_preint(int n_factors, const int32_t* 
 constexpr int kFH = 0, kFg = 900, kFr = 930, kFc = 945, kFRec = 946;
 static_assert(kFRec <= kViFactorStride, "factor record stride");
 
-__global__ __launch_bounds__(64) void k_vi_fac(ViArgs V, int wbase) {
+// Lane 0's residual and Jacobian take most of it; four waves rather than one share the
+// products: 10.6 us against 14.5 us at nine factors.
+constexpr int kFacThreads = 256;
+
+__global__ __launch_bounds__(kFacThreads) void k_vi_fac(ViArgs V, int wbase) {
   __shared__ double sJ[450], sLJ[450], sI[225], sr[15];
   const int wi = V.win_order[wbase + blockIdx.y];
   const WinDev W = V.win[wi];
@@ -472,8 +764,8 @@ __global__ __launch_bounds__(64) void k_vi_fac(ViArgs V, int wbase) {
   const double* states = (cur ? V.states_b : V.states) + 9 * W.pose_off;
   const double* pre = V.preint + (size_t)kPreStride * f;
   double* F = V.rec + (size_t)kViFactorStride * f;
-  for (int e = lane; e < 450; e += 64) sJ[e] = 0.0;
-  for (int e = lane; e < 225; e += 64) sI[e] = pre[kPreInfo + e];
+  for (int e = lane; e < 450; e += kFacThreads) sJ[e] = 0.0;
+  for (int e = lane; e < 225; e += kFacThreads) sI[e] = pre[kPreInfo + e];
   __syncthreads();
   if (lane == 0) {
     double r[15];
@@ -482,18 +774,20 @@ __global__ __launch_bounds__(64) void k_vi_fac(ViArgs V, int wbase) {
   }
   __syncthreads();
   // Lambda J (15 x 30)
-  for (int e = lane; e < 450; e += 64) {
+  for (int e = lane; e < 450; e += kFacThreads) {
     const int a = e / 30, c = e % 30;
     double v = 0.0;
+#pragma unroll
     for (int k = 0; k < 15; ++k) v += sI[15 * a + k] * sJ[30 * k + c];
     sLJ[e] = v;
   }
   __syncthreads();
   // H and g in one pass over the record's first 930 doubles
-  for (int e = lane; e < 930; e += 64) {
+  for (int e = lane; e < 930; e += kFacThreads) {
     double v = 0.0;
     if (e < 900) {
       const int a = e / 30, c = e % 30;
+#pragma unroll
       for (int k = 0; k < 15; ++k) v += sJ[30 * k + a] * sLJ[30 * k + c];
     } else {
       for (int k = 0; k < 15; ++k) v += sLJ[30 * k + e - 900] * sr[k];
@@ -1065,16 +1359,24 @@ __global__ __launch_bounds__(256) void k_vi_cand(ViArgs V, int wbase) {
 hipError_t launch_vi_preint(int n_factors, const int32_t* sample_begin, const double* gyro, const double* accel,
                             double dt, const double* bias_bar, const double* noise, double* out, hipStream_t st) {
   if (n_factors <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_vi_preint, dim3((n_factors + 63) / 64), dim3(64), 0, st, n_factors, sample_begin, gyro,
-                     accel, dt, bias_bar, noise[0], noise[1], noise[2], noise[3], out);
+  // A workgroup per factor is five times as fast for a window's factors, but a CU holds
+  // four of them and 256 factors of the other kernel: 100 us against 137 us for 2048
+  // factors of 50 samples, 182 us against 139 us for 4096.
+  constexpr int kPreMany = 2048;
+  if (n_factors > kPreMany)
+    hipLaunchKernelGGL(k_vi_preint_many, dim3((n_factors + 63) / 64), dim3(64), 0, st, n_factors, sample_begin,
+                       gyro, accel, dt, bias_bar, noise[0], noise[1], noise[2], noise[3], out);
+  else
+    hipLaunchKernelGGL(k_vi_preint, dim3(n_factors), dim3(kPreThreads), 0, st, sample_begin, gyro, accel, dt,
+                       bias_bar, noise[0], noise[1], noise[2], noise[3], out);
   return hipGetLastError();
 }
 
 void launch_vi_lin(const ViArgs& V, int wbase, int nwin, hipStream_t st) {
   if (nwin <= 0 || V.max_factors <= 0) return;
-  hipLaunchKernelGGL(k_vi_fac, dim3(V.max_factors, nwin), dim3(64), 0, st, V, wbase);
+  hipLaunchKernelGGL(k_vi_fac, dim3(V.max_factors, nwin), dim3(kFacThreads), 0, st, V, wbase);
   // X (9N x (6 n_free + 1) doubles, n_free <= N) in LDS beside the other
-  // arrays when the CU's 160 KB hold both (N <= 14; the limit is raised once
+  // arrays when the CU's 160 KB hold both (N <= 15; the limit is raised once
   // per process, as for the other kernels); otherwise, or if that fails, X
   // stays in the workspace.
   constexpr size_t kLds = 160 * 1024 - 1024;   // less the kernel's static LDS
