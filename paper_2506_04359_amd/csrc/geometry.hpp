@@ -221,4 +221,99 @@ __device__ __forceinline__ void exp_se3(const double* xi, double* T /*3x4*/) {
   }
 }
 
+// a -= b(s, C) m with b(s, C) the s of lane C of the own row of sixteen lanes: one
+// v_fmac_f64 with a row broadcast instead of two lane reads and an fma.  The compiler
+// does not see the DPP reads, so the two wait states that they need after a VALU write
+// of s lead each block (nothing else in the kernels that use it reads by DPP).
+#define BA_FMAC_ROW(d, s, m, c) "v_fmac_f64_dpp %" #d ", -%" #s ", %" #m " row_newbcast:%" #c " row_mask:0xf bank_mask:0xf\n"
+// one broadcast column over two accumulators: a0 -= b(s, C) m0, a1 -= b(s, C) m1
+template <int C>
+__device__ __forceinline__ void sub_row(double& a0, double& a1, double s, double m0, double m1) {
+  __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 2, 3, 5) BA_FMAC_ROW(1, 2, 4, 5)
+                   : "+&v"(a0), "+&v"(a1)
+                   : "v"(s), "v"(m0), "v"(m1), "n"(C));
+}
+template <int C>
+__device__ __forceinline__ void sub_row2(double& a0, double& a1, double& b0, double& b1, double s, double m0,
+                                         double m1) {
+  __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 4, 5, 7) BA_FMAC_ROW(1, 4, 6, 7) BA_FMAC_ROW(2, 4, 5, 8)
+                       BA_FMAC_ROW(3, 4, 6, 8)
+                   : "+&v"(a0), "+&v"(a1), "+&v"(b0), "+&v"(b1)
+                   : "v"(s), "v"(m0), "v"(m1), "n"(C), "n"(C + 1));
+}
+// columns C .. C + 3 of x and y
+template <int C, int N>
+__device__ __forceinline__ void sub_row4(double (&x)[N], double (&y)[N], double s, double m0, double m1) {
+  __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 8, 9, 11) BA_FMAC_ROW(1, 8, 10, 11) BA_FMAC_ROW(2, 8, 9, 12)
+                       BA_FMAC_ROW(3, 8, 10, 12) BA_FMAC_ROW(4, 8, 9, 13) BA_FMAC_ROW(5, 8, 10, 13)
+                           BA_FMAC_ROW(6, 8, 9, 14) BA_FMAC_ROW(7, 8, 10, 14)
+                   : "+&v"(x[C]), "+&v"(y[C]), "+&v"(x[C + 1]), "+&v"(y[C + 1]), "+&v"(x[C + 2]), "+&v"(y[C + 2]),
+                     "+&v"(x[C + 3]), "+&v"(y[C + 3])
+                   : "v"(s), "v"(m0), "v"(m1), "n"(C), "n"(C + 1), "n"(C + 2), "n"(C + 3));
+}
+// columns C .. N - 1 of x and y
+template <int C, int N>
+__device__ __forceinline__ void sub_rows(double (&x)[N], double (&y)[N], double s, double m0, double m1) {
+  if constexpr (C + 3 < N) {
+    sub_row4<C, N>(x, y, s, m0, m1);
+    sub_rows<C + 4, N>(x, y, s, m0, m1);
+  } else if constexpr (C + 1 < N) {
+    sub_row2<C>(x[C], y[C], x[C + 1], y[C + 1], s, m0, m1);
+    sub_rows<C + 2, N>(x, y, s, m0, m1);
+  } else if constexpr (C < N) {
+    sub_row<C>(x[C], y[C], s, m0, m1);
+  }
+}
+// a[C] -= b(s, C) m, C = 0 .. 5
+__device__ __forceinline__ void sub_vec6(double (&a)[6], double s, double m) {
+  __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 6, 7, 8) BA_FMAC_ROW(1, 6, 7, 9) BA_FMAC_ROW(2, 6, 7, 10)
+                       BA_FMAC_ROW(3, 6, 7, 11) BA_FMAC_ROW(4, 6, 7, 12) BA_FMAC_ROW(5, 6, 7, 13)
+                   : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3]), "+&v"(a[4]), "+&v"(a[5])
+                   : "v"(s), "v"(m), "n"(0), "n"(1), "n"(2), "n"(3), "n"(4), "n"(5));
+}
+
+__device__ __forceinline__ void pin(double& v) { __asm__ volatile("" : "+v"(v)); }   // not moved past a block above
+
+// Step J of a Cholesky factorisation of N columns in panels: each row of sixteen lanes
+// holds in w the N entries of the block's rows (lanes 0 to N - 1: row r, its column r
+// being the pivot's) and of columns to solve (the other lanes), in p more columns.
+// Column J of the panels is scaled by the pivot's reciprocal root ir (which takes the
+// pivot's place), then subtracted from the later columns, right-looking, and its
+// products with p's rows 0 to N - 1 from the next block's sums aw (w's lanes) and ap
+// (p's).  The next pivot's root (an estimate and one third-order refinement, as rsqrt
+// takes it) is worked out between the products.  A pivot that is not positive and
+// finite makes it NaN and with it every later pivot; the last root is returned.
+template <int J, int N>
+__device__ __forceinline__ double panel_steps(double (&w)[N], double (&p)[N], double (&aw)[N], double (&ap)[N],
+                                              int row, double ir) {
+  w[J] = row == J ? ir : w[J] * ir;
+  p[J] *= ir;
+  if constexpr (J < N - 1) {
+    constexpr int H = N > 8 ? 4 : 0;   // products before the estimate's first refinement step
+    sub_row<J + 1>(w[J + 1], p[J + 1], w[J], w[J], p[J]);
+    const double d = wave_bcast(w[J + 1], J + 1);
+    double y = __builtin_amdgcn_rsq(d);
+    pin(y);
+    if constexpr (H > 0) sub_row4<0, N>(aw, ap, p[J], w[J], p[J]);
+    double t = y * -d;
+    pin(t);
+    sub_row<H>(aw[H], ap[H], p[J], w[J], p[J]);
+    double e = fma(t, y, 1.0);
+    pin(e);
+    sub_row4<H + 1, N>(aw, ap, p[J], w[J], p[J]);
+    double m = y * e;
+    pin(m);
+    double q = fma(e, 0.375, 0.5);
+    pin(q);
+    sub_rows<H + 5, N>(aw, ap, p[J], w[J], p[J]);
+    double in = fma(m, q, y);
+    pin(in);
+    sub_rows<J + 2, N>(w, p, w[J], w[J], p[J]);
+    return panel_steps<J + 1, N>(w, p, aw, ap, row, in);
+  } else {
+    sub_rows<0, N>(aw, ap, p[J], w[J], p[J]);
+    return ir;
+  }
+}
+
 }  // namespace ba

@@ -1156,75 +1156,16 @@ __global__ __launch_bounds__(kPassAThreads, (sizeof(Real) == 4 ? 2 : 1)) void k_
 // the accumulating workgroups).
 constexpr int kRS = 36;
 
-// Waits for the LDS reads that produced v before anything that uses v: the
-// reads of a step are issued together and waited for once, instead of the
-// compiler's interleaving of each read with its first use.
-template <int N>
-__device__ __forceinline__ void lds_fence(double (&v)[N]) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) __asm__ volatile("" : "+v"(v[i]));
-}
-
-// Upper Cholesky of one symmetric 6x6 block, by one wave: lane l < 36 brings
-// entry (l / 6, l % 6).  Writes the upper triangle of R to D and 1 / R_pp to
-// inv; raises *fail on a non-positive or non-finite pivot.  The lanes put
-// their entries into D, then every lane factors the whole block in registers
-// (the same values in every lane): the serial pivot chain has no cross-lane
-// traffic.
-__device__ __forceinline__ void factor_diag(double a, double* D, double* inv, int* fail) {
-  const int lane = threadIdx.x & 63;
-  if (lane < 36) D[lane] = a;
-  __builtin_amdgcn_wave_barrier();
-  double R[21];   // upper triangle, row-major: row p starts at 6 p - p (p - 1) / 2
-#pragma unroll
-  for (int p = 0, e = 0; p < 6; ++p)
-#pragma unroll
-    for (int q = p; q < 6; ++q, ++e) R[e] = D[6 * p + q];
-  lds_fence(R);
-  __builtin_amdgcn_wave_barrier();
-  double ir6[6];
-#pragma unroll
-  for (int p = 0; p < 6; ++p) {
-    const int rp = 6 * p - p * (p - 1) / 2;   // (p, p)
-    const double d = R[rp];
-    if (!(d > 0.0) || !isfinite(d)) {   // the same in every lane
-      if (lane == 0) *fail = 1;
-      return;
-    }
-    const double ir = rsqrt(d), sd = d * ir;
-    ir6[p] = ir;
-    R[rp] = sd;
-#pragma unroll
-    for (int q = p + 1; q < 6; ++q) R[rp + q - p] *= ir;
-#pragma unroll
-    for (int x = p + 1; x < 6; ++x) {
-      const int rx = 6 * x - x * (x - 1) / 2;
-#pragma unroll
-      for (int q = x; q < 6; ++q) R[rx + q - x] -= R[rp + x - p] * R[rp + q - p];
-    }
-  }
-  // every lane holds the same factor: lane 0 stores it (27 stores instead of
-  // a per-lane selection of its entry)
-  if (lane == 0) {
-#pragma unroll
-    for (int p = 0, e = 0; p < 6; ++p)
-#pragma unroll
-      for (int q = p; q < 6; ++q, ++e) D[6 * p + q] = R[e];
-#pragma unroll
-    for (int p = 0; p < 6; ++p) inv[p] = ir6[p];
-  }
-}
-
 // One item of the trailing update of step k of the blocked Cholesky in the
-// reduction workgroup: RG rows of one block of the upper pairs k < i <= j
-// (S_ij -= R_ki^T R_kj; the next diagonal block is excluded), or, past the
-// npair blocks, of the right-hand side (b_i -= R_ki^T y_k).  A block splits
+// reduction workgroup: RG rows of one block of the upper pairs k + 2 <= i <= j
+// (S_ij -= R_ki^T R_kj; block row k + 1 is the panel waves' own), n block rows, or,
+// past their pairs, of the right-hand side (b_i -= R_ki^T y_k).  A block splits
 // into 6 / RG items: rows 4s, 4s + 1, 2 + s for RG = 3, rows 2s, 2s + 1 for
 // RG = 2, row s for RG = 1, so a row pair is one 128-bit read.  Every read is
 // issued before the first product; each entry is summed over m in order and
 // then subtracted, whatever RG.
 template <int RG>
-__device__ __forceinline__ void trail_item(double* sS, double* sB, int k, int nf, int nt, int npair, int e) {
+__device__ __forceinline__ void trail_item(double* sS, double* sB, int k, int nf, int n, int e) {
   constexpr int G = 6 / RG;
   const int sub = e % G, blkno = e / G;
   int rows[3];
@@ -1240,11 +1181,12 @@ __device__ __forceinline__ void trail_item(double* sS, double* sB, int k, int nf
     rows[0] = sub;
     rows[1] = rows[2] = 0;
   }
+  const int npair = n * (n + 1) / 2;
   const bool rhs = blkno >= npair;
   int i, j = 0;
   if (rhs) i = blkno - npair;
-  else upper_pair(blkno + 1, nt, i, j);
-  const double* A = sS + kRS * blk_index(k, k + 1 + i, nf);
+  else upper_pair(blkno, n, i, j);
+  const double* A = sS + kRS * blk_index(k, k + 2 + i, nf);
   double u[6][RG];
 #pragma unroll
   for (int m = 0; m < 6; ++m) {
@@ -1258,8 +1200,8 @@ __device__ __forceinline__ void trail_item(double* sS, double* sB, int k, int nf
     }
   }
   if (!rhs) {
-    const double* Bm = sS + kRS * blk_index(k, k + 1 + j, nf);
-    double* D = sS + kRS * blk_index(k + 1 + i, k + 1 + j, nf);
+    const double* Bm = sS + kRS * blk_index(k, k + 2 + j, nf);
+    double* D = sS + kRS * blk_index(k + 2 + i, k + 2 + j, nf);
     double v[6][6], d[RG][6];
 #pragma unroll
     for (int m = 0; m < 6; ++m)
@@ -1298,7 +1240,7 @@ __device__ __forceinline__ void trail_item(double* sS, double* sB, int k, int nf
     double yk[6];
 #pragma unroll
     for (int m = 0; m < 6; ++m) yk[m] = sB[6 * k + m];
-    double* bi = sB + 6 * (k + 1 + i);
+    double* bi = sB + 6 * (k + 2 + i);
 #pragma unroll
     for (int r = 0; r < RG; ++r) {
       double v = 0.0;
@@ -1399,9 +1341,8 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
   double* sS = reinterpret_cast<double*>(smem);   // nblk * kRS
   double* sB = sS + nblk * kRS;                   // nS
   double* sD = sB + nS;                           // nS
-  double* sInv = sD + nS;                         // nS: 1 / R_pp of the diagonal blocks
-  int* sFail = reinterpret_cast<int*>(sInv + nS); // 2 ints (one double): failure, freeze
-  double* sMax = sInv + nS + 1;                   // NT / 64 (<= 8): freeze test
+  int* sFail = reinterpret_cast<int*>(sD + nS);   // 2 ints (one double): failure, freeze
+  double* sMax = sD + nS + 1;                     // NT / 64 (<= 8): freeze test
   const int c0 = W.chunk_begin, c1 = W.chunk_end;
   const int ne = nblk * kBS + 2 * nS;
   if (!ADJ && st.frozen) return;
@@ -1504,90 +1445,90 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
 
   // Blocked Cholesky S = R^T R on 6x6 blocks (upper block storage), right-
   // looking.  The right-hand side rides along as one more column, so the
-  // forward substitution R^T y = b happens inside the factorisation.  Wave 0
-  // factors the next diagonal block while the other waves run the trailing
-  // update (one step of look-ahead); the back substitution runs in wave 0.
+  // forward substitution R^T y = b happens inside the factorisation; the back
+  // substitution runs in wave 0.  The chain over the block rows k bounds it.
+  // The first waves keep the columns right of block column 0 and the right-hand
+  // side, a column per lane throughout (kColWave a wave); lanes 0-5 of each row of
+  // sixteen repeat the diagonal block (k, k), in w, and block (k, k + 1), in p.
+  // Block row k is factored and solved in one pass over these panels, whose
+  // products with block (k, k + 1) are the update of block row k + 1: added up in
+  // registers along the way, they keep the other waves' update of the rows below
+  // (with R_{k-1}, meanwhile) off the chain, and one barrier a block row is left (and
+  // one after the panels' reads where two or three waves share them).
+  // At 19 free poses: 47 us with a diagonal factor in one wave, a panel solve and
+  // a trailing update a barrier apart each (3.8k cycles a block row); XXX us so.
   const int wave = tid >> 6, lane = tid & 63;
-  const int lr = lane / 6, lc = lane - 6 * (lane / 6);   // entry of a 6x6 block (lanes 0..35)
   bool failed = sFail[0] != 0;
-  if (!failed && nf > 0 && wave == 0) {
-    double a = lane < 36 ? sS[kRS * blk_index(0, 0, nf) + lane] : 0.0;
-    factor_diag(a, sS + kRS * blk_index(0, 0, nf), sInv, sFail);
-  }
-  __syncthreads();
-  failed = sFail[0] != 0;
-  for (int k = 0; k < nf && !failed; ++k) {
-    const double* Dk = sS + kRS * blk_index(k, k, nf);
-    const double* ik = sInv + 6 * k;
-    const int nt = nf - k - 1;
-    // panel: R_kj = R_kk^-T S_kj for j > k, one thread per column; the last
-    // item is the right-hand side y_k = R_kk^-T b_k
-    for (int e = tid; e <= 6 * nt; e += NT) {
-      double* B;
-      int stride;
-      if (e < 6 * nt) {
-        B = sS + kRS * blk_index(k, k + 1 + e / 6, nf) + e % 6;
-        stride = 6;
-      } else {
-        B = sB + 6 * k;
-        stride = 1;
-      }
-      double col[6], dku[15], iv[6];
+  if (!failed && nf > 0) {
+    constexpr int kColWave = 80;
+    const int nc = 6 * (nf - 1);                        // columns, then the right-hand side
+    const int npw = nc / kColWave + 1;                  // panel waves (at most 3 of 8)
+    const int row = lane & 15;
+    const int oB = nblk * kRS;                          // sB behind sS
+    // the lane's columns of w and p: block column j (kRhs: the right-hand side; 0: none), column c
+    constexpr int kRhs = 1 << 20;
+    int j[2], c[2];
 #pragma unroll
-      for (int i = 0; i < 6; ++i) col[i] = B[stride * i];
-#pragma unroll
-      for (int i = 1, q = 0; i < 6; ++i)
-#pragma unroll
-        for (int m = 0; m < i; ++m, ++q) dku[q] = Dk[6 * m + i];
-#pragma unroll
-      for (int i = 0; i < 6; ++i) iv[i] = ik[i];
-      lds_fence(col);
-      lds_fence(dku);
-      lds_fence(iv);
-      double y[6];
-#pragma unroll
-      for (int i = 0, q = 0; i < 6; ++i) {
-        double v = col[i];
-#pragma unroll
-        for (int m = 0; m < i; ++m, ++q) v -= dku[q] * y[m];
-        y[i] = v * iv[i];
-      }
-#pragma unroll
-      for (int i = 0; i < 6; ++i) B[stride * i] = y[i];
+    for (int q = 0; q < 2; ++q) {
+      const int x = kColWave * wave + 20 * (lane >> 4) + 10 * q + row - 6;
+      j[q] = row < 6 || x > nc ? 0 : x == nc ? kRhs : 1 + x / 6;
+      c[q] = row < 6 ? row : x % 6;
     }
-    __syncthreads();
-    if (wave == 0) {
-      // look-ahead: update and factor the next diagonal block
-      if (nt > 0) {
-        const double* R = sS + kRS * blk_index(k, k + 1, nf);
-        double* Dn = sS + kRS * blk_index(k + 1, k + 1, nf);
-        double a = 0.0;
-        if (lane < 36) {
-          double ra[6], rb[6], dn[1];
+    double w[6], p[6], aw[6], ap[6], aq[6];
 #pragma unroll
-          for (int m = 0; m < 6; ++m) {
-            ra[m] = R[6 * m + lr];
-            rb[m] = R[6 * m + lc];
-          }
-          dn[0] = Dn[lane];
-          lds_fence(ra);
-          lds_fence(rb);
-          lds_fence(dn);
-          double acc = 0.0;
+    for (int i = 0; i < 6; ++i) p[i] = aw[i] = ap[i] = aq[i] = 0.0;
+    for (int k = 0; k < nf; ++k) {
+      if (wave < npw) {
+        const int dk = blk_index(k, k, nf);
+        // where the panels' columns of block row k stand, and of R_{k-1,k+1}
+        int o[2], s[2];
 #pragma unroll
-          for (int m = 0; m < 6; ++m) acc += ra[m] * rb[m];
-          a = dn[0] - acc;
+        for (int q = 0; q < 2; ++q) {
+          s[q] = j[q] == kRhs ? 1 : 6;
+          o[q] = j[q] == kRhs ? oB + 6 * k : kRS * (dk + (j[q] > k ? j[q] - k : 0)) + c[q];
         }
-        factor_diag(a, Dn, sInv + 6 * (k + 1), sFail);
+        if (row < 6) o[1] += k + 1 < nf ? kRS : 0;
+        double sw[6], sp[6], qv[6];
+        const double* Q = sS + kRS * (blk_index(k > 0 ? k - 1 : 0, k > 0 ? k : 0, nf) + (k > 0 && k + 1 < nf)) +
+                          (row < 6 ? row : 0);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+          qv[i] = Q[6 * i];
+          sw[i] = sS[o[0] + s[0] * i];
+          sp[i] = sS[o[1] + s[1] * i];
+        }
+        if (npw > 1) __syncthreads();   // another panel wave's stores below wait for these reads
+        if (k > 0) {   // block (k, k + 1) less R_{k-1,k}^T R_{k-1,k+1}
+#pragma unroll
+          for (int i = 0; i < 6; ++i) aq[i] = 0.0;
+#pragma unroll
+          for (int m = 0; m < 6; ++m) sub_vec6(aq, p[m], qv[m]);
+        }
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+          w[i] = sw[i] + (row < 6 ? ap[i] : aw[i]);
+          p[i] = sp[i] + (row < 6 ? aq[i] : ap[i]);
+          aw[i] = ap[i] = 0.0;
+        }
+        const double ir = panel_steps<0, 6>(w, p, aw, ap, row, rsqrt(wave_bcast(w[0], 0)));
+        if (tid == 0 && !(ir > 0.0 && isfinite(ir))) sFail[0] = 1;
+        // the block's own columns once, its pivots' reciprocals on the diagonal
+        if (j[0] > k || tid < 6) {
+#pragma unroll
+          for (int i = 0; i < 6; ++i) sS[o[0] + s[0] * i] = w[i];
+        }
+        if (j[1] > k) {
+#pragma unroll
+          for (int i = 0; i < 6; ++i) sS[o[1] + s[1] * i] = p[i];
+        }
+      } else {
+        if (npw > 1) __syncthreads();
+        const int n = k > 0 ? nf - k - 1 : 0;   // block rows below k, two items of three rows per block
+        for (int e = tid - 64 * npw; e < n * (n + 3); e += NT - 64 * npw) trail_item<3>(sS, sB, k - 1, nf, n, e);
       }
-    } else {
-      // trailing update over the npair upper blocks and the nt right-hand
-      // side blocks, two items of three rows per block
-      const int npair = nt * (nt + 1) / 2 - 1;
-      for (int e = tid - 64; e < 2 * (npair + nt); e += NT - 64) trail_item<3>(sS, sB, k, nf, nt, npair, e);
+      __syncthreads();
     }
-    __syncthreads();
-    failed = sFail[0] != 0;
+    failed = sFail[0] != 0;   // a failed pivot's NaNs have gone no further than S and b
   }
   // The candidate poses are wave 1's (a window has at most 64 poses): its reads
   // go out while wave 0 substitutes.
@@ -1616,7 +1557,7 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
 #pragma unroll
         for (int m = i + 1; m < 6; ++m, ++q) dku[q] = Dk[6 * i + m];
 #pragma unroll
-      for (int i = 0; i < 6; ++i) iv[i] = sInv[6 * k + i];
+      for (int i = 0; i < 6; ++i) iv[i] = Dk[7 * i];
       const int l = lane < 2 * k ? lane : 0;   // lanes at or past block row k read block row 0
       const double* B = sS + kRS * blk_index(l >> 1, k, nf) + 18 * (l & 1);
 #pragma unroll
@@ -2038,7 +1979,7 @@ size_t pass_b_lds() {
 // The reduce kernel's LDS: the reduced system of the largest window.
 size_t reduce_lds(int max_nf) {
   const int nblk = max_nf * (max_nf + 1) / 2;
-  return (size_t)(nblk * kRS + 18 * max_nf + 11) * sizeof(double);
+  return (size_t)(nblk * kRS + 12 * max_nf + 11) * sizeof(double);
 }
 
 constexpr int kReduceThreads = 512;

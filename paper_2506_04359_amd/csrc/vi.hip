@@ -807,57 +807,6 @@ __global__ __launch_bounds__(kFacThreads) void k_vi_fac(ViArgs V, int wbase) {
 __device__ inline int hx_row(int q) { return q < 6 ? q : 9 + q; }
 __device__ inline int hy_col(int c) { return c < 9 ? 6 + c : 12 + c; }
 
-// A double of another lane of the wave, as a wave-uniform value.
-__device__ __forceinline__ double lane_value(double v, int lane) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = __builtin_amdgcn_readlane((int)b, lane);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-  return __longlong_as_double(((long long)hi << 32) | lo);
-}
-
-// a -= b(s, C) m with b(s, C) the s of lane C of the own row of sixteen lanes: one
-// v_fmac_f64 with a row broadcast instead of two lane reads and an fma.  The compiler
-// does not see the DPP reads, so the two wait states that they need after a VALU write
-// of s lead each block (nothing else in the kernels that use it reads by DPP).
-#define BA_FMAC_ROW(d, s, m, c) "v_fmac_f64_dpp %" #d ", -%" #s ", %" #m " row_newbcast:%" #c " row_mask:0xf bank_mask:0xf\n"
-// one broadcast column over two accumulators: a0 -= b(s, C) m0, a1 -= b(s, C) m1
-template <int C>
-__device__ __forceinline__ void sub_row(double& a0, double& a1, double s, double m0, double m1) {
-  __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 2, 3, 5) BA_FMAC_ROW(1, 2, 4, 5)
-                   : "+&v"(a0), "+&v"(a1)
-                   : "v"(s), "v"(m0), "v"(m1), "n"(C));
-}
-template <int C>
-__device__ __forceinline__ void sub_row2(double& a0, double& a1, double& b0, double& b1, double s, double m0,
-                                         double m1) {
-  __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 4, 5, 7) BA_FMAC_ROW(1, 4, 6, 7) BA_FMAC_ROW(2, 4, 5, 8)
-                       BA_FMAC_ROW(3, 4, 6, 8)
-                   : "+&v"(a0), "+&v"(a1), "+&v"(b0), "+&v"(b1)
-                   : "v"(s), "v"(m0), "v"(m1), "n"(C), "n"(C + 1));
-}
-// columns C .. C + 3 of x and y
-template <int C>
-__device__ __forceinline__ void sub_row4(double (&x)[9], double (&y)[9], double s, double m0, double m1) {
-  __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 8, 9, 11) BA_FMAC_ROW(1, 8, 10, 11) BA_FMAC_ROW(2, 8, 9, 12)
-                       BA_FMAC_ROW(3, 8, 10, 12) BA_FMAC_ROW(4, 8, 9, 13) BA_FMAC_ROW(5, 8, 10, 13)
-                           BA_FMAC_ROW(6, 8, 9, 14) BA_FMAC_ROW(7, 8, 10, 14)
-                   : "+&v"(x[C]), "+&v"(y[C]), "+&v"(x[C + 1]), "+&v"(y[C + 1]), "+&v"(x[C + 2]), "+&v"(y[C + 2]),
-                     "+&v"(x[C + 3]), "+&v"(y[C + 3])
-                   : "v"(s), "v"(m0), "v"(m1), "n"(C), "n"(C + 1), "n"(C + 2), "n"(C + 3));
-}
-// columns C .. 8 of x and y
-template <int C>
-__device__ __forceinline__ void sub_rows(double (&x)[9], double (&y)[9], double s, double m0, double m1) {
-  if constexpr (C < 6) {
-    sub_row4<C>(x, y, s, m0, m1);
-    sub_rows<C + 4>(x, y, s, m0, m1);
-  } else if constexpr (C < 8) {
-    sub_row2<C>(x[C], y[C], x[C + 1], y[C + 1], s, m0, m1);
-    sub_rows<C + 2>(x, y, s, m0, m1);
-  } else if constexpr (C == 8) {
-    sub_row<C>(x[C], y[C], s, m0, m1);
-  }
-}
 // t[i] -= b(r[i], M) m for all nine
 template <int M>
 __device__ __forceinline__ void sub_col(double (&t)[9], const double (&r)[9], double m) {
@@ -882,50 +831,11 @@ __device__ __forceinline__ void sub_chain(double& v, double s, const double (&u)
     __asm__ volatile("s_nop 1\n" BA_FMAC_ROW(0, 1, 2, 3) : "+&v"(v) : "v"(s), "v"(u[8]), "n"(8));
   }
 }
-#undef BA_FMAC_ROW
-
-__device__ __forceinline__ void pin(double& v) { __asm__ volatile("" : "+v"(v)); }   // not moved past a block above
-
-// Step j of the forward sweep (below): column j of the panels scaled by the pivot's
-// reciprocal root ir, then subtracted from the later columns and from the next state's.
-// The next pivot's root (an estimate and one third-order refinement, as rsqrt takes it)
-// is worked out between the products.  A pivot that is not positive and finite makes it
-// NaN and with it every later pivot; the last root is returned.
-template <int J>
-__device__ __forceinline__ double vi_panel_steps(double (&w)[9], double (&p)[9], double (&aw)[9], double (&ap)[9],
-                                                 int row, double ir) {
-  w[J] = row == J ? ir : w[J] * ir;
-  p[J] *= ir;
-  if constexpr (J < 8) {
-    sub_row<J + 1>(w[J + 1], p[J + 1], w[J], w[J], p[J]);
-    const double d = lane_value(w[J + 1], J + 1);
-    double y = __builtin_amdgcn_rsq(d);
-    pin(y);
-    sub_row4<0>(aw, ap, p[J], w[J], p[J]);
-    double t = y * -d;
-    pin(t);
-    sub_row<4>(aw[4], ap[4], p[J], w[J], p[J]);
-    double e = fma(t, y, 1.0);
-    pin(e);
-    sub_row4<5>(aw, ap, p[J], w[J], p[J]);
-    double m = y * e;
-    pin(m);
-    double q = fma(e, 0.375, 0.5);
-    pin(q);
-    double in = fma(m, q, y);
-    pin(in);
-    sub_rows<J + 2>(w, p, w[J], w[J], p[J]);
-    return vi_panel_steps<J + 1>(w, p, aw, ap, row, in);
-  } else {
-    sub_rows<0>(aw, ap, p[J], w[J], p[J]);
-    return ir;
-  }
-}
 template <int I>
 __device__ __forceinline__ void vi_back_steps(const double (&t)[9], const double (&r)[9], double (&u)[9]) {
   double v = t[I];
   sub_chain<I + 1>(v, r[I], u);
-  u[I] = v * lane_value(r[I], I);
+  u[I] = v * wave_bcast(r[I], I);
   if constexpr (I > 0) vi_back_steps<I - 1>(t, r, u);
 }
 
@@ -1169,7 +1079,7 @@ __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
         aw[y] = nw[y];
         ap[y] = row < 9 ? 0.0 : np[y];
       }
-      const double ir = vi_panel_steps<0>(w, p, aw, ap, row, rsqrt(lane_value(w[0], 0)));
+      const double ir = panel_steps<0, 9>(w, p, aw, ap, row, rsqrt(wave_bcast(w[0], 0)));
       ok = __builtin_amdgcn_readfirstlane(ir > 0.0 && isfinite(ir));   // the same in every lane and wave
       if (!ok) break;
       if (tid < 9) {
