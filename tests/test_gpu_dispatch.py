@@ -1,0 +1,38 @@
+"""The rules that choose a kernel's variant by the window's size, at their
+edges: the Schur units of windows with few free poses, and the FP64 tile and
+work-item tables of a batch's size classes."""
+import pytest
+
+import bagen
+from helpers import check_decisions, gpu_solve, gpu_solve_batched, oracle_replay, rel_err
+
+pytestmark = pytest.mark.gpu
+TOL64 = 1e-9
+
+
+def _replay_parity(w, s, g):
+    prob, ref = oracle_replay(w, s, g["trace"])
+    check_decisions(ref, g["trace"])
+    assert abs(g["report"]["final_cost"] - ref.final_cost) <= TOL64 * ref.final_cost
+    assert rel_err(g["poses"], ref.poses) <= TOL64 and rel_err(g["points"], ref.points) <= TOL64
+
+
+@pytest.mark.parametrize("n_free", [1, 2, 4, 5, 7, 8, 9, 10])
+def test_schur_units_of_few_free_poses(n_free):
+    # off-diagonal blocks n (n - 1) / 2: a thread per entry up to 7 blocks (4 free poses),
+    # per three columns up to 21 (7), per row up to 42 (9), two rows above
+    import paper_2506_04359_amd as ba
+    w = bagen.tiny_window(seed=8100 + n_free, n_kf=n_free + 2, n_lm=150, noise=0.5, fixed=(0, 1))
+    s = ba.Settings(max_iters=6, precision=ba.BA_FP64)
+    _replay_parity(w, s, gpu_solve(w, s))
+
+
+@pytest.mark.parametrize("chunk_obs", [512, 2048])
+def test_fp64_batch_of_every_size_class(chunk_obs):
+    # up to 23 free poses 256-pair tiles, above 64-pair tiles, in one batch
+    import paper_2506_04359_amd as ba
+    ws = [bagen.tiny_window(seed=8200 + n, n_kf=n + 2, n_lm=300, noise=0.5, fixed=(0, 1)) for n in (6, 12, 23, 24, 28)]
+    s = ba.Settings(max_iters=5, precision=ba.BA_FP64)
+    for w, g in zip(ws, gpu_solve_batched(ws, s, chunk_obs=chunk_obs)):
+        assert g["report"]["status"] == 0
+        _replay_parity(w, s, g)
