@@ -14,12 +14,14 @@
 //              chunk's private partial of S = U* - sum Z Z^T and of the reduced
 //              right-hand side in LDS
 //   sum        per window: the chunk partials added in FP64 in chunk order
-//   reduce     per window: sum the chunk partials in FP64 in a fixed order,
-//              damp, blocked Cholesky (6x6 blocks) of S, two triangular solves,
+//   reduce     per window: damp, blocked Cholesky (6x6 blocks) of S, two triangular solves,
 //              candidate poses T' = Exp(dp) T
 //   pass_b     per chunk: re-linearise (cheaper than storing W), back-substitute
 //              dl_j, candidate points, robust cost of the candidate
-//   accept     per window: compare costs, update lambda, switch state buffers
+//   accept     per window: compare costs, update lambda, switch state buffers;
+//              done by every wave of the next pass_a for itself (the last one
+//              by finalize), a launch only for windows of very many chunks
+//              and in the per-stage timing solve
 //
 // The observation stream is coalesced SoA (du, dv, w) in landmark-major order.
 // Within a workgroup, a tile of at most TP pairs is handled one thread per pair

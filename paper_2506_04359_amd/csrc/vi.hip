@@ -749,12 +749,14 @@ __global__ __launch_bounds__(64) void k_vi_preint_many(int n_factors, const int3
 constexpr int kFH = 0, kFg = 900, kFr = 930, kFc = 945, kFRec = 946;
 static_assert(kFRec <= kViFactorStride, "factor record stride");
 
-// Lane 0's residual and Jacobian take most of it; four waves rather than one share the
-// products: 10.6 us against 14.5 us at nine factors.
+// Lane 0's residual and Jacobian take most of it, from LDS, where all lanes put what it
+// reads; four waves rather than one share the products: 14.5 us at nine factors with one
+// wave, 10.6 with four, 9.5 with the staging.
 constexpr int kFacThreads = 256;
 
 __global__ __launch_bounds__(kFacThreads) void k_vi_fac(ViArgs V, int wbase) {
   __shared__ double sJ[450], sLJ[450], sI[225], sr[15];
+  __shared__ double sX[24 + 18 + kPreInfo];   // both poses, both states, the factor's record up to Lambda
   const int wi = V.win_order[wbase + blockIdx.y];
   const WinDev W = V.win[wi];
   const int f = blockIdx.x, lane = threadIdx.x;
@@ -766,10 +768,12 @@ __global__ __launch_bounds__(kFacThreads) void k_vi_fac(ViArgs V, int wbase) {
   double* F = V.rec + (size_t)kViFactorStride * f;
   for (int e = lane; e < 450; e += kFacThreads) sJ[e] = 0.0;
   for (int e = lane; e < 225; e += kFacThreads) sI[e] = pre[kPreInfo + e];
+  if (lane < 24 + 18 + kPreInfo)
+    sX[lane] = lane < 24 ? poses[12 * f + lane] : lane < 42 ? states[9 * f + lane - 24] : pre[lane - 42];
   __syncthreads();
   if (lane == 0) {
     double r[15];
-    imu_factor<true>(poses + 12 * f, states + 9 * f, poses + 12 * (f + 1), states + 9 * (f + 1), pre, V.g, r, sJ);
+    imu_factor<true>(sX, sX + 24, sX + 12, sX + 33, sX + 42, V.g, r, sJ);
     for (int k = 0; k < 15; ++k) sr[k] = r[k];
   }
   __syncthreads();
