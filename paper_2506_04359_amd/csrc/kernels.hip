@@ -1443,6 +1443,9 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
       D[6 * r + c] = D[6 * c + r];
     }
   }
+  // A landmark failure.  Read before the barrier: a pivot failure is raised in the same
+  // word right behind it, and every wave has to go through the same barriers below.
+  bool failed = sFail[0] != 0;
   __syncthreads();
 
   // Blocked Cholesky S = R^T R on 6x6 blocks (upper block storage), right-
@@ -1460,7 +1463,6 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
   // At 19 free poses: 47 us with a diagonal factor in one wave, a panel solve and
   // a trailing update a barrier apart each (3.8k cycles a block row); 41 us so.
   const int wave = tid >> 6, lane = tid & 63;
-  bool failed = sFail[0] != 0;
   if (!failed && nf > 0) {
     constexpr int kColWave = 80;
     const int nc = 6 * (nf - 1);                        // columns, then the right-hand side
