@@ -281,8 +281,8 @@ __device__ __forceinline__ void pin(double& v) { __asm__ volatile("" : "+v"(v));
 // pivot's place), then subtracted from the later columns, right-looking, and its
 // products with p's rows 0 to N - 1 from the next block's sums aw (w's lanes) and ap
 // (p's).  The next pivot's root (an estimate and one third-order refinement, as rsqrt
-// takes it) is worked out between the products.  A pivot that is not positive and
-// finite makes it NaN and with it every later pivot; the last root is returned.
+// takes it) is worked out between the products.  A pivot past the first that is not
+// positive and finite makes it NaN and with it every later pivot; the last root is returned.
 template <int J, int N>
 __device__ __forceinline__ double panel_steps(double (&w)[N], double (&p)[N], double (&aw)[N], double (&ap)[N],
                                               int row, double ir) {
@@ -314,6 +314,17 @@ __device__ __forceinline__ double panel_steps(double (&w)[N], double (&p)[N], do
     sub_rows<0, N>(aw, ap, p[J], w[J], p[J]);
     return ir;
   }
+}
+
+// All N steps; false when a pivot is not positive and finite (the same in every lane).
+// The first root is tested too: an infinite first pivot's is 0, and the columns that it
+// scales to zero leave the later pivots finite.
+template <int N>
+__device__ __forceinline__ bool factor_panels(double (&w)[N], double (&p)[N], double (&aw)[N], double (&ap)[N],
+                                              int row) {
+  const double first = rsqrt(wave_bcast(w[0], 0));
+  const double last = panel_steps<0, N>(w, p, aw, ap, row, first);
+  return first > 0.0 && last > 0.0 && isfinite(last);
 }
 
 }  // namespace ba

@@ -1514,8 +1514,8 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
           p[i] = sp[i] + (row < 6 ? aq[i] : ap[i]);
           aw[i] = ap[i] = 0.0;
         }
-        const double ir = panel_steps<0, 6>(w, p, aw, ap, row, rsqrt(wave_bcast(w[0], 0)));
-        if (tid == 0 && !(ir > 0.0 && isfinite(ir))) sFail[0] = 1;
+        const bool ok = factor_panels<6>(w, p, aw, ap, row);
+        if (tid == 0 && !ok) sFail[0] = 1;
         // the block's own columns once, its pivots' reciprocals on the diagonal
         if (j[0] > k || tid < 6) {
 #pragma unroll

@@ -1083,8 +1083,7 @@ __global__ __launch_bounds__(kViLinThreads) void k_vi_lin(ViArgs V, int wbase) {
         aw[y] = nw[y];
         ap[y] = row < 9 ? 0.0 : np[y];
       }
-      const double ir = panel_steps<0, 9>(w, p, aw, ap, row, rsqrt(wave_bcast(w[0], 0)));
-      ok = __builtin_amdgcn_readfirstlane(ir > 0.0 && isfinite(ir));   // the same in every lane and wave
+      ok = __builtin_amdgcn_readfirstlane(factor_panels<9>(w, p, aw, ap, row));   // the same in every lane and wave
       if (!ok) break;
       if (tid < 9) {
 #pragma unroll
