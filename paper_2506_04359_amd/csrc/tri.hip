@@ -12,7 +12,7 @@
 // in LDS too (pixel minus principal point, transform, weight), read once in
 // order: a lane walks its own range, so reading them from memory in every pass
 // touched a cache line per lane and load, and those loads bound the kernel
-// (1 M landmarks, 5.9 M observations, 12 passes: 626 -> 324 us).
+// (1 M landmarks, 5.9 M observations, 12 passes: 607 -> 319 us).
 //   start     the weighted least-squares intersection of the viewing rays,
 //             (sum w (I - d d^T)) p0 = sum w (I - d d^T) c, by a 3x3 FP64
 //             Cholesky; fewer than two views or a pivot <= 1e-10 trace marks
@@ -40,17 +40,12 @@ constexpr int kTriPoseCache = 128;   // (pose, camera) transforms a workgroup ke
 // Stride of a transform's record in doubles: 16 are used, and 18 keep the records 16
 // bytes aligned while records that lanes read together start in different banks.
 constexpr int kTriRec = 18;
-// Waves per SIMD the kernel is compiled for, and the LDS of a workgroup for its
-// transforms and observations.  256 threads: four waves (128 registers, a few
-// spilled) in FP32 measured 324 us against 363 with three, at 1 M landmarks; FP64
-// accumulators would spill 177 registers there, so it keeps three.  Smaller
-// workgroups, for longer tracks, run two.
+// Waves per SIMD the kernel is compiled for.  256 threads: four waves in FP32 measured
+// 320 us against 350 with three, at 1 M landmarks; FP64 accumulators would spill there,
+// so it keeps three.  Smaller workgroups, for longer tracks, are left at what they need
+// (three).
 template <typename Real, int NT>
 constexpr int tri_waves() { return NT < 256 ? 2 : sizeof(Real) == 4 ? 4 : 3; }
-template <typename Real, int NT>
-constexpr int tri_pool() {
-  return (NT == 256 ? (sizeof(Real) == 4 ? 34 : 40) : NT == 128 ? 36 : 20) * 1024;
-}
 
 // Cholesky solve of a 3x3 SPD system stored as (00, 01, 02, 11, 12, 22):
 // x = A^-1 b.  False on a pivot <= floor or a non-finite one.
@@ -88,14 +83,24 @@ struct TriStage {
   const uint8_t* rec;   // record of the composed transform
 };
 
+// The values are there before anything below uses them.
+template <typename T, int N>
+__device__ __forceinline__ void pin_all(T (&v)[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) __asm__ volatile("" : "+v"(v[k]));
+}
+
 // Ray start and LM refinement of landmark j (observations [o0, o1), indices
 // already checked).  COMPOSED: P holds, per (pose i, camera c) at
 // kTriRec ((i - pbase) n_cams + c), the camera record with the world-to-camera
 // transform T_cb T_bw_i in place of T_cb (so the point goes to the camera in
 // one transform and A R_cw is the Jacobian); otherwise P holds the poses
 // (at 12 (i - pbase)) and the cameras come from sCam.  STAGED (composed): the
-// observations come from G.
-template <typename Real, bool COMPOSED, bool STAGED>
+// observations come from G.  TIGHT (neither): the registers of four waves per SIMD.
+// Left to the compiler they spilled 14, which the loop over the observations read back
+// (200 poses in no order, 3.2 M landmarks of two views, 10 attempts: 975 us against 754
+// with three waves and no spill; 738 us so).
+template <typename Real, bool COMPOSED, bool STAGED, bool TIGHT = false>
 __device__ __forceinline__ void tri_landmark(const TriArgs& A, int j, long long o0, long long o1,
                                              const double* sCam, const double* P, int pbase, const TriStage& G) {
   const DevSettings S = A.settings;
@@ -213,9 +218,18 @@ __device__ __forceinline__ void tri_landmark(const TriArgs& A, int j, long long 
     for (int k = 0; k < 3; ++k) g[k] = 0;
     F = 0.0;
     nbad = 0;
-    Ob cur = load(o0);
+    long long first = o0;
+    // the first observation's addresses are formed anew in each pass
+    if constexpr (TIGHT) __asm__ volatile("" : "+v"(first));
+    Ob cur = load(first);
     for (long long o = o0; o < o1; ++o) {
+      double T[COMPOSED ? 1 : 12];
+      if constexpr (!COMPOSED) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) T[k] = P[12 * cur.i + k];
+      }
       const Ob nxt = load(o + 1 < o1 ? o + 1 : o);
+      if constexpr (TIGHT) pin_all(T);   // all reads go out first, none after a wait for another
       Real J0[3], J1[3];
       Lin<Real> L;
       if constexpr (COMPOSED) {
@@ -229,17 +243,20 @@ __device__ __forceinline__ void tri_landmark(const TriArgs& A, int j, long long 
           J1[b] = L.a1[b];
         }
       } else {
-        const double* T = P + 12 * cur.i;
         const double* C = sCam + 16 * cur.c;
         double xb[3];
+        Real R[9];   // R_i
 #pragma unroll
         for (int a = 0; a < 3; ++a) xb[a] = T[4 * a] * q[0] + T[4 * a + 1] * q[1] + T[4 * a + 2] * q[2] + T[4 * a + 3];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) R[k] = (Real)T[4 * (k / 3) + k % 3];
+        if constexpr (TIGHT) pin_all(R);   // in FP32 over the linearisation: half the registers
         L = linearise<Real>(xb, C, cur.u - C[2], cur.v - C[3], cur.w, S.huber_delta);
         // J rows = (rows of A R_c) R_i
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
-          J0[b] = L.a0[0] * (Real)T[b] + L.a0[1] * (Real)T[4 + b] + L.a0[2] * (Real)T[8 + b];
-          J1[b] = L.a1[0] * (Real)T[b] + L.a1[1] * (Real)T[4 + b] + L.a1[2] * (Real)T[8 + b];
+          J0[b] = L.a0[0] * R[b] + L.a0[1] * R[3 + b] + L.a0[2] * R[6 + b];
+          J1[b] = L.a1[0] * R[b] + L.a1[1] * R[3 + b] + L.a1[2] * R[6 + b];
         }
       }
       nbad += (L.Z > S.min_depth) ? 0 : 1;
@@ -328,14 +345,21 @@ __device__ __forceinline__ void tri_landmark(const TriArgs& A, int j, long long 
   }
 }
 
+constexpr int kTriBins = 64;
+// The kernel's static LDS: cameras, bins, order, ranges.
+template <int NT>
+constexpr int tri_static_lds() {
+  return kMaxCams * 16 * 8 + 4 * (kTriBins + NT) + (NT / 64) * (3 * 4 + 2 * 8);
+}
+
 template <typename Real, int NT>
-__global__ __launch_bounds__(NT, (tri_waves<Real, NT>())) void k_tri(TriArgs A) {
-  constexpr int NW = NT / 64, kBins = 64;
+__global__ __launch_bounds__(NT, (tri_waves<Real, NT>())) void k_tri(TriArgs A, int pool) {
+  constexpr int NW = NT / 64, kBins = kTriBins;
   __shared__ double sCam[kMaxCams * 16];
-  __shared__ __align__(16) unsigned char sPool[tri_pool<Real, NT>()];   // transforms, then the observations
+  extern __shared__ __align__(16) unsigned char sPool[];   // `pool` bytes: transforms, then the observations
   __shared__ int sBin[kBins];
   __shared__ int sOrder[NT];
-  __shared__ int sRange[2][NW];
+  __shared__ int sRange[3][NW];
   __shared__ long long sObs[2][NW];
   const int tid = threadIdx.x;
   for (int k = tid; k < A.n_cams * 16; k += NT) sCam[k] = A.cams[k];
@@ -404,12 +428,13 @@ __global__ __launch_bounds__(NT, (tri_waves<Real, NT>())) void k_tri(TriArgs A) 
   // no order, or a very long track, gives a range that does not fit.)
   const long long nobs = omax > omin ? omax - omin : 0;
   const int per = A.obs_w ? 25 : 17;   // bytes of one observation: two doubles, a byte [, the weight]
-  const bool maybe = nobs > 0 && nobs * per + 32 <= (tri_pool<Real, NT>());
+  const bool maybe = nobs > 0 && nobs * per + 32 <= pool;
 
   // structure checks and the range of pose indices: over the workgroup's
   // observations in order when they are to be staged (those of no valid index are
   // marked below), else over each landmark's own
   int pmin = 0x7fffffff, pmax = -1;
+  bool bad = false;
   auto look = [&](long long o) {
     const int i = A.obs_pose[o], c = A.obs_cam ? A.obs_cam[o] : 0;
     const bool ok = i >= 0 && i < A.n_poses && c >= 0 && c < A.n_cams;
@@ -420,7 +445,7 @@ __global__ __launch_bounds__(NT, (tri_waves<Real, NT>())) void k_tri(TriArgs A) 
     return ok;
   };
   if (maybe) {
-    for (long long o = omin + tid; o < omax; o += NT) look(o);
+    for (long long o = omin + tid; o < omax; o += NT) bad = !look(o) || bad;
   } else {
     for (long long o = o0; o < o1; ++o)
       if (!look(o)) status = 2;
@@ -431,15 +456,18 @@ __global__ __launch_bounds__(NT, (tri_waves<Real, NT>())) void k_tri(TriArgs A) 
     pmin = a < pmin ? a : pmin;
     pmax = b > pmax ? b : pmax;
   }
+  bad = __any(bad);
   if ((tid & 63) == 0) {
     sRange[0][tid >> 6] = pmin;
     sRange[1][tid >> 6] = pmax;
+    sRange[2][tid >> 6] = bad;
   }
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
     pmin = sRange[0][w] < pmin ? sRange[0][w] : pmin;
     pmax = sRange[1][w] > pmax ? sRange[1][w] : pmax;
+    bad = bad || sRange[2][w] != 0;
   }
   // only indices checked against n_poses count, so [pmin, pmax] is in range;
   // compose T_cb T_bw_i for every (pose, camera) the range holds
@@ -447,9 +475,8 @@ __global__ __launch_bounds__(NT, (tri_waves<Real, NT>())) void k_tri(TriArgs A) 
   const bool cached = span > 0 && span <= kTriPoseCache;
   double* sComp = reinterpret_cast<double*>(sPool);
   const int oD = cached ? (int)span * kTriRec * 8 : 0;   // bytes of the transforms, a multiple of 16
-  static_assert(kTriPoseCache * kTriRec * 8 <= (tri_pool<Real, NT>()), "the transforms fit the pool");
   static_assert(kTriPoseCache <= 255, "a staged observation's record is a byte, 255 marks a bad index");
-  const bool staged = maybe && cached && oD + nobs * per <= (tri_pool<Real, NT>());
+  const bool staged = maybe && cached && oD + nobs * per <= pool;
   if (cached) {
     const int n = (int)span;
     for (int r = tid; r < n; r += NT) {
@@ -494,9 +521,9 @@ __global__ __launch_bounds__(NT, (tri_waves<Real, NT>())) void k_tri(TriArgs A) 
   __syncthreads();
   if (j >= A.n_points) return;
   if (staged) {
-    for (long long o = o0; o < o1; ++o)
+    for (long long o = o0; bad && o < o1; ++o)
       if (sRec[o - omin] == 255) status = 2;
-  } else if (maybe) {   // looked at in order above: this landmark's own still have to be
+  } else if (maybe && bad) {   // looked at in order above: this landmark's own still have to be
     for (long long o = o0; o < o1; ++o) {
       const int i = A.obs_pose[o], c = A.obs_cam ? A.obs_cam[o] : 0;
       if (i < 0 || i >= A.n_poses || c < 0 || c >= A.n_cams) status = 2;
@@ -527,26 +554,49 @@ __global__ __launch_bounds__(NT, (tri_waves<Real, NT>())) void k_tri(TriArgs A) 
   else if (cached)
     tri_landmark<Real, true, false>(A, j, o0, o1, sCam, sComp, pmin, G);
   else
-    tri_landmark<Real, false, false>(A, j, o0, o1, sCam, A.poses, 0, G);
+    tri_landmark<Real, false, false, (NT == 256 && sizeof(Real) == 4)>(A, j, o0, o1, sCam, A.poses, 0, G);
 }
 
 template <typename Real, int NT>
-static hipError_t launch_tri(const TriArgs& A) {
+static hipError_t launch_tri(const TriArgs& A, int pool) {
   const int blocks = (A.n_points + NT - 1) / NT;
-  hipLaunchKernelGGL((k_tri<Real, NT>), dim3(blocks), dim3(NT), 0, (hipStream_t)A.stream, A);
+  hipLaunchKernelGGL((k_tri<Real, NT>), dim3(blocks), dim3(NT), pool, (hipStream_t)A.stream, A, pool);
   return hipGetLastError();
 }
 
-// The largest workgroup whose share of the observations (by the mean per landmark,
-// an eighth to spare) fits its LDS beside about 40 transforms.
+// The pool of an NT-thread workgroup when `count` of them share a CU's LDS.
+template <int NT>
+constexpr int tri_pool(int count) {
+  constexpr int kLds = 160 * 1024, kUnit = 1280;   // a CU's LDS, and the unit it is given out in
+  return kLds / count / kUnit * kUnit - tri_static_lds<NT>() - 128;
+}
+static_assert(kTriPoseCache * kTriRec * 8 <= tri_pool<256>(4) && kTriPoseCache * kTriRec * 8 <= tri_pool<128>(6) &&
+                  kTriPoseCache * kTriRec * 8 <= tri_pool<64>(6),
+              "the transforms fit every pool");
+
+// The largest count, max_count down to min_count, whose pool holds the observations of
+// NT landmarks (by the mean per landmark, a sixteenth to spare) beside `poses`
+// transforms; 0 when none does.
+template <int NT>
+static int tri_fit(double bytes, int poses, int max_count, int min_count) {
+  for (int count = max_count; count >= min_count; --count)
+    if (NT * bytes * 1.0625 + poses * (kTriRec * 8.0) <= tri_pool<NT>(count)) return count;
+  return 0;
+}
+
+// Workgroup size and pool by the bytes of a landmark's observations: the kernel waits
+// for memory and LDS most of the time, so what counts is how many landmarks a CU holds.
+// 256 threads while three workgroups hold theirs (8 views without weights: a fixed 36 KB
+// for 128 threads, three to a CU, took 359 us for 600 k landmarks, the unstaged kernel
+// 357, this 246), 128 while four do (12 views: 345, 565, 304 us for 400 k), and 64 above,
+// six to a CU while those fit and otherwise five (30 views: 600, 1040, 539 us for 160 k).
 template <typename Real>
 hipError_t run_triangulate(const TriArgs& A) {
   if (A.n_points <= 0) return hipSuccess;
-  const double bytes = (double)A.n_obs / A.n_points * 1.125 * (A.obs_w ? 25 : 17);
-  const double room = 40.0 * kTriRec * 8;
-  if (256 * bytes + room <= (tri_pool<Real, 256>())) return launch_tri<Real, 256>(A);
-  if (128 * bytes + room <= (tri_pool<Real, 128>())) return launch_tri<Real, 128>(A);
-  return launch_tri<Real, 64>(A);
+  const double bytes = (double)A.n_obs / A.n_points * (A.obs_w ? 25 : 17);
+  if (const int n = tri_fit<256>(bytes, 40, tri_waves<Real, 256>(), 3)) return launch_tri<Real, 256>(A, tri_pool<256>(n));
+  if (const int n = tri_fit<128>(bytes, 40, 6, 4)) return launch_tri<Real, 128>(A, tri_pool<128>(n));
+  return launch_tri<Real, 64>(A, tri_pool<64>(tri_fit<64>(bytes, 24, 6, 6) ? 6 : 5));
 }
 
 template hipError_t run_triangulate<float>(const TriArgs&);

@@ -181,3 +181,42 @@ def test_workgroup_edges(n_kf, n_lm, weighted, bad):
     _check_fp64(b, s, clean, obs_w=w, every=max(1, n_lm // 40))
     assert np.array_equal(clean["points"][keep], g["points"][keep])
     assert np.all(np.isnan(g["points"][marked]))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("track,weighted", [(2, False), (8, False), (8, True), (12, False), (16, False), (40, False)])
+def test_landmarks_over_many_poses(track, weighted, precision):
+    """Tracks over 200 poses in no order: more transforms than a workgroup keeps, in
+    workgroups of 256, 128 and 64 landmarks; a bad index marks its own landmark only."""
+    import paper_2506_04359_amd as ba
+    rng = np.random.default_rng(100 + track)
+    n_pose, n_lm = 200, 300
+    poses = np.tile(np.eye(3, 4), (n_pose, 1, 1))
+    poses[:, 0, 3] = np.linspace(-3, 3, n_pose)
+    pts = np.stack([rng.uniform(-3, 3, n_lm), rng.uniform(-2, 2, n_lm), rng.uniform(6, 15, n_lm)], 1)
+    op = rng.random((n_lm, n_pose)).argsort(1)[:, :track].ravel()
+    oj = np.repeat(np.arange(n_lm), track)
+    x = pts[oj] + poses[op][:, :, 3]
+    uv = 458.0 * x[:, :2] / x[:, 2:] + [367.0, 248.0] + rng.normal(scale=0.4, size=(len(op), 2))
+    w = rng.uniform(0.3, 2.0, len(op)) if weighted else None
+    b = bagen.TriBatch(intrinsics=np.array([[458.0, 458.0, 367.0, 248.0]]), extrinsics=np.eye(3, 4)[None], poses=poses,
+                       points_gt=pts, point_obs_begin=(np.arange(n_lm + 1) * track).astype(np.int32),
+                       obs_pose=op.astype(np.int32), obs_cam=np.zeros(len(op), np.int32), obs_uv=uv,
+                       obs_w=np.ones(len(op)))
+    s = ba.Settings(max_iters=8, precision=ba.BA_FP64 if precision == "fp64" else ba.BA_MIXED)
+    g = _gpu(b, s, obs_w=w)
+    if precision == "fp64":
+        _check_fp64(b, s, g, obs_w=w, every=7)
+    else:
+        for j in range(0, n_lm, 7):
+            ref = tri.triangulate(_obs(b, j, w), _osettings(s))
+            assert g["reports"][j]["status"] == ref.status
+            if ref.status == 0:
+                assert np.abs(g["points"][j] - ref.point).max() <= 1e-6 * max(1.0, np.linalg.norm(ref.point)), j
+    bad = b.obs_pose.copy()
+    bad[[3 * track, 290 * track + track - 1]] = [n_pose, -1]
+    h = _gpu(b, s, obs_w=w, obs_pose=bad)
+    keep = np.setdiff1d(np.arange(n_lm), [3, 290])
+    assert np.flatnonzero(h["reports"]["status"] == 2).tolist() == [3, 290]
+    assert np.array_equal(h["points"][keep], g["points"][keep], equal_nan=True)
+    assert np.all(np.isnan(h["points"][[3, 290]]))
