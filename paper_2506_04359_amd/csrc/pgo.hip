@@ -381,76 +381,94 @@ __global__ __launch_bounds__(kPgoEdgeThreads) void k_pgo_assemble(PgoArgs A) {
 // with the step's records read in one go, partials and blocks in LDS, four tiers and
 // the back substitution in the same groups it takes 254 us.  Same sums in the same
 // order.
-// Phase (1) over the update chunks [q0, q1) and forward chunks [f0, f1).
-__device__ __forceinline__ void pgo_phase1_range(const PgoDev& G, const PgoWork& W, int q0, int q1, int f0, int f1,
-                                                 int t0, int stride) {
+// A column too large for a step: its partials go through memory.  Phase (1) over all its
+// chunks: per update chunk four tasks, of 3 x 3 entries each, per forward chunk six.
+// One entry per task reads three times as much.  With that, the rows of the panel solved
+// by one wave and the column's back substitution by six lanes, an attempt took 4.55 ms on
+// a complete graph of 80 poses and 59 ms on a chain of 1500 with 300 random closures;
+// now 1.91 and 23.7 ms.
+__device__ __forceinline__ void pgo_big_sums(const PgoDev& G, const PgoWork& W, int c, int bd, int n, int t0,
+                                             int stride) {
   double* fpart = W.part + 36 * (long long)G.n_chunks;
-  const int nq = (q1 - q0) * 36;
-  for (int t = t0; t < nq + (f1 - f0) * 6; t += stride) {
+  const int q0 = G.chunk_ptr[bd], nq = (G.chunk_ptr[bd + n] - q0) * 4;
+  const int f0 = G.fchunk_ptr[c], nf = (G.fchunk_ptr[c + 1] - f0) * 6;
+  for (int t = t0; t < nq + nf; t += stride) {
     if (t < nq) {
-      const int q = q0 + t / 36, e = t % 36, a = e / 6, c = e % 6;
-      // the chunk's block pairs in one read (-1 past the list's end; those
-      // entries read the first pair and add nothing)
-      const int32_t* ab = G.chunk_ab + 2 * kPgoChunk * (long long)q;
-      int ia[kPgoChunk], ib[kPgoChunk];
+      const long long q = q0 + t / 4;
+      const int32_t* ab = G.chunk_ab + 2 * kPgoChunk * q;
+      const int r0 = (t & 2) ? 3 : 0, c0 = (t & 1) ? 3 : 0;
+      double acc[9];
 #pragma unroll
+      for (int e = 0; e < 9; ++e) acc[e] = 0.0;
+#pragma unroll 2
       for (int k = 0; k < kPgoChunk; ++k) {
-        ia[k] = ab[k];
-        ib[k] = ab[kPgoChunk + k];
-      }
-      double acc = 0.0;
+        const int ia = ab[k], ib = ab[kPgoChunk + k];
+        const bool on = ia >= 0;
+        const double* La = W.L + 36 * (long long)max(ia, 0) + 6 * r0;
+        const double* Lb = W.L + 36 * (long long)max(ib, 0) + 6 * c0;
+        double la[18], lb[18];
 #pragma unroll
-      for (int k = 0; k < kPgoChunk; ++k) {
-        const bool on = ia[k] >= 0;
-        const double* La = W.L + 36 * (long long)(on ? ia[k] : ia[0]) + 6 * a;
-        const double* Lb = W.L + 36 * (long long)(on ? ib[k] : ib[0]) + 6 * c;
-        double s = 0.0;
+        for (int m = 0; m < 18; ++m) {
+          la[m] = La[m];
+          lb[m] = Lb[m];
+        }
 #pragma unroll
-        for (int m = 0; m < 6; ++m) s += La[m] * Lb[m];
-        acc += on ? s : 0.0;
+        for (int e = 0; e < 9; ++e) {
+          double s = 0.0;
+#pragma unroll
+          for (int m = 0; m < 6; ++m) s += la[6 * (e / 3) + m] * lb[6 * (e % 3) + m];
+          acc[e] += on ? s : 0.0;
+        }
       }
-      W.part[36 * (long long)q + e] = acc;
+      double* out = W.part + 36 * q + 6 * r0 + c0;
+#pragma unroll
+      for (int e = 0; e < 9; ++e) out[6 * (e / 3) + e % 3] = acc[e];
     } else {
-      const int fq = f0 + (t - nq) / 6, a = (t - nq) % 6;
-      const int32_t* bc = G.fchunk_bc + 2 * kPgoChunk * (long long)fq;
-      int ib[kPgoChunk], ik[kPgoChunk];
-#pragma unroll
-      for (int k = 0; k < kPgoChunk; ++k) {
-        ib[k] = bc[k];
-        ik[k] = bc[kPgoChunk + k];
-      }
+      const int u = t - nq, a = u % 6;
+      const long long fq = f0 + u / 6;
+      const int32_t* bc = G.fchunk_bc + 2 * kPgoChunk * fq;
       double acc = 0.0;
 #pragma unroll
       for (int k = 0; k < kPgoChunk; ++k) {
-        const bool on = ib[k] >= 0;
-        const double* Lf = W.L + 36 * (long long)(on ? ib[k] : ib[0]) + 6 * a;
-        const double* yk = W.y + 6 * (on ? ik[k] : ik[0]);
+        const int ib = bc[k], ik = bc[kPgoChunk + k];
+        const double* Lf = W.L + 36 * (long long)max(ib, 0) + 6 * a;
+        const double* yk = W.y + 6 * max(ik, 0);
         double s = 0.0;
 #pragma unroll
         for (int m = 0; m < 6; ++m) s += Lf[m] * yk[m];
-        acc += on ? s : 0.0;
+        acc += ib >= 0 ? s : 0.0;
       }
-      fpart[6 * (long long)fq + a] = acc;
+      fpart[6 * fq + a] = acc;
     }
   }
 }
 
-// Columns too large for a step: the partials go through memory.  Subtracts column c's
-// from its blocks and right-hand side, one entry per thread, in chunk order.
-__device__ __forceinline__ void pgo_big_subtract(const PgoDev& G, const PgoWork& W, int c, int t0, int stride) {
+// v minus p[0], p[stride], ..., p[(n - 1) stride] in order, eight reads in flight.
+__device__ __forceinline__ double minus_list(double v, const double* p, int stride, int n) {
+  for (int q = 0; q < n; q += 8) {
+    double x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = p[(long long)stride * min(q + j, n - 1)];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (q + j < n) v -= x[j];
+  }
+  return v;
+}
+
+// Phase (2) of a large column c: its partials subtracted from its blocks and right-hand
+// side, one entry per thread, in chunk order.
+__device__ __forceinline__ void pgo_big_subtract(const PgoDev& G, const PgoWork& W, int c, int bd, int n, int t0,
+                                                 int stride) {
   const double* fpart = W.part + 36 * (long long)G.n_chunks;
-  const int b0 = G.blk_ptr[c], nb = (G.blk_ptr[c + 1] - b0) * 36;
-  for (int t = t0; t < nb + 6; t += stride) {
-    if (t < nb) {
-      const int b = b0 + t / 36, e = t % 36;
-      double v = W.L[36 * (long long)b + e];
-      for (int q = G.chunk_ptr[b]; q < G.chunk_ptr[b + 1]; ++q) v -= W.part[36 * (long long)q + e];
-      W.L[36 * (long long)b + e] = v;
+  for (int t = t0; t < n * 36 + 6; t += stride) {
+    if (t < n * 36) {
+      const int b = bd + t / 36, e = t % 36, q0 = G.chunk_ptr[b];
+      double* L = W.L + 36 * (long long)b + e;
+      *L = minus_list(*L, W.part + 36 * (long long)q0 + e, 36, G.chunk_ptr[b + 1] - q0);
     } else {
-      const int a = t - nb;
-      double v = W.y[6 * c + a];
-      for (int q = G.fchunk_ptr[c]; q < G.fchunk_ptr[c + 1]; ++q) v -= fpart[6 * (long long)q + a];
-      W.y[6 * c + a] = v;
+      const int a = t - n * 36, f0 = G.fchunk_ptr[c];
+      W.y[6 * c + a] = minus_list(W.y[6 * c + a], fpart + 6 * (long long)f0 + a, 6, G.fchunk_ptr[c + 1] - f0);
     }
   }
 }
@@ -477,25 +495,25 @@ __device__ __forceinline__ bool pgo_chol6(double (&m)[36]) {
   return ok;
 }
 
-// One wave factors a column whose diagonal block and rows (updates subtracted) are at
-// blk (36 per block, the diagonal first) and rhs, and stores the factor and y.  The
-// right-hand side is solved as one more row.
-__device__ __forceinline__ void pgo_column(const PgoWork& W, int c, int bd, int nblk, const double* blk,
-                                           const double* rhs, int lane, int* sfail) {
-  double m[36];
+// Factors the diagonal block at blk (its updates subtracted) in registers, the same in
+// every lane, and solves rows t0, t0 + stride, ... of the column's blocks behind it (36
+// per block) and of rhs, which is one more row, into the factor and y.  A pivot failure
+// is raised instead.
+__device__ __forceinline__ bool pgo_rows(const PgoWork& W, int c, int bd, int nblk, const double* blk,
+                                         const double* rhs, int t0, int stride, int* sfail, double (&m)[36]) {
 #pragma unroll
   for (int i = 0; i < 6; ++i)
 #pragma unroll
     for (int k = 0; k <= i; ++k) m[6 * i + k] = blk[6 * i + k];
   if (!pgo_chol6(m)) {
-    if (lane == 0) {
+    if (t0 == 0) {
       W.istate[4] = 1;
       *sfail = 1;
     }
-    return;
+    return false;
   }
   const int nrow = (nblk - 1) * 6;
-  for (int t = lane; t <= nrow; t += 64) {
+  for (int t = t0; t <= nrow; t += stride) {
     const double* row = t < nrow ? blk + 36 + 6 * t : rhs;
     double* out = t < nrow ? W.L + 36 * (long long)(bd + 1) + 6 * t : W.y + 6 * c;
     double x[6];
@@ -511,13 +529,14 @@ __device__ __forceinline__ void pgo_column(const PgoWork& W, int c, int bd, int 
 #pragma unroll
     for (int k = 0; k < 6; ++k) out[k] = x[k];
   }
-  if (lane == 0) {
-    double* Lc = W.L + 36 * (long long)bd;
+  return true;
+}
+__device__ __forceinline__ void pgo_store_diag(const PgoWork& W, int bd, const double (&m)[36]) {
+  double* Lc = W.L + 36 * (long long)bd;
 #pragma unroll
-    for (int i = 0; i < 6; ++i)
+  for (int i = 0; i < 6; ++i)
 #pragma unroll
-      for (int k = 0; k <= i; ++k) Lc[6 * i + k] = m[6 * i + k];
-  }
+    for (int k = 0; k <= i; ++k) Lc[6 * i + k] = m[6 * i + k];
 }
 
 constexpr int kTreeThreads = 512;
@@ -669,13 +688,16 @@ __device__ __forceinline__ void pgo_tree_factor(const PgoDev& G, const PgoWork& 
     }
     if (R.nq < 0) {   // one large column, through memory
       const int c = R.col.x, bd = R.col.y, n = R.col.z;
-      pgo_phase1_range(G, W, G.chunk_ptr[bd], G.chunk_ptr[bd + n], G.fchunk_ptr[c], G.fchunk_ptr[c + 1], tid,
-                       kTreeThreads);
+      pgo_big_sums(G, W, c, bd, n, tid, kTreeThreads);
       __syncthreads();
-      pgo_big_subtract(G, W, c, tid, kTreeThreads);
+      pgo_big_subtract(G, W, c, bd, n, tid, kTreeThreads);
       __syncthreads();
       if (s + 1 < s1) step_values(W, N, V);
-      if (wave == 0) pgo_column(W, c, bd, n, W.L + 36 * (long long)bd, W.y + 6 * c, lane, &S.fail);
+      // every wave factors the diagonal block and solves its share of the rows in place
+      double m[36];
+      const bool ok = pgo_rows(W, c, bd, n, W.L + 36 * (long long)bd, W.y + 6 * c, tid, kTreeThreads, &S.fail, m);
+      __syncthreads();   // the block has been read by all
+      if (ok && tid == 0) pgo_store_diag(W, bd, m);
     } else {
       // (1) the chunks' sums
       const int nu = R.nq * kUpdTasks, nt = nu + R.nf * kFwdTasks;
@@ -699,7 +721,9 @@ __device__ __forceinline__ void pgo_tree_factor(const PgoDev& G, const PgoWork& 
       for (int i = wave; i < nc; i += kTreeThreads / 64) {
         int4 col = R.col;
         if (i != wave) col = reinterpret_cast<const int4*>(G.step_col)[2 * ((long long)R.c0 + i)];
-        pgo_column(W, col.x, col.y, col.z, S.blk + 36 * col.w, S.rhs + 6 * i, lane, &S.fail);
+        double m[36];
+        if (pgo_rows(W, col.x, col.y, col.z, S.blk + 36 * col.w, S.rhs + 6 * i, lane, 64, &S.fail, m) && lane == 0)
+          pgo_store_diag(W, col.y, m);
       }
     }
     __syncthreads();
@@ -735,12 +759,14 @@ __device__ __forceinline__ void back_fetch(const PgoDev& G, const PgoWork& W, in
   }
   const int i = 10 * wave + lane / 6;
   R.c = -1;
-  if (lane < 60 && i < R.nc) {
-    const int32_t* col = G.step_col + 8 * ((long long)st[6] + i);
-    R.c = col[0];
+  if (R.big || (lane < 60 && i < R.nc)) {   // (a large column's blocks are every thread's)
+    const int32_t* col = G.step_col + 8 * ((long long)st[6] + (R.big ? 0 : i));
     R.bd = col[1];
     R.n = col[2];
     R.b0 = col[3];
+    if (lane < 60 && i < R.nc) R.c = col[0];
+  }
+  if (R.c >= 0) {
     R.y = W.y[6 * R.c + lane % 6];
     const double* D = W.L + 36 * (long long)R.bd;
 #pragma unroll
@@ -772,19 +798,25 @@ __device__ __forceinline__ void pgo_tree_back(const PgoDev& G, const PgoWork& W,
       __syncthreads();
     }
     double v = 0.0;
-    if (R.c >= 0) {
-      v = R.y;
-      for (int k = 1; k < R.n; ++k) {
-        double x = 0.0;
-        if (R.big) {
-          const int r = G.blk_row[R.bd + k];
+    if (R.c >= 0) v = R.y;
+    if (R.big) {   // as many of the column's product rows at a time as there is room for
+      constexpr int kRoom = (int)(sizeof(S.part) / (6 * sizeof(double)));
+      for (int k0 = 1; k0 < R.n; k0 += kRoom) {
+        const int nk = min(kRoom, R.n - k0);
+        for (int t = tid; t < nk * 6; t += kTreeThreads) {
+          const int b = R.bd + k0 + t / 6, r = G.blk_row[b];
+          const double* L = W.L + 36 * (long long)b + t % 6;
+          double x = 0.0;
 #pragma unroll
-          for (int m = 0; m < 6; ++m) x += W.L[36 * (long long)(R.bd + k) + 6 * m + a] * W.x[6 * r + m];
-        } else {
-          x = S.blk[6 * (R.b0 + k) + a];
+          for (int m = 0; m < 6; ++m) x += L[6 * m] * W.x[6 * r + m];
+          S.part[t] = x;
         }
-        v -= x;
+        __syncthreads();
+        if (R.c >= 0) v = minus_list(v, S.part + a, 6, nk);
+        __syncthreads();
       }
+    } else if (R.c >= 0) {
+      for (int k = 1; k < R.n; ++k) v -= S.blk[6 * (R.b0 + k) + a];
     }
     S.v[tid] = v;
     __builtin_amdgcn_wave_barrier();   // the six lanes are of one wave, whose LDS operations stay in order

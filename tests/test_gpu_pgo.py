@@ -14,7 +14,7 @@ import numpy as np
 import pytest
 
 import bagen
-from oracle import pgo
+from oracle import pgo, se3
 from oracle.lm import LMSettings
 
 pytestmark = pytest.mark.gpu
@@ -162,3 +162,53 @@ def test_graph_replays_equal_the_eager_solve():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(P, eager_P) and torch.equal(rep, eager_rep)
+
+
+def _linked(n, ei, ej, seed, fixed=(0,)):
+    """A graph over poses of a loop with the given edges, measurements slightly off."""
+    d = bagen.make_pose_graph(laps=1, per_lap=n, seed=seed, sigma_rot=0.01, sigma_trans=0.05)
+    rng = np.random.default_rng(seed)
+    ei, ej = np.asarray(ei, np.int32), np.asarray(ej, np.int32)
+    D = []
+    for i, j in zip(ei, ej):   # D_ij = T_i^-1 T_j Exp(noise), in the solver's convention T_j = T_i D_ij
+        D.append(pgo.compose(pgo.compose(pgo.inverse(d.poses_gt[i]), d.poses_gt[j]),
+                             se3.exp_se3(rng.normal(scale=0.01, size=6))))
+    fx = np.zeros(n, np.uint8)
+    fx[list(fixed)] = 1
+    return bagen.PoseGraphData(poses_gt=d.poses_gt, poses_init=d.poses_init, edge_i=ei, edge_j=ej, deltas=np.array(D),
+                               edge_w=np.ones(ei.size), pose_fixed=fx, loop=np.zeros(ei.size, bool))
+
+
+def _dense_graph(kind):
+    rng = np.random.default_rng(41)
+    chain = [(k, k + 1) for k in range(399)]
+    if kind == "complete":   # a chain of columns, most of them too large for a step
+        n, e = 80, [(a, b) for a in range(80) for b in range(a + 1, 80)]
+    elif kind == "star":     # one column with 599 forward updates
+        n, e = 600, [(0, k) for k in range(1, 600)]
+    else:                    # large and ordinary steps in turn, several tiers
+        n, e = 400, chain + [tuple(int(v) for v in rng.choice(400, 2, replace=False)) for _ in range(120)]
+    return _linked(n, [a for a, _ in e], [b for _, b in e], 40, fixed=(5,) if kind == "star" else (0,))
+
+
+@pytest.mark.parametrize("kind", ["complete", "star", "random"])
+def test_columns_too_large_for_a_step(kind):
+    import paper_2506_04359_amd as ba
+    d = _dense_graph(kind)
+    s = ba.Settings(max_iters=3, precision=ba.BA_FP64)
+    g = _gpu(d, s)
+    assert g["report"]["accepted"] >= 2 and g["report"]["chol_failures"] == 0
+    _check(d, s, g, backend="sparse" if kind == "random" else "dense")
+
+
+def test_failure_in_a_large_column():
+    """One pose's edges weighted negative in the complete graph: every factorisation
+    fails in a column of its own step, and the poses stay."""
+    import paper_2506_04359_amd as ba
+    d = _dense_graph("complete")
+    w = np.ones(d.n_edges)
+    w[(d.edge_i == 40) | (d.edge_j == 40)] = -1.0
+    s = ba.Settings(max_iters=3, precision=ba.BA_FP64)
+    g = _gpu(d, s, edge_w=w)
+    assert g["report"]["chol_failures"] == 3 and g["report"]["accepted"] == 0
+    assert np.array_equal(g["poses"], d.poses_init)
