@@ -259,9 +259,9 @@ ba_status ba_adjoint(ba_window w, ba_batch b, const ba_settings* s, const double
                      void* stream);
 
 /* Launch shape of a plan's batched solve (one launch per
- * stage and size class).  Defaults: chunk_obs from the plan's size (FP64 solves
- * of small batches use smaller work items than the value reported here, until one is
- * set), tile_pairs 0, every class_chunk_mult 1, class_streams 1. */
+ * stage and size class).  Defaults: chunk_obs from the plan's size (the default stands
+ * for smaller work items in FP64 solves of small batches; any other value is used as
+ * it is), tile_pairs 0, every class_chunk_mult 1, class_streams 1. */
 typedef struct {
   int32_t chunk_obs;            /* target observations per work item, 128..65536 */
   int32_t tile_pairs;           /* pairs per tile: 0 = 256 when its LDS fits, else 64 (in BA_FP64 by

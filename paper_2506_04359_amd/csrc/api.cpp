@@ -341,11 +341,15 @@ bool tables_fit(const ba_batch_s* b, const DeviceTables& t, bool fp64) {
   return true;
 }
 
-// The tables of a plan for work items of chunk_obs (mixed) and chunk_obs_fp64
-// observations.  FP64 solves use 256-pair tiles for the size classes whose
-// partial leaves room for them (up to 23 free poses) and 64-pair tiles for the
+// The tables of a plan for work items of chunk_obs observations.  The default
+// stands for both precisions' own defaults, so a shape that is read and set back is
+// the same shape in either.  FP64 solves use 256-pair tiles for the size classes
+// whose partial leaves room for them (up to 23 free poses) and 64-pair tiles for the
 // others.
-ba_status upload_all(ba_batch_s* b, int chunk_obs, int chunk_obs_fp64) {
+ba_status upload_all(ba_batch_s* b, int chunk_obs) {
+  const size_t nw = b->wins.size();
+  const int chunk_obs_fp64 =
+      chunk_obs == default_chunk_obs(b->n_obs, nw) ? default_chunk_obs_fp64(b->n_obs, nw) : chunk_obs;
   ba_status s = upload_tables(b, 1, kTileLarge, chunk_obs);
   if (s != BA_OK) return s;
   int tp[kClasses];
@@ -421,7 +425,7 @@ ba_status batch_build(std::vector<HostWindow>&& wins, ba_batch_s** out) {
   b->plan.obs_perm = (const int32_t*)(m + o_op);
   b->plan.n_windows = (int32_t)b->wins.size();
   b->chunk_obs = default_chunk_obs(b->n_obs, b->wins.size());
-  const ba_status s = upload_all(b.get(), b->chunk_obs, default_chunk_obs_fp64(b->n_obs, b->wins.size()));
+  const ba_status s = upload_all(b.get(), b->chunk_obs);
   if (s != BA_OK) return s;
   *out = b.release();
   return BA_OK;
@@ -1325,12 +1329,11 @@ ba_status ba_set_launch_config(ba_batch b, const ba_launch_config* cfg) {
   const int old_tp = b->tile_pairs;
   for (int c = 0; c < kClasses; ++c) b->class_mult[c] = cfg->class_chunk_mult[c];
   b->tile_pairs = cfg->tile_pairs;
-  const int old_chunk64 = b->tables[b->fp64_tables].chunk_obs;
-  ba_status s = upload_all(b, cfg->chunk_obs, cfg->chunk_obs);
+  ba_status s = upload_all(b, cfg->chunk_obs);
   if (s != BA_OK) {   // put the previous shape back (best effort: this only fails on OOM)
     for (int c = 0; c < kClasses; ++c) b->class_mult[c] = old_mult[c];
     b->tile_pairs = old_tp;
-    (void)upload_all(b, b->chunk_obs, old_chunk64);
+    (void)upload_all(b, b->chunk_obs);
     return s;
   }
   b->chunk_obs = cfg->chunk_obs;

@@ -36,3 +36,21 @@ def test_fp64_batch_of_every_size_class(chunk_obs):
     for w, g in zip(ws, gpu_solve_batched(ws, s, chunk_obs=chunk_obs)):
         assert g["report"]["status"] == 0
         _replay_parity(w, s, g)
+
+
+def test_launch_shape_read_and_set_back_is_the_same_shape():
+    # the default work items of an FP64 batch are smaller than the mixed ones
+    import paper_2506_04359_amd as ba
+    ws = [bagen.tiny_window(seed=8250 + n, n_kf=n + 2, n_lm=300, noise=0.5, fixed=(0, 1)) for n in (6, 12, 24)]
+    B = ba.Batch([ba.Window.from_problem(w, host_only=True) for w in ws])
+    sizes = lambda: [B.workspace_size(ba.Settings(max_iters=5, precision=p)) for p in (ba.BA_FP64, ba.BA_MIXED)]
+    first, cfg = sizes(), B.get_launch()
+    B.set_launch_config(**cfg)
+    assert sizes() == first
+    B.set_launch_config(**dict(cfg, class_streams=0))
+    assert sizes() == first
+    B.set_launch(16384)
+    one_item = sizes()
+    assert one_item[0] < first[0]   # fewer partials than the default's
+    B.set_launch_config(**cfg)
+    assert sizes() == first and B.get_launch() == cfg
