@@ -1364,8 +1364,10 @@ ba_status ba_autotune(ba_batch b, const ba_settings* s, double* poses, double* p
     cls_obs[size_class(w.n_free)] += w.n_obs;
   }
   std::ostringstream keyss;
-  keyss << prop.gcnArchName << "|" << s->precision << "|" << b->wins.size() << "|" << bucket_of(b->n_obs) << "|"
-        << b->max_nf;
+  // FP64's second grid of shapes (work items from 256 observations, tiles by size
+  // class) has keys of its own: a shape found on the first is slower than the default
+  keyss << prop.gcnArchName << "|" << s->precision << (s->precision == BA_FP64 ? ".2" : "") << "|" << b->wins.size()
+        << "|" << bucket_of(b->n_obs) << "|" << b->max_nf;
   for (int c = 0; c < kClasses; ++c) keyss << "|" << cls_win[c] << ":" << bucket_of(cls_obs[c]);
   const std::string key = keyss.str();
   const char* cache = std::getenv("BA_TUNE_CACHE");

@@ -54,3 +54,28 @@ def test_launch_shape_read_and_set_back_is_the_same_shape():
     assert one_item[0] < first[0]   # fewer partials than the default's
     B.set_launch_config(**cfg)
     assert sizes() == first and B.get_launch() == cfg
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_cached_shapes_of_the_first_fp64_grid_are_not_taken(precision, tmp_path, monkeypatch):
+    # a line of the older FP64 grid would replace a default that is faster; mixed lines stand
+    import numpy as np
+    import torch
+    import paper_2506_04359_amd as ba
+    dev = torch.device("cuda:0")
+    cache = tmp_path / "tune"
+    monkeypatch.setenv("BA_TUNE_CACHE", str(cache))
+    ws = [bagen.tiny_window(seed=8270 + n, n_kf=n + 2, n_lm=200, noise=0.5, fixed=(0, 1)) for n in (4, 8)]
+    s = ba.Settings(max_iters=3, precision=ba.BA_FP64 if precision == "fp64" else ba.BA_MIXED)
+    t = lambda k: torch.tensor(np.concatenate([getattr(w, k) for w in ws]), dtype=torch.float64, device=dev)
+    B = ba.Batch([ba.Window.from_problem(w, host_only=True) for w in ws])
+    mem = torch.empty(4 * B.workspace_size(s), dtype=torch.uint8, device=dev)
+    tune = lambda: B.autotune(s, t("poses_init"), t("points_init"), t("obs_uv"), None, mem)
+    tune()
+    key, *shape = cache.read_text().split()
+    cache.write_text(" ".join([key.replace("|0.2|", "|0|"), "65536", *shape[1:]]) + "\n")
+    chosen = tune()
+    if precision == "mixed":
+        assert chosen == 65536 and B.get_launch()["chunk_obs"] == 65536
+    else:
+        assert chosen != 65536 and cache.read_text().splitlines()[1].split()[0] == key
