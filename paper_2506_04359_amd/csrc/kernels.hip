@@ -1481,8 +1481,10 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
     double w[6], p[6], aw[6], ap[6], aq[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) p[i] = aw[i] = ap[i] = aq[i] = 0.0;
-    for (int k = 0; k < nf; ++k) {
-      if (wave < npw) {
+    // Both sides go through the same barriers, so the branch has to be a scalar one; inside
+    // one loop it cost 0.1 us a block row.
+    if (__builtin_amdgcn_readfirstlane(wave < npw)) {
+      for (int k = 0; k < nf; ++k) {
         const int dk = blk_index(k, k, nf);
         // where the panels' columns of block row k stand, and of R_{k-1,k+1}
         int o[2], s[2];
@@ -1525,12 +1527,15 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
 #pragma unroll
           for (int i = 0; i < 6; ++i) sS[o[1] + s[1] * i] = p[i];
         }
-      } else {
+        __syncthreads();
+      }
+    } else {
+      for (int k = 0; k < nf; ++k) {
         if (npw > 1) __syncthreads();
         const int n = k > 0 ? nf - k - 1 : 0;   // block rows below k, two items of three rows per block
         for (int e = tid - 64 * npw; e < n * (n + 3); e += NT - 64 * npw) trail_item<3>(sS, sB, k - 1, nf, n, e);
+        __syncthreads();
       }
-      __syncthreads();
     }
     failed = sFail[0] != 0;   // a failed pivot's NaNs have gone no further than S and b
   }

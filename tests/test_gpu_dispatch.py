@@ -1,6 +1,7 @@
 """The rules that choose a kernel's variant by the window's size, at their
 edges: the Schur units of windows with few free poses, and the FP64 tile and
 work-item tables of a batch's size classes."""
+import numpy as np
 import pytest
 
 import bagen
@@ -59,7 +60,6 @@ def test_launch_shape_read_and_set_back_is_the_same_shape():
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 def test_cached_shapes_of_the_first_fp64_grid_are_not_taken(precision, tmp_path, monkeypatch):
     # a line of the older FP64 grid would replace a default that is faster; mixed lines stand
-    import numpy as np
     import torch
     import paper_2506_04359_amd as ba
     dev = torch.device("cuda:0")
@@ -79,3 +79,49 @@ def test_cached_shapes_of_the_first_fp64_grid_are_not_taken(precision, tmp_path,
         assert chosen == 65536 and B.get_launch()["chunk_obs"] == 65536
     else:
         assert chosen != 65536 and cache.read_text().splitlines()[1].split()[0] == key
+
+
+def _many_item_window():
+    w = bagen.tiny_window(seed=8601, n_kf=8, n_lm=7000, noise=0.5, fixed=(0, 1))
+    assert w.obs_pose.shape[0] > 300 * 128   # more than 256 work items of 128 observations
+    return w
+
+
+@pytest.mark.parametrize("iters,freeze", [(4, None), (5, None), (9, "grad"), (9, "step")])
+def test_windows_of_more_work_items_than_pass_a_decides_for(iters, freeze):
+    # above 256 work items in any window the acceptance is a launch of its own, for
+    # every window of the solve; the state's two copies end in either parity
+    import math
+    import oracle
+    import paper_2506_04359_amd as ba
+    from helpers import oracle_settings
+    from oracle import lm as olm
+    big = _many_item_window()
+    ws = [bagen.tiny_window(seed=8602, n_kf=5, n_lm=60, noise=0.5, fixed=(0, 1)), big,
+          bagen.tiny_window(seed=8603, n_kf=14, n_lm=120, noise=0.5, fixed=(0, 1))]
+    s = ba.Settings(max_iters=iters, precision=ba.BA_FP64)
+    prob = oracle.Problem.from_window(big)
+    if freeze:   # a tolerance between two values that are far apart in the converging phase
+        run = oracle.lm_solve(big.poses_init, big.points_init, prob, oracle_settings(s), backend="schur")
+        v = []
+        if freeze == "step":
+            v = [t["step_norm"] for t in run.trace if t["accepted"]]
+        else:
+            P, L = big.poses_init, big.points_init
+            for t in run.trace:
+                sy = olm.normal_equations_blocks(P, L, prob, s.huber_delta)
+                v.append(olm.reduced_gradient_norm(sy, "schur", t["lam"], prob.n_free))
+                if t["accepted"]:
+                    P, L = olm.apply_step(P, L, prob, olm.solve_schur(sy, t["lam"], olm._pairs_of_pairs(sy)))
+        k = next(k for k in range(2, len(v)) if v[k] < 0.3 * v[k - 1])
+        setattr(s, freeze + "_tol", math.sqrt(v[k] * v[k - 1]))
+    g = gpu_solve_batched(ws, s, launch=dict(chunk_obs=128, tile_pairs=64))
+    ref = oracle.lm_solve(big.poses_init, big.points_init, prob, oracle_settings(s), backend="schur",
+                          decisions=[bool(a) for a in g[1]["trace"]["accepted"]])
+    check_decisions(ref, g[1]["trace"])
+    assert g[1]["report"]["iters"] == ref.iters and (freeze is None or ref.iters < iters)
+    assert abs(g[1]["report"]["final_cost"] - ref.final_cost) <= TOL64 * ref.final_cost
+    assert rel_err(g[1]["poses"], ref.poses) <= TOL64 and rel_err(g[1]["points"], ref.points) <= TOL64
+    for i in (0, 2):
+        _replay_parity(ws[i], s, g[i])
+        assert np.array_equal(g[i]["poses"], gpu_solve_batched([ws[i]], s, launch=dict(chunk_obs=128, tile_pairs=64))[0]["poses"])

@@ -282,3 +282,26 @@ def test_preintegration_across_the_factor_counts(n):
             assert np.abs(pre[f][off:off + arr.size] - arr).max() <= 1e-12 * max(1.0, np.abs(arr).max()), (f, off)
         Info = imu.imu_information(o, noise)
         assert np.abs(pre[f][67:67 + 225].reshape(15, 15) - Info).max() <= 1e-9 * np.abs(Info).max(), f
+
+
+@pytest.mark.parametrize("n", [6, 2049])
+def test_preintegration_of_large_rotations_per_sample(n):
+    # from 1 rad per sample on the exponential's sine and cosine take the place of its
+    # series, in both kernels
+    import torch
+    import paper_2506_04359_amd as ba
+    rng = np.random.default_rng(9121)
+    dt, m = 0.005, 20
+    ang = np.resize([0.999, 1.0, 1.001, 1.7, math.pi, 5.0], n)
+    ax = rng.normal(size=(n, m, 3))
+    gy = (ang[:, None, None] / dt * ax / np.linalg.norm(ax, axis=2, keepdims=True)).reshape(-1, 3)
+    ac = rng.normal(scale=2.0, size=(n * m, 3)) + np.array([0.0, 0.0, 9.81])
+    dens = (1e-3, 2e-2, 1e-5, 1e-4)
+    t = lambda a, d=torch.float64: torch.tensor(a, dtype=d, device="cuda:0")
+    pre = ba.vi_preintegrate(t(np.arange(n + 1) * m, torch.int32), t(gy), t(ac), dt, t(np.zeros((n, 6))), dens).cpu().numpy()
+    for f in list(range(6)) + [n - 1]:
+        o = imu.preintegrate(gy[m * f:m * f + m], ac[m * f:m * f + m], dt, np.zeros(3), np.zeros(3), imu.ImuNoise(*dens))
+        for arr, off in ((o.dR, 0), (o.dv, 9), (o.dp, 12), (o.J_Rg, 16), (o.J_vg, 25), (o.J_va, 34), (o.J_pg, 43),
+                         (o.J_pa, 52)):
+            arr = arr.reshape(-1)
+            assert np.abs(pre[f][off:off + arr.size] - arr).max() <= 1e-12 * max(1.0, np.abs(arr).max()), (f, off)
