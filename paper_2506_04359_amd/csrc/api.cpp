@@ -92,8 +92,6 @@ struct DeviceTables {
   int32_t* tile_lm_begin = nullptr;
   int32_t* chunk_window = nullptr;
   int32_t* chunk_tile_begin = nullptr;
-  int64_t* chunk_part_off = nullptr;
-  int32_t* chunk_order = nullptr;
   int32_t* pair_rec = nullptr;
   int32_t* tile_rec = nullptr;
   uint32_t* lists = nullptr;
@@ -238,8 +236,6 @@ ba_status upload_tables(ba_batch_s* b, int which, int tp, int chunk_obs, const i
   const size_t o_tile = blob.add(t.tile_lm_begin);
   const size_t o_cw = blob.add(t.chunk_window);
   const size_t o_ct = blob.add(t.chunk_tile_begin);
-  const size_t o_cp = blob.add(t.chunk_part_off);
-  const size_t o_co = blob.add(t.chunk_order);
   const size_t o_wo = blob.add(t.win_order);
   const size_t o_pr = blob.add(t.pair_rec);
   const size_t o_tr = blob.add(t.tile_rec);
@@ -272,8 +268,6 @@ ba_status upload_tables(ba_batch_s* b, int which, int tp, int chunk_obs, const i
   D.tile_lm_begin = (int32_t*)((char*)mem + o_tile);
   D.chunk_window = (int32_t*)((char*)mem + o_cw);
   D.chunk_tile_begin = (int32_t*)((char*)mem + o_ct);
-  D.chunk_part_off = (int64_t*)((char*)mem + o_cp);
-  D.chunk_order = (int32_t*)((char*)mem + o_co);
   D.win_order = (int32_t*)((char*)mem + o_wo);
   D.pair_rec = (int32_t*)((char*)mem + o_pr);
   D.tile_rec = (int32_t*)((char*)mem + o_tr);
@@ -571,9 +565,6 @@ DevTiles dev_tiles(const DeviceTables& t) {
   d.tile_lm_begin = t.tile_lm_begin;
   d.chunk_window = t.chunk_window;
   d.chunk_tile_begin = t.chunk_tile_begin;
-  d.chunk_part_off = t.chunk_part_off;
-  d.chunk_order = t.chunk_order;
-  d.win_order = t.win_order;
   d.pair_rec = t.pair_rec;
   d.tile_rec = t.tile_rec;
   d.lists = t.lists;

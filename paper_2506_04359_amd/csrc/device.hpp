@@ -78,17 +78,14 @@ struct DevPlan {
 };
 
 struct DevTiles {
-  const ChunkRec* chunk_rec;      // per chunk, grouped by size class (as chunk_order)
-  const WinDev* win_rec;          // per window, grouped by size class (as win_order)
-  const int32_t* chunk_order;     // chunks grouped by size class
-  const int32_t* win_order;       // windows grouped by size class
+  const ChunkRec* chunk_rec;      // per chunk, grouped by size class
+  const WinDev* win_rec;          // per window, grouped by size class
   const int32_t* pair_rec;        // 4 per pair position (thread order of its tile)
   const int32_t* tile_rec;        // 8 per tile
   const uint32_t* lists;          // per tile: segment words then products
   const int32_t* tile_lm_begin;
   const int32_t* chunk_window;
   const int32_t* chunk_tile_begin;
-  const int64_t* chunk_part_off;
   int32_t n_chunks;
 };
 

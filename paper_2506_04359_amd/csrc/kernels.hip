@@ -1159,52 +1159,32 @@ __global__ __launch_bounds__(kPassAThreads, (sizeof(Real) == 4 ? 2 : 1)) void k_
 constexpr int kRS = 36;
 
 // One item of the trailing update of step k of the blocked Cholesky in the
-// reduction workgroup: RG rows of one block of the upper pairs k + 2 <= i <= j
-// (S_ij -= R_ki^T R_kj; block row k + 1 is the panel waves' own), n block rows, or,
-// past their pairs, of the right-hand side (b_i -= R_ki^T y_k).  A block splits
-// into 6 / RG items: rows 4s, 4s + 1, 2 + s for RG = 3, rows 2s, 2s + 1 for
-// RG = 2, row s for RG = 1, so a row pair is one 128-bit read.  Every read is
-// issued before the first product; each entry is summed over m in order and
-// then subtracted, whatever RG.
-template <int RG>
+// reduction workgroup: rows 4 sub, 4 sub + 1 and 2 + sub (sub = 0, 1; a row pair is one
+// 128-bit read) of one block of the upper pairs k + 2 <= i <= j (S_ij -= R_ki^T R_kj;
+// block row k + 1 is the panel waves' own), n block rows, or, past their pairs, of the
+// right-hand side (b_i -= R_ki^T y_k).  Every read is issued before the first product;
+// each entry is summed over m in order and then subtracted.
 __device__ __forceinline__ void trail_item(double* sS, double* sB, int k, int nf, int n, int e) {
-  constexpr int G = 6 / RG;
-  const int sub = e % G, blkno = e / G;
-  int rows[3];
-  if (RG == 3) {
-    rows[0] = 4 * sub;
-    rows[1] = 4 * sub + 1;
-    rows[2] = 2 + sub;
-  } else if (RG == 2) {
-    rows[0] = 2 * sub;
-    rows[1] = 2 * sub + 1;
-    rows[2] = 0;
-  } else {
-    rows[0] = sub;
-    rows[1] = rows[2] = 0;
-  }
+  const int sub = e % 2, blkno = e / 2;
+  const int rows[3] = {4 * sub, 4 * sub + 1, 2 + sub};
   const int npair = n * (n + 1) / 2;
   const bool rhs = blkno >= npair;
   int i, j = 0;
   if (rhs) i = blkno - npair;
   else upper_pair(blkno, n, i, j);
   const double* A = sS + kRS * blk_index(k, k + 2 + i, nf);
-  double u[6][RG];
+  double u[6][3];
 #pragma unroll
   for (int m = 0; m < 6; ++m) {
-    if (RG >= 2) {
-      const double2 a01 = *reinterpret_cast<const double2*>(A + 6 * m + rows[0]);
-      u[m][0] = a01.x;
-      u[m][1] = a01.y;
-      if (RG == 3) u[m][RG - 1] = A[6 * m + rows[2]];
-    } else {
-      u[m][0] = A[6 * m + rows[0]];
-    }
+    const double2 a01 = *reinterpret_cast<const double2*>(A + 6 * m + rows[0]);
+    u[m][0] = a01.x;
+    u[m][1] = a01.y;
+    u[m][2] = A[6 * m + rows[2]];
   }
   if (!rhs) {
     const double* Bm = sS + kRS * blk_index(k, k + 2 + j, nf);
     double* D = sS + kRS * blk_index(k + 2 + i, k + 2 + j, nf);
-    double v[6][6], d[RG][6];
+    double v[6][6], d[3][6];
 #pragma unroll
     for (int m = 0; m < 6; ++m)
 #pragma unroll
@@ -1214,26 +1194,26 @@ __device__ __forceinline__ void trail_item(double* sS, double* sB, int k, int nf
         v[m][c + 1] = b2.y;
       }
 #pragma unroll
-    for (int r = 0; r < RG; ++r)
+    for (int r = 0; r < 3; ++r)
 #pragma unroll
       for (int c = 0; c < 6; c += 2) {
         const double2 d2 = *reinterpret_cast<const double2*>(D + 6 * rows[r] + c);
         d[r][c] = d2.x;
         d[r][c + 1] = d2.y;
       }
-    double acc[RG][6];
+    double acc[3][6];
 #pragma unroll
-    for (int r = 0; r < RG; ++r)
+    for (int r = 0; r < 3; ++r)
 #pragma unroll
       for (int c = 0; c < 6; ++c) acc[r][c] = 0.0;
 #pragma unroll
     for (int m = 0; m < 6; ++m)
 #pragma unroll
-      for (int r = 0; r < RG; ++r)
+      for (int r = 0; r < 3; ++r)
 #pragma unroll
         for (int c = 0; c < 6; ++c) acc[r][c] += u[m][r] * v[m][c];
 #pragma unroll
-    for (int r = 0; r < RG; ++r)
+    for (int r = 0; r < 3; ++r)
 #pragma unroll
       for (int c = 0; c < 6; c += 2)
         *reinterpret_cast<double2*>(D + 6 * rows[r] + c) =
@@ -1244,7 +1224,7 @@ __device__ __forceinline__ void trail_item(double* sS, double* sB, int k, int nf
     for (int m = 0; m < 6; ++m) yk[m] = sB[6 * k + m];
     double* bi = sB + 6 * (k + 2 + i);
 #pragma unroll
-    for (int r = 0; r < RG; ++r) {
+    for (int r = 0; r < 3; ++r) {
       double v = 0.0;
 #pragma unroll
       for (int m = 0; m < 6; ++m) v += u[m][r] * yk[m];
@@ -1533,7 +1513,7 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
       for (int k = 0; k < nf; ++k) {
         if (npw > 1) __syncthreads();
         const int n = k > 0 ? nf - k - 1 : 0;   // block rows below k, two items of three rows per block
-        for (int e = tid - 64 * npw; e < n * (n + 3); e += NT - 64 * npw) trail_item<3>(sS, sB, k - 1, nf, n, e);
+        for (int e = tid - 64 * npw; e < n * (n + 3); e += NT - 64 * npw) trail_item(sS, sB, k - 1, nf, n, e);
         __syncthreads();
       }
     }
