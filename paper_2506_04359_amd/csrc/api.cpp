@@ -306,9 +306,9 @@ int default_chunk_obs(int64_t n_obs, size_t n_windows) {
 // Work-item size of FP64 solves.  A batch's aim at n_obs / 1024 observations too,
 // but may be as small as one tile: an FP64 tile takes about twice an FP32 one's
 // time, a workgroup's partial takes most of a CU's LDS, and a small batch in items of
-// 1024 observations leaves CUs idle while few run several tiles in series (with the
-// tiles below: 16 windows, 154 k observations, 10 attempts 6.4 -> 2.0 ms; a training
-// step of 4 windows, 11 k observations, 1.66 -> 1.00 ms).
+// 1024 observations leaves CUs idle while few run several tiles in series (together
+// with the tiles below and the rest of a solve: 16 windows, 154 k observations, 10
+// attempts 5.9 -> 1.7 ms; a training step of 4 windows, 11 k observations, 1.83 -> 0.96 ms).
 int default_chunk_obs_fp64(int64_t n_obs, size_t n_windows) {
   if (n_windows == 1) return default_chunk_obs(n_obs, 1);
   return (int)std::min<int64_t>(8192, std::max<int64_t>(256, n_obs / 1024));

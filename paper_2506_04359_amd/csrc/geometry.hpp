@@ -224,7 +224,10 @@ __device__ __forceinline__ void exp_se3(const double* xi, double* T /*3x4*/) {
 // a -= b(s, C) m with b(s, C) the s of lane C of the own row of sixteen lanes: one
 // v_fmac_f64 with a row broadcast instead of two lane reads and an fma.  The compiler
 // does not see the DPP reads, so the two wait states that they need after a VALU write
-// of s lead each block (nothing else in the kernels that use it reads by DPP).
+// of s lead each block.  Nor does it see the writes: a lane read of a block's output
+// needs one instruction in between and a DPP read or lane swap two.  The one such read is
+// panel_steps's of the next pivot, which sub_row writes first of two; the wave sums and
+// swaps of the kernels that use the blocks read nothing that a block wrote.
 #define BA_FMAC_ROW(d, s, m, c) "v_fmac_f64_dpp %" #d ", -%" #s ", %" #m " row_newbcast:%" #c " row_mask:0xf bank_mask:0xf\n"
 // one broadcast column over two accumulators: a0 -= b(s, C) m0, a1 -= b(s, C) m1
 template <int C>

@@ -1441,7 +1441,7 @@ __global__ __launch_bounds__(NT) void k_reduce(DevPlan P, DevTiles T, DevWork<Re
   // (with R_{k-1}, meanwhile) off the chain, and one barrier a block row is left (and
   // one after the panels' reads where two or three waves share them).
   // At 19 free poses: 47 us with a diagonal factor in one wave, a panel solve and
-  // a trailing update a barrier apart each (3.8k cycles a block row); 41 us so.
+  // a trailing update a barrier apart each (3.8k cycles a block row); 40 us so.
   const int wave = tid >> 6, lane = tid & 63;
   if (!failed && nf > 0) {
     constexpr int kColWave = 80;

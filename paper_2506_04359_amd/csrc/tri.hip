@@ -98,8 +98,8 @@ __device__ __forceinline__ void pin_all(T (&v)[N]) {
 // (at 12 (i - pbase)) and the cameras come from sCam.  STAGED (composed): the
 // observations come from G.  TIGHT (neither): the registers of four waves per SIMD.
 // Left to the compiler they spilled 14, which the loop over the observations read back
-// (200 poses in no order, 3.2 M landmarks of two views, 10 attempts: 975 us against 754
-// with three waves and no spill; 738 us so).
+// (200 poses in no order, 2.4 M landmarks of two views, 10 attempts: 732 us against 563
+// of a kernel of three waves without staging; 537 us so).
 template <typename Real, bool COMPOSED, bool STAGED, bool TIGHT = false>
 __device__ __forceinline__ void tri_landmark(const TriArgs& A, int j, long long o0, long long o1,
                                              const double* sCam, const double* P, int pbase, const TriStage& G) {
