@@ -186,19 +186,22 @@ def _dense_graph(kind):
         n, e = 80, [(a, b) for a in range(80) for b in range(a + 1, 80)]
     elif kind == "star":     # one column with 599 forward updates
         n, e = 600, [(0, k) for k in range(1, 600)]
-    else:                    # large and ordinary steps in turn, several tiers
+    elif kind == "clusters":   # large steps in the first tier's groups already
+        n, e = 250, [(50 * c + a, 50 * c + b) for c in range(5) for a in range(50) for b in range(a + 1, 50)]
+        e += [(50 * c - 1, 50 * c) for c in range(1, 5)]
+    else:                    # large and ordinary steps in turn
         n, e = 400, chain + [tuple(int(v) for v in rng.choice(400, 2, replace=False)) for _ in range(120)]
     return _linked(n, [a for a, _ in e], [b for _, b in e], 40, fixed=(5,) if kind == "star" else (0,))
 
 
-@pytest.mark.parametrize("kind", ["complete", "star", "random"])
+@pytest.mark.parametrize("kind", ["complete", "star", "clusters", "random"])
 def test_columns_too_large_for_a_step(kind):
     import paper_2506_04359_amd as ba
     d = _dense_graph(kind)
     s = ba.Settings(max_iters=3, precision=ba.BA_FP64)
     g = _gpu(d, s)
     assert g["report"]["accepted"] >= 2 and g["report"]["chol_failures"] == 0
-    _check(d, s, g, backend="sparse" if kind == "random" else "dense")
+    _check(d, s, g, backend="sparse" if kind in ("clusters", "random") else "dense")
 
 
 def test_failure_in_a_large_column():
